@@ -18,13 +18,16 @@ LIB = os.path.join(HERE, "libpfc_hip.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["kernels.hip", "smooth.hip", "residual.hip", "runtime.cpp", "mixed.cpp", "timeloop.cpp", "adjoint.hip", "batch.cpp", "noalloc.hip"]
+SOURCES = ["brick.hip", "brick_mob.hip", "brick_f32.hip", "brick_adj.hip", "kernels.hip", "smooth.hip",
+           "residual.hip", "tail.hip", "runtime.cpp", "mixed.cpp", "timeloop.cpp", "adjoint.hip",
+           "batch.cpp", "noalloc.hip"]
 
 # Contraction off: every kernel evaluates a formula exactly as written, so
 # kernels that share a formula (the half-sweep and the fused sweep) agree
 # bitwise.
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", f"--offload-arch={ARCH}",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-fconstexpr-steps=100000000",  # the brick kernels' point lists
          "-Wall", "-Wno-unused-result", "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

@@ -38,11 +38,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_D(Lay lay, double eps, const dou
     D[sidx32(lay, i, j, k)] = Cubic<false>::dg(phin[t], phk[t], 0.0) + 0.5 * (1.0 - eps);
 }
 
-// Red-black block Gauss-Seidel on J^T: at a point, with the six neighbours held,
-//     lambda1 - c lambda2 + Dd lambda3 = s1 = b1 + S_l3 / (2 h^2)
-//     A lambda1 + lambda2              = s2 = b2 + tau S_l1 / h^2
-//     B lambda2 + lambda3              = s3 = b3 + S_l2 / h^2
-// (A = 6 tau/h^2, B = 6/h^2, Dd = 3/h^2, c = D at the point).
+// Red-black block Gauss-Seidel on J^T, one colour (adj_point_solve).
 __global__ __launch_bounds__(kBlock) void k_adj_smooth(OpParams op, int colour, Tri<double> lam,
                                                        Tri<const double> b,
                                                        const double *__restrict__ D) {
@@ -57,30 +53,27 @@ __global__ __launch_bounds__(kBlock) void k_adj_smooth(OpParams op, int colour, 
     const int j = (int)(row - (unsigned)k * (unsigned)n);
     const int i = 2 * m + ((colour + j + k) & 1);
     const Off q = offs(L, i, j, k);
-    const double s1 = b.a[q.c] + 0.5 * nsum(lam.c, q) * op.h2inv;
-    const double s2 = b.b[q.c] + op.tau * nsum(lam.a, q) * op.h2inv;
-    const double s3 = b.c[q.c] + nsum(lam.b, q) * op.h2inv;
-    const double A = 6.0 * op.tau * op.h2inv, B = 6.0 * op.h2inv, Dd = 3.0 * op.h2inv;
-    const double c = D[q.c];
-    const double l1 = (s1 + (c + B * Dd) * s2 - Dd * s3) / (1.0 + A * (c + B * Dd));
-    const double l2 = s2 - A * l1;
-    const double l3 = s3 - B * l2;
-    lam.a[q.c] = l1;
-    lam.b[q.c] = l2;
-    lam.c[q.c] = l3;
+    const double s[3] = {nsum(lam.a, q), nsum(lam.b, q), nsum(lam.c, q)};
+    double l[3];
+    adj_point_solve(op, D[q.c], b.a[q.c], b.b[q.c], b.c[q.c], s, l);
+    lam.a[q.c] = l[0];
+    lam.b[q.c] = l[1];
+    lam.c[q.c] = l[2];
 }
 
 // r = b - J^T lambda at one point.
 __device__ __forceinline__ void adj_resid_at(const OpParams &op, const Tri<const double> &lam,
                                              const Tri<const double> &b, const double *D,
                                              const Off &q, double &r1, double &r2, double &r3) {
-    const double l1 = lam.a[q.c], l2 = lam.b[q.c], l3 = lam.c[q.c];
-    const double L1 = (nsum(lam.a, q) - 6.0 * l1) * op.h2inv;
-    const double L2 = (nsum(lam.b, q) - 6.0 * l2) * op.h2inv;
-    const double L3 = (nsum(lam.c, q) - 6.0 * l3) * op.h2inv;
-    r1 = b.a[q.c] - (l1 - D[q.c] * l2 - 0.5 * L3);
-    r2 = b.b[q.c] - (l2 - op.tau * L1);
-    r3 = b.c[q.c] - (l3 - L2);
+    const double w[3] = {lam.a[q.c], lam.b[q.c], lam.c[q.c]};
+    const double ls[3] = {(nsum(lam.a, q) - 6.0 * w[0]) * op.h2inv,
+                          (nsum(lam.b, q) - 6.0 * w[1]) * op.h2inv,
+                          (nsum(lam.c, q) - 6.0 * w[2]) * op.h2inv};
+    double r[3];
+    adj_resid_from_lap(op, ls, w, b.a[q.c], b.b[q.c], b.c[q.c], D[q.c], r);
+    r1 = r[0];
+    r2 = r[1];
+    r3 = r[2];
 }
 
 __global__ __launch_bounds__(kBlock) void k_adj_resid_max(OpParams op, Tri<const double> lam,

@@ -183,34 +183,66 @@ __device__ __forceinline__ unsigned long long umax(unsigned long long a, unsigne
     return a > b ? a : b;
 }
 
-// Block max of non-negative IEEE bit patterns (NaN sorts above +Inf, so a
-// NaN residual is never lost).
-__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v) {
-    __shared__ unsigned long long red[kBlock];
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = umax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    return red[0];
+// Lane permutation of a double by a DPP control word (no LDS round trip).
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
 }
 
-// Block max of non-negative IEEE bit patterns through wave shuffles and one
-// word per wave of LDS (wm: blockDim.x / 64 entries); for kernels whose LDS
-// budget leaves no room for a per-thread array.  Every thread calls it.
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+    const int lo = __builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), CTRL, 0xf, 0xf, true);
+    return (unsigned long long)(unsigned)hi << 32 | (unsigned)lo;
+}
+
+__device__ __forceinline__ unsigned long long lane_u64(unsigned long long v, int lane) {
+    const int lo = __builtin_amdgcn_readlane((int)v, lane), hi = __builtin_amdgcn_readlane((int)(v >> 32), lane);
+    return (unsigned long long)(unsigned)hi << 32 | (unsigned)lo;
+}
+
+// The value of lane I of each quad of lanes, in all four.
+template <int I>
+__device__ __forceinline__ double quad_bcast(double v) {
+    return dpp<I * 0x55>(v);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+
+// Maximum over a wave of non-negative IEEE bit patterns (NaN sorts above +Inf,
+// so a NaN residual is never lost), in every lane: rotations within the rows
+// of 16 lanes, then the four rows' values.
+__device__ __forceinline__ unsigned long long wave_umax(unsigned long long v) {
+    v = umax(v, dpp_u64<0x128>(v));
+    v = umax(v, dpp_u64<0x124>(v));
+    v = umax(v, dpp_u64<0x122>(v));
+    v = umax(v, dpp_u64<0x121>(v));
+    return umax(umax(lane_u64(v, 0), lane_u64(v, 16)), umax(lane_u64(v, 32), lane_u64(v, 48)));
+}
+
+// Block max of non-negative IEEE bit patterns with one word per wave of LDS
+// (wm: blockDim.x / 64 entries, whole waves).  Every thread calls it.
 __device__ __forceinline__ unsigned long long block_max_u64_waves(unsigned long long v,
                                                                   unsigned long long *wm) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const unsigned long long o = (unsigned long long)__double_as_longlong(
-            __shfl_xor(__longlong_as_double((long long)v), off, 64));
-        v = umax(v, o);
-    }
+    v = wave_umax(v);
     if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = v;
     __syncthreads();
     unsigned long long r = wm[0];
     for (unsigned w = 1; w < blockDim.x / 64; ++w) r = umax(r, wm[w]);
     return r;
+}
+
+// The same for workgroups of kBlock threads, with its own LDS.
+__device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v) {
+    __shared__ unsigned long long wm[kBlock / 64];
+    return block_max_u64_waves(v, wm);
 }
 
 // r = S - N(u) at one point (M = 1) from the discrete Laplacians ls of phi, mu
@@ -243,15 +275,57 @@ __device__ __forceinline__ void n_of_point(const OpParams &op, const double (&ls
     nv[2] = om - w3_of(op) * ls[0];
 }
 
+// r = b - J^T lambda at one point (adjoint of the step's operator) from the
+// Laplacians ls of lambda's components w; D: the diagonal of the second
+// equation's slope.
+__device__ __forceinline__ void adj_resid_from_lap(const OpParams &op, const double (&ls)[3],
+                                                   const double (&w)[3], double b1, double b2,
+                                                   double b3, double D, double (&r)[3]) {
+    r[0] = b1 - (w[0] - D * w[1] - 0.5 * ls[2]);
+    r[1] = b2 - (w[1] - op.tau * ls[0]);
+    r[2] = b3 - (w[2] - ls[1]);
+}
+
+// One point of the red-black block Gauss-Seidel on J^T from lambda's neighbour
+// sums s: with the six neighbours held,
+//     lambda1 - c lambda2 + Dd lambda3 = s1 = b1 + S_l3 / (2 h^2)
+//     A lambda1 + lambda2              = s2 = b2 + tau S_l1 / h^2
+//     B lambda2 + lambda3              = s3 = b3 + S_l2 / h^2
+// (A = 6 tau/h^2, B = 6/h^2, Dd = 3/h^2, c = D at the point).
+__device__ __forceinline__ void adj_point_solve(const OpParams &op, double c, double b1, double b2,
+                                                double b3, const double (&s)[3], double (&l)[3]) {
+    const double s1 = b1 + 0.5 * s[2] * op.h2inv;
+    const double s2 = b2 + op.tau * s[0] * op.h2inv;
+    const double s3 = b3 + s[1] * op.h2inv;
+    const double A = 6.0 * op.tau * op.h2inv, B = 6.0 * op.h2inv, Dd = 3.0 * op.h2inv;
+    l[0] = (s1 + (c + B * Dd) * s2 - Dd * s3) / (1.0 + A * (c + B * Dd));
+    l[1] = s2 - A * l[0];
+    l[2] = s3 - B * l[1];
+}
+
+// Maximum over a wave, in every lane: rotations within the rows of 16 lanes,
+// then the four rows' values.
 __device__ __forceinline__ double wave_max(double v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+    v = fmax(v, dpp<0x128>(v));
+    v = fmax(v, dpp<0x124>(v));
+    v = fmax(v, dpp<0x122>(v));
+    v = fmax(v, dpp<0x121>(v));
+    return fmax(fmax(lane_value(v, 0), lane_value(v, 16)), fmax(lane_value(v, 32), lane_value(v, 48)));
 }
 
 
+
+// Orders the LDS accesses of one wavefront's lanes (a barrier among the lanes
+// of a wave, for code that only the first wave of a workgroup runs): a wave's
+// LDS operations execute in order, so only the compiler has to keep theirs.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // In-place inverse of the P x P matrix A (column-major, A[col * P + row], in
 // LDS) by Gauss-Jordan elimination with partial (row) pivoting.  Called by
-// one whole 64-lane workgroup: lane p eliminates in row p and swaps entries
+// one whole wavefront, the first of its workgroup: lane p eliminates in row p and swaps entries
 // of column p; perm is 64 ints of LDS.  Row interchanges are undone as column
 // interchanges at the end.
 __device__ __forceinline__ void gj_invert(double *A, int P, int *perm) {
@@ -275,11 +349,11 @@ __device__ __forceinline__ void gj_invert(double *A, int P, int *perm) {
             A[p * P + c] = A[p * P + pr];
             A[p * P + pr] = tmp;
         }
-        __syncthreads();
+        wave_sync();
         const double pinv = 1.0 / A[c * P + c];
-        __syncthreads();
+        wave_sync();
         if (act) A[p * P + c] = (p == c ? 1.0 : A[p * P + c]) * pinv;  // scale pivot row
-        __syncthreads();
+        wave_sync();
         if (act && p != c) {
             // full chunks of 16 columns take all their loads before their
             // stores (the pivot row is not written in this phase), so the LDS
@@ -302,7 +376,7 @@ __device__ __forceinline__ void gj_invert(double *A, int P, int *perm) {
                 A[q * P + p] = old - fr * A[q * P + c];
             }
         }
-        __syncthreads();
+        wave_sync();
     }
     for (int c = P - 1; c >= 0; --c) {  // undo the row swaps as column swaps
         const int pr = perm[c];
@@ -311,7 +385,7 @@ __device__ __forceinline__ void gj_invert(double *A, int P, int *perm) {
             A[c * P + p] = A[pr * P + p];
             A[pr * P + p] = tmp;
         }
-        __syncthreads();
+        wave_sync();
     }
 }
 

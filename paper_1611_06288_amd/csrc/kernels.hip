@@ -16,6 +16,7 @@
 // Storage type T is double (FP64 path) or float (the correction cycle of the
 // mixed-precision form); operator arithmetic and the pointwise 3x3 solve run
 // in FP64 in both.
+#include "coarse.h"
 #include "device_common.h"
 #include "pfc.h"
 #include "smooth.h"
@@ -187,13 +188,14 @@ void launch_run_reset(hipStream_t s, RunState st) {
 __global__ __launch_bounds__(kBlock) void k_stop_test(const unsigned long long *partial,
                                                       int count, double tol, int max_cycles,
                                                       RunState st) {
-    if (*st.active == 0) return;  // the same for every thread of the block
-    unsigned long long m = 0;
-    for (int b = threadIdx.x; b < count; b += kBlock) m = umax(m, partial[b]);
+    // the state and the first partials are loaded together
+    const int active = *st.active, c = *st.cycles;
+    unsigned long long m = (int)threadIdx.x < count ? partial[threadIdx.x] : 0;
+    if (active == 0) return;  // the same for every thread of the block
+    for (int b = threadIdx.x + kBlock; b < count; b += kBlock) m = umax(m, partial[b]);
     m = block_max_u64(m);
     if (threadIdx.x != 0) return;
     const double r = __longlong_as_double((long long)m);
-    const int c = *st.cycles;
     if (c == 0) *st.res0 = r;
     *st.res = r;
     if (!isfinite(r)) {
@@ -334,48 +336,6 @@ void launch_restrict(hipStream_t s, const Lay &fine, const Lay &coarse, const T 
 }
 
 // ------------------------------------------------------- tau correction
-//
-// Coarse right-hand side of the FAS: f_c = N_c(I u) + I r (f holds I r on
-// entry); also starts the coarse iterate at I u, unless u.a is null.
-template <typename T, bool DELTA, bool MOB = false>
-__device__ __forceinline__ void tau_body(const OpParams &op, Tri<const T> ubar, Tri<T> f, Tri<T> u,
-                                         const T *__restrict__ phk, const T *__restrict__ base,
-                                         unsigned t) {
-    const Lay &L = op.lay;
-    if (t >= (unsigned)npts(L)) return;
-    int i, j, k;
-    decode(L, t, i, j, k);
-    const Off q = offs(L, i, j, k);
-    const double phi = ubar.a[t], mu = ubar.b[t], om = ubar.c[t];
-    double lmu;
-    if constexpr (MOB) {
-        const double *ps = op.mob.phs;
-        const double pc = ps[q.c];
-        const unsigned nb6[6] = {q.xp, q.xm, q.yp, q.ym, q.zp, q.zm};
-        double sm = 0.0;
-#pragma unroll
-        for (int e = 0; e < 6; ++e)
-            sm += face_mob(op.mob, pc, ps[nb6[e]]) * ((double)ubar.b[nb6[e]] - mu);
-        lmu = sm * op.h2inv;
-    } else {
-        lmu = (nsum(ubar.b, q) - 6.0 * mu) * op.h2inv;
-    }
-    const double ls[3] = {(nsum(ubar.a, q) - 6.0 * phi) * op.h2inv, lmu,
-                          (nsum(ubar.c, q) - 6.0 * om) * op.h2inv};
-    // every load ahead of the first store (which may alias them as far as the
-    // compiler knows); I u's own values are copied from phi, mu, om (exact)
-    const double f0 = f.a[t], f1 = f.b[t], f2 = f.c[t];
-    double nv[3];
-    n_of_point<DELTA>(op, ls, phi, mu, om, (double)phk[t], DELTA ? (double)base[t] : 0.0, nv);
-    f.a[t] = (T)(f0 + nv[0]);
-    f.b[t] = (T)(f1 + nv[1]);
-    f.c[t] = (T)(f2 + nv[2]);
-    if (u.a) {
-        u.a[t] = (T)phi;
-        u.b[t] = (T)mu;
-        u.c[t] = (T)om;
-    }
-}
 
 template <typename T, bool DELTA, bool MOB>
 __global__ __launch_bounds__(kBlock) void k_tau(OpParams op, Tri<const T> ubar, Tri<T> f, Tri<T> u,
@@ -677,200 +637,6 @@ void launch_prolong(hipStream_t s, const Lay &coarse, const Lay &fine, Tri<const
 }
 
 // ------------------------------------------------------ coarsest solve
-//
-// Exact solve of N_c(u) = f on the coarsest level (natural layout, n = 3 or
-// 4, P = n^3 <= 64 points), one 64-lane wavefront, lane p owning point p.
-// omega and mu enter linearly and are eliminated exactly:
-//   F(phi) = phi - tau Lap(g(phi) + (1-eps)/2 phi) - tau/2 Lap^3 phi - b = 0,
-//   b = f1 + tau Lap(f2 + Lap f3),
-//   F'(phi) = I - tau Lap diag(g'(phi) + (1-eps)/2) - tau/2 Lap^3,
-// then omega = f3 + Lap phi / 2 and mu = f2 + g(phi) + (1-eps)/2 phi + Lap omega.
-// Iteration: phi <- phi - Minv F(phi) with Minv = F'(phi_0)^{-1} kept across
-// calls (chord method); when an iteration contracts by less than 4x, Minv is
-// rebuilt at the current iterate (which makes that step a Newton step).  The
-// inverse comes from Gauss-Jordan elimination with partial pivoting in LDS.
-// Stops when max|update| <= 1e-14 max(1, max|phi|) (or after 60 iterations).
-// First-order scheme (op.fo): g(phi) = phi^3, (1-eps) phi, the Lap^3 term with
-// tau instead of tau/2 and omega = f3 + Lap phi.
-// MOB (variable mobility): the outer Lap of the first equation becomes the
-// flux operator L_M = d(M D), so F(phi) = phi - tau L_M(g(phi) + (1-eps)/2 phi)
-// - tau/2 L_M Lap^2 phi - b with b = f1 + tau L_M(f2 + Lap f3); its Jacobian
-// uses the dense Lap^2 (lap2) for the L_M Lap^2 block.
-template <typename T, bool DELTA, bool MOB = false>
-__device__ __forceinline__ void coarse_body(const OpParams &op, Tri<T> u, Tri<const T> f,
-                                            const T *__restrict__ phk, const T *__restrict__ base,
-                                            const double *__restrict__ lap1,
-                                            const double *__restrict__ lap3, double *minv,
-                                            int *valid, int *iters,
-                                            const double *__restrict__ lap2 = nullptr) {
-    __shared__ double A[64 * 64];  // column-major: A[col * P + row]
-    __shared__ double vec[64];
-    __shared__ double dvec[64];
-    __shared__ int perm[64];
-    const int n = op.lay.n, P = n * n * n;
-    const int p = threadIdx.x;
-    const bool act = p < P;
-    const double h2inv = op.h2inv, tau = op.tau, lc = lin_of(op), w3 = w3_of(op);
-
-    int nb[6] = {0, 0, 0, 0, 0, 0};
-    if (act) {
-        const int i = p % n, j = (p / n) % n, k = p / (n * n);
-        nb[0] = (k * n + j) * n + wrap_p(i, n);
-        nb[1] = (k * n + j) * n + wrap_m(i, n);
-        nb[2] = (k * n + wrap_p(j, n)) * n + i;
-        nb[3] = (k * n + wrap_m(j, n)) * n + i;
-        nb[4] = (wrap_p(k, n) * n + j) * n + i;
-        nb[5] = (wrap_m(k, n) * n + j) * n + i;
-    }
-    // Lap of the field held in vec[] at point p (call between barriers)
-    auto lap_lds = [&](double own) -> double {
-        return ((vec[nb[0]] + vec[nb[1]]) + (vec[nb[2]] + vec[nb[3]]) + (vec[nb[4]] + vec[nb[5]]) -
-                6.0 * own) * h2inv;
-    };
-    // face mobilities of point p (MOB), and L_M of the field held in vec[]
-    double mf[6] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0}, msum = 6.0;
-    if constexpr (MOB) {
-        if (act) {
-            msum = 0.0;
-            for (int e = 0; e < 6; ++e) {
-                mf[e] = face_mob(op.mob, op.mob.phs[p], op.mob.phs[nb[e]]);
-                msum += mf[e];
-            }
-        }
-    }
-    auto lapo_lds = [&](double own) -> double {  // the first equation's outer operator
-        if constexpr (MOB) {
-            double sm = 0.0;
-            for (int e = 0; e < 6; ++e) sm += mf[e] * (vec[nb[e]] - own);
-            return sm * h2inv;
-        } else {
-            return lap_lds(own);
-        }
-    };
-    const double a = act ? (double)phk[p] : 0.0;
-    const double bs = (DELTA && act) ? (double)base[p] : 0.0;
-    const double F1 = act ? (double)f.a[p] : 0.0;
-    const double F2 = act ? (double)f.b[p] : 0.0;
-    const double F3 = act ? (double)f.c[p] : 0.0;
-    double x = act ? (double)u.a[p] : 0.0;
-
-    vec[p] = F3;
-    __syncthreads();
-    const double t3 = act ? lap_lds(F3) : 0.0;
-    __syncthreads();
-    vec[p] = F2 + t3;
-    __syncthreads();
-    const double bp = F1 + tau * (act ? lapo_lds(F2 + t3) : 0.0);
-    __syncthreads();
-
-    // Builds Minv = F'(x)^{-1} into global memory.
-    auto rebuild = [&]() {
-        dvec[p] = dg_of<DELTA>(op.fo, x, a, bs) + lc;
-        __syncthreads();
-        if (act && !MOB) {
-            // row p of F'(x); the dense Lap and Lap^3 come from global memory,
-            // so their loads are issued 16 at a time ahead of the stores
-            for (int q0 = 0; q0 < P; q0 += 16) {
-                double l1v[16], l3v[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int q = q0 + i;
-                    l1v[i] = q < P ? lap1[q * P + p] : 0.0;
-                    l3v[i] = q < P ? lap3[q * P + p] : 0.0;
-                }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int q = q0 + i;
-                    if (q < P)
-                        A[q * P + p] =
-                            (q == p ? 1.0 : 0.0) - tau * l1v[i] * dvec[q] - w3 * tau * l3v[i];
-                }
-            }
-        }
-        if constexpr (MOB) {
-            if (act)
-                for (int q = 0; q < P; ++q) {
-                    // row p of L_M and of L_M Lap^2 (lap2 column-major: [col * P + row])
-                    double lm = q == p ? -msum : 0.0, lmd2 = -msum * lap2[q * P + p];
-                    for (int e = 0; e < 6; ++e) {
-                        if (nb[e] == q) lm += mf[e];
-                        lmd2 += mf[e] * lap2[q * P + nb[e]];
-                    }
-                    A[q * P + p] = (q == p ? 1.0 : 0.0) - tau * (lm * h2inv) * dvec[q] -
-                                   0.5 * tau * (lmd2 * h2inv);
-                }
-        }
-        __syncthreads();
-        gj_invert(A, P, perm);
-        if (act)
-            for (int q = 0; q < P; ++q) minv[q * P + p] = A[q * P + p];
-        __syncthreads();
-    };
-
-    bool fresh = false;
-    if (!*valid) {
-        rebuild();
-        fresh = true;
-    }
-    double dprev = 0.0;
-    int it;
-    for (it = 1; it <= 60; ++it) {
-        const double w = g_of<DELTA>(op.fo, x, a, bs) + lc * x;
-        vec[p] = w;
-        __syncthreads();
-        const double lw = act ? lapo_lds(w) : 0.0;
-        __syncthreads();
-        vec[p] = x;
-        __syncthreads();
-        const double l1 = act ? lap_lds(x) : 0.0;
-        __syncthreads();
-        vec[p] = l1;
-        __syncthreads();
-        const double l2 = act ? lap_lds(l1) : 0.0;
-        __syncthreads();
-        vec[p] = l2;
-        __syncthreads();
-        const double l3 = act ? lapo_lds(l2) : 0.0;
-        __syncthreads();
-        dvec[p] = act ? (x - tau * lw - w3 * tau * l3 - bp) : 0.0;
-        __syncthreads();
-        double d = 0.0;
-        if (act)
-            for (int q = 0; q < P; ++q) d -= minv[q * P + p] * dvec[q];
-        x += d;
-        const double dm = wave_max(fabs(d));
-        const double xm = wave_max(fabs(x));
-        __syncthreads();
-        if (!(dm == dm)) break;
-        if (dm <= 1e-14 * fmax(1.0, xm)) break;
-        if (!fresh && it > 1 && dm > 0.25 * dprev) {
-            rebuild();
-            fresh = true;
-        } else {
-            fresh = false;
-        }
-        dprev = dm;
-    }
-    if (it > 60) it = 60;
-    vec[p] = x;
-    __syncthreads();
-    const double lx = act ? lap_lds(x) : 0.0;
-    __syncthreads();
-    const double om = F3 + w3 * lx;
-    vec[p] = om;
-    __syncthreads();
-    const double lom = act ? lap_lds(om) : 0.0;
-    const double mu = F2 + g_of<DELTA>(op.fo, x, a, bs) + lc * x + lom;
-    if (act) {
-        u.a[p] = (T)x;
-        u.b[p] = (T)mu;
-        u.c[p] = (T)om;
-    }
-    if (p == 0) {
-        *valid = 1;
-        if (iters) *iters = it;
-    }
-}
 
 // With ubar.a set, the level's tau correction comes first: f += N(I u) with
 // I u = ubar (f holds I r; written through fw, the same buffer as f) and the
@@ -884,13 +650,15 @@ __global__ __launch_bounds__(64) void k_coarse(OpParams op, Tri<T> u, Tri<const 
                                                int *valid, int *iters,
                                                const double *__restrict__ lap2, Tri<const T> ubar,
                                                Tri<T> fw) {
+    __shared__ CoarseShared sm;
     if (gate_closed(op.gate)) return;
+    const bool ok = coarse_load_inverse<64>(minv, valid, sm);
     if (ubar.a) {
         for (unsigned t = threadIdx.x; t < (unsigned)npts(op.lay); t += blockDim.x)
             tau_body<T, DELTA, MOB>(op, ubar, fw, u, phk, base, t);
-        __syncthreads();
     }
-    coarse_body<T, DELTA, MOB>(op, u, f, phk, base, lap1, lap3, minv, valid, iters, lap2);
+    __syncthreads();
+    coarse_body<T, DELTA, MOB>(op, u, f, phk, base, lap1, lap3, minv, ok, valid, iters, sm, lap2);
 }
 
 template <typename T, bool DELTA>
@@ -1291,16 +1059,18 @@ __global__ __launch_bounds__(512) void kb_phase(const BSeg *segs, int nseg, unsi
 
 // tau: each segment's tau correction first (as k_coarse with ubar set).
 __global__ __launch_bounds__(64) void kb_coarse(const BSeg *segs, int nseg, int tau) {
+    __shared__ CoarseShared sm;
     const int s = blockIdx.x;
     if (s >= nseg || !*segs[s].active) return;
     const BSeg &g = segs[s];
+    const bool ok = coarse_load_inverse<64>(g.minv, g.valid, sm);
     if (tau) {
         for (unsigned t = threadIdx.x; t < (unsigned)npts(g.op.lay); t += blockDim.x)
             tau_body<double, false>(g.op, cst(g.ubar), g.f, g.u, g.phk, nullptr, t);
-        __syncthreads();
     }
-    coarse_body<double, false>(g.op, g.u, cst(g.f), g.phk, nullptr, g.lap1, g.lap3, g.minv, g.valid,
-                               g.iters);
+    __syncthreads();
+    coarse_body<double, false>(g.op, g.u, cst(g.f), g.phk, nullptr, g.lap1, g.lap3, g.minv, ok,
+                               g.valid, g.iters, sm);
 }
 
 // Residual maxima of every instance's finest level, one per norm tile

@@ -51,6 +51,19 @@ pfc_status mixed_init(pfc_handle *H) {
         A.e = Tri<float>{e, e + P, e + 2 * P};
         A.f = Tri<float>{f, f + P, f + 2 * P};
         A.ebar = Tri<float>{eb, eb + P, eb + 2 * P};
+        if (H->lev[l].brick) {
+            float *e2, *fr;
+            if (!dalloc(H, &e2, 3 * P) || !dalloc(H, &fr, 3 * P))
+                return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
+            A.e2 = Tri<float>{e2, e2 + P, e2 + 2 * P};
+            A.fr = Tri<float>{fr, fr + P, fr + 2 * P};
+            if (!brick_small(H->lev[l].n)) {
+                float *e3;
+                if (!dalloc(H, &e3, 3 * P))
+                    return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
+                A.e3 = Tri<float>{e3, e3 + P, e3 + 2 * P};
+            }
+        }
     }
     return PFC_OK;
 }
@@ -79,10 +92,82 @@ static void sweep32(pfc_handle *H, int l, bool tau = false) {
     }
 }
 
+// Where the restriction onto level l leaves I r.
+static Tri<float> rhs_in32(pfc_handle *H, int l) {
+    return H->lev[l].brick ? H->lev32[l].fr : H->lev32[l].f;
+}
+
+static BrickArgs<float> brick_args32(pfc_handle *H, int l) {
+    Level32 &A = H->lev32[l];
+    BrickArgs<float> a;
+    a.op = op_of(H, l);
+    a.f = cst(A.f);
+    a.phk = A.phk;
+    a.base = A.base;
+    a.LC = H->lev[l + 1].lay;
+    return a;
+}
+
+static void brick_pre32(pfc_handle *H, int l, bool tau) {
+    Level32 &A = H->lev32[l], &B = H->lev32[l + 1];
+    BrickArgs<float> a = brick_args32(H, l);
+    if (tau) a.f = cst(A.fr);
+    a.fo = A.f;
+    a.cu = B.ebar;
+    a.cr = rhs_in32(H, l + 1);
+    brick_run_pre<float>(a, H->cfg.nu1, tau ? cst(A.ebar) : cst(A.e), A.e2, A.e3,
+                         tau ? BRICK_FIRST : BRICK_PLAIN,
+                         [&](const BrickArgs<float> &b, int kind, int sweeps, int form) {
+                             launch_brick32(H->stream, b, kind, sweeps, form);
+                         });
+}
+
+static void brick_post32(pfc_handle *H, int l) {
+    Level32 &A = H->lev32[l], &B = H->lev32[l + 1];
+    BrickArgs<float> a = brick_args32(H, l);
+    a.v = cst(B.e);
+    a.ub = cst(B.ebar);
+    brick_run_post<float>(a, H->cfg.nu1, H->cfg.nu2, A.e, A.e2, A.e3,
+                          [&](const BrickArgs<float> &b, int kind, int sweeps, int form) {
+                              launch_brick32(H->stream, b, kind, sweeps, form);
+                          });
+}
+
+// The levels from l (8^3 or 6^3) down; an F-cycle's second visit included.
+static void tail32(pfc_handle *H, int l, bool fcycle) {
+    Level32 &A = H->lev32[l], &B = H->lev32[l + 1];
+    TailArgs<float> a;
+    a.op = op_of(H, l);
+    a.opc = op_of(H, l + 1);
+    a.nu1 = H->cfg.nu1;
+    a.nu2 = H->cfg.nu2;
+    a.fcycle = fcycle ? 1 : 0;
+    a.u = A.e;
+    a.f = cst(A.f);
+    a.ub = cst(A.ebar);
+    a.phk = A.phk;
+    a.base = A.base;
+    a.phkc = B.phk;
+    a.basec = B.base;
+    a.lap1 = H->lap1;
+    a.lap3 = H->lap3;
+    a.minv = H->minv32;
+    a.valid = H->valid32;
+    a.iters = H->d_iters;
+    launch_tail32(H->stream, a);
+}
+
 // tau: f of level l holds I r and its iterate is still in ebar (the first
 // pre-sweep, on the coarsest the solve's launch, forms the tau correction).
 static void cycle32(pfc_handle *H, int l, bool fcycle, bool tau = false) {
     Level32 &A = H->lev32[l];
+    if (H->lev[l].tail) return tail32(H, l, fcycle);
+    if (H->lev[l].brick) {
+        brick_pre32(H, l, tau);
+        cycle32(H, l + 1, fcycle, true);
+        if (fcycle && !H->lev[l + 1].tail) cycle32(H, l + 1, false);
+        return brick_post32(H, l);
+    }
     if (l == H->nlev - 1) {
         H->begin_timed(PFC_KERNEL_COARSE, l);
         launch_coarse<float, true>(
@@ -104,11 +189,11 @@ static void cycle32(pfc_handle *H, int l, bool fcycle, bool tau = false) {
         ra.b32 = A.base;
         ra.LC = LB;
         ra.ebar32 = B.ebar;
-        ra.rr32 = B.f;
+        ra.rr32 = rhs_in32(H, l + 1);
         launch_resid_tile(H->stream, RT_RESTRICT32, op_of(H, l), H->lev[l].rt_nz[RT_RESTRICT32], ra);
     } else {
         launch_resid_restrict<float, true>(H->stream, op_of(H, l), LB, cst(A.e), cst(A.f), A.phk,
-                                           A.base, B.ebar, B.f);
+                                           A.base, B.ebar, rhs_in32(H, l + 1));
     }
     H->end_timed();
     // a coarse level forms the tau correction in its first pre-sweep, the
@@ -117,7 +202,7 @@ static void cycle32(pfc_handle *H, int l, bool fcycle, bool tau = false) {
     if (!tau_sweep)
         launch_tau<float, true>(H->stream, op_of(H, l + 1), cst(B.ebar), B.f, B.e, B.phk, B.base);
     cycle32(H, l + 1, fcycle, tau_sweep);
-    if (fcycle) cycle32(H, l + 1, false);
+    if (fcycle && !H->lev[l + 1].tail) cycle32(H, l + 1, false);
     H->begin_timed(PFC_KERNEL_PROLONG0, l);
     launch_prolong<float>(H->stream, LB, H->lev[l].lay, cst(B.e), cst(B.ebar), A.e, nullptr,
                           H->cfg.nu2 >= 1, H->lev[l].pz[1]);

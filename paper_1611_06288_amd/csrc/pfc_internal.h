@@ -119,6 +119,94 @@ int fused_slots(int device, bool mob = false);      // resident fused-sweep work
 int fused_nz(int n, int slots);   // plane ranges per column for a level of size n
 constexpr int kFusedMinN = 128;  // smaller levels use the half-sweeps
 
+// ---- brick launches (brick.h): one level's part of a cycle on either side of
+// the descent, for levels of 12^3 to 96^3 ----
+enum { BRICK_PRE = 0, BRICK_SWEEP = 1, BRICK_POST = 2 };  // kinds
+enum { BRICK_PLAIN = 0, BRICK_FIRST = 1, BRICK_NORM = 2 };  // forms of the first two
+template <typename T>
+struct BrickArgs {
+    OpParams op;
+    int picard = 0;
+    int skip0 = 0;                               // BRICK_SWEEP, BRICK_POST: another sweep follows
+    Tri<const T> u{nullptr, nullptr, nullptr};   // iterate (BRICK_FIRST: I u) read
+    Tri<T> uo{nullptr, nullptr, nullptr};        // iterate written, another buffer
+    Tri<const T> f{nullptr, nullptr, nullptr};   // right-hand side (BRICK_FIRST: I r)
+    Tri<T> fo{nullptr, nullptr, nullptr};        // BRICK_FIRST: f + N(I u), another buffer
+    const T *phk = nullptr, *base = nullptr;
+    Lay LC{};                                    // the next coarser level
+    Tri<T> cu{nullptr, nullptr, nullptr}, cr{nullptr, nullptr, nullptr};  // pre: its I u and I r
+    Tri<const T> v{nullptr, nullptr, nullptr}, ub{nullptr, nullptr, nullptr};  // post: its iterate, I u
+    unsigned long long *part = nullptr;          // BRICK_NORM: per-workgroup max |S - N(u)|
+};
+// 4^3 boxes with both sweeps of a side in one launch up to 32^3, where a launch
+// has CUs to spare; from 48^3 on 8^3 boxes and one sweep per launch, whose
+// halos cost less than the launch they would save.
+inline bool brick_small(int n) { return n <= 32; }
+inline bool brick_size(int n) { return n >= 12 && n <= 96 && n % (brick_small(n) ? 4 : 8) == 0; }
+constexpr int kBrickMaxSweeps = 2;  // sweeps per side of the descent
+inline int brick_blocks(int n) {
+    const int m = n / (brick_small(n) ? 4 : 8);
+    return m * m * m;
+}
+// sweeps of the launch: 1 or, with small boxes, 2
+void launch_brick64(hipStream_t s, const BrickArgs<double> &a, int kind, int sweeps, int form);
+void launch_brick64_mob(hipStream_t s, const BrickArgs<double> &a, int kind, int sweeps, int form);
+void launch_brick32(hipStream_t s, const BrickArgs<float> &a, int kind, int sweeps, int form);
+void launch_brick_adj(hipStream_t s, const BrickArgs<double> &a, int kind, int sweeps, int form);
+
+// The launches of one level with their buffers: u is the iterate between
+// cycles, x and y two more.  Before the descent u -> x (-> y), after it back
+// to u, so the iterate is never overwritten before the cycle's last launch.
+// a: everything but u, uo and skip0; go(args, kind, sweeps, form).
+template <typename T>
+inline Tri<T> brick_mid(int n, int nu1, Tri<T> x, Tri<T> y) {
+    return nu1 == 1 || brick_small(n) ? x : y;
+}
+template <typename T, typename Go>
+inline void brick_run_pre(BrickArgs<T> a, int nu1, Tri<const T> u, Tri<T> x, Tri<T> y, int form, Go go) {
+    a.u = u;
+    a.uo = x;
+    if (nu1 == 1 || brick_small(a.op.lay.n)) return go(a, BRICK_PRE, nu1, form);
+    a.skip0 = 1;
+    go(a, BRICK_SWEEP, 1, form);
+    a.u = cst(x);
+    a.uo = y;
+    if (form == BRICK_FIRST) a.f = cst(a.fo);
+    go(a, BRICK_PRE, 1, BRICK_PLAIN);
+}
+template <typename T, typename Go>
+inline void brick_run_post(BrickArgs<T> a, int nu1, int nu2, Tri<T> u, Tri<T> x, Tri<T> y, Go go) {
+    const Tri<T> mid = brick_mid(a.op.lay.n, nu1, x, y);
+    a.u = cst(mid);
+    a.uo = u;
+    if (nu2 == 1 || brick_small(a.op.lay.n)) return go(a, BRICK_POST, nu2, BRICK_PLAIN);
+    const Tri<T> other = mid.a == x.a ? y : x;
+    a.uo = other;
+    a.skip0 = 1;
+    go(a, BRICK_POST, 1, BRICK_PLAIN);
+    a.u = cst(other);
+    a.uo = u;
+    a.skip0 = 0;
+    go(a, BRICK_SWEEP, 1, BRICK_PLAIN);
+}
+
+// ---- the 8^3 (6^3) level and the coarsest below it in one launch (tail.h) ----
+template <typename T>
+struct TailArgs {
+    OpParams op, opc;  // the level, the coarsest level
+    int picard = 0, nu1 = 0, nu2 = 0;
+    int fcycle = 0;    // an F-cycle followed by a V-cycle, as the cycle above visits the level
+    Tri<T> u{nullptr, nullptr, nullptr};         // iterate (written)
+    Tri<const T> f{nullptr, nullptr, nullptr}, ub{nullptr, nullptr, nullptr};  // I r, I u
+    const T *phk = nullptr, *base = nullptr, *phkc = nullptr, *basec = nullptr;
+    const double *lap1 = nullptr, *lap2 = nullptr, *lap3 = nullptr;
+    double *minv = nullptr;
+    int *valid = nullptr, *iters = nullptr;
+};
+inline bool tail_size(int n) { return n == 8 || n == 6; }
+void launch_tail64(hipStream_t s, const TailArgs<double> &a);
+void launch_tail32(hipStream_t s, const TailArgs<float> &a);
+
 // Residual of a large level by z-marching column tiles (residual.hip), with
 // one of five epilogues.
 enum { RT_NORM = 0, RT_RESTRICT = 1, RT_CAST = 2, RT_CAST_CORR = 3, RT_RESTRICT32 = 4, RT_MODES = 5 };

@@ -155,7 +155,7 @@ void invalidate_coarse(pfc_handle *H) {
 
 // ------------------------------------------------------------ timing
 
-void pfc_handle::begin_timed(int kind, int level, double bytes) {
+void pfc_handle::begin_timed(int kind, int level, double bytes, int n, bool ahead) {
     cur_event = -1;
     if (!timing || kind < 0) return;
     if (kind != PFC_KERNEL_COARSE && level != 0) return;
@@ -173,7 +173,8 @@ void pfc_handle::begin_timed(int kind, int level, double bytes) {
         }
     }
     (void)hipEventRecord(a, stream);
-    pending.push_back(TimedLaunch{kind, a, b, bytes >= 0.0 ? bytes : algorithmic_bytes(this, kind)});
+    pending.push_back(
+        TimedLaunch{kind, a, b, bytes >= 0.0 ? bytes : algorithmic_bytes(this, kind), n, ahead});
     cur_event = (int)pending.size() - 1;
 }
 
@@ -187,14 +188,29 @@ void pfc_handle::collect_timings() {
     for (auto &t : pending) {
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) {
-            t_count[t.kind] += 1;
+            t_count[t.kind] += t.n;
             t_ms[t.kind] += ms;
             t_bytes[t.kind] += t.bytes;
+            if (t.ahead) {
+                if (ahead_kind < 0) ahead_n = 0, ahead_ms = 0, ahead_bytes = 0;
+                ahead_kind = t.kind;
+                ahead_n += t.n;
+                ahead_ms += ms;
+                ahead_bytes += t.bytes;
+            }
         }
         pool.push_back(t.a);
         pool.push_back(t.b);
     }
     pending.clear();
+}
+
+void pfc_handle::retract_ahead() {
+    if (ahead_kind < 0) return;
+    t_count[ahead_kind] -= ahead_n;
+    t_ms[ahead_kind] -= ahead_ms;
+    t_bytes[ahead_kind] -= ahead_bytes;
+    ahead_kind = -1;
 }
 
 pfc_handle::~pfc_handle() {
@@ -269,8 +285,98 @@ void sweep64(pfc_handle *H, int l, int nrm, bool then_sweep, bool tau) {
     }
 }
 
+// Where the restriction onto level l leaves I r.
+static Tri<double> rhs_in(pfc_handle *H, int l) {
+    return H->lev[l].brick ? H->lev[l].fr : H->lev[l].f;
+}
+
+static BrickArgs<double> brick_args64(pfc_handle *H, int l) {
+    BrickArgs<double> a;
+    a.op = op_of(H, l);
+    a.picard = H->cfg.lin == PFC_LIN_PICARD;
+    a.f = frhs(H, l);
+    a.phk = H->lev[l].phk;
+    a.LC = H->lev[l + 1].lay;
+    a.part = H->partial;
+    return a;
+}
+
+// A launch's algorithmic bytes per point: read phi everywhere, mu and omega at
+// colour-1 points, f2, f3 and phi^k (40), write the same fields (16) or all
+// (24), plus 6 for I u and I r or for v and I u.
+static double brick_bytes(const BrickArgs<double> &a, int kind) {
+    const bool full = kind != BRICK_PRE && !a.skip0;
+    return (40.0 + (full ? 24.0 : 16.0) + (kind == BRICK_SWEEP ? 0.0 : 6.0)) * (double)npts_host(a.op.lay);
+}
+
+int brick_pre64(pfc_handle *H, int l, int form) {
+    Level &A = H->lev[l], &B = H->lev[l + 1];
+    BrickArgs<double> a = brick_args64(H, l);
+    if (form == BRICK_FIRST) a.f = cst(A.fr);
+    a.fo = A.f;
+    a.cu = B.ubar;
+    a.cr = rhs_in(H, l + 1);
+    H->ahead_kind = -1;
+    brick_run_pre<double>(a, H->cfg.nu1, form == BRICK_FIRST ? cst(A.ubar) : cst(A.u), A.u2, A.u3, form,
+                          [&](const BrickArgs<double> &b, int kind, int sweeps, int fm) {
+                              // counted as the half-sweeps it runs
+                              H->begin_timed(PFC_KERNEL_SMOOTH0, l, brick_bytes(b, kind), 2 * sweeps,
+                                             form == BRICK_NORM);
+                              launch_brick64(H->stream, b, kind, sweeps, fm);
+                              H->end_timed();
+                          });
+    return brick_blocks(A.n);
+}
+
+static void brick_post64(pfc_handle *H, int l) {
+    Level &A = H->lev[l], &B = H->lev[l + 1];
+    BrickArgs<double> a = brick_args64(H, l);
+    a.v = cst(B.u);
+    a.ub = cst(B.ubar);
+    brick_run_post<double>(a, H->cfg.nu1, H->cfg.nu2, A.u, A.u2, A.u3,
+                           [&](const BrickArgs<double> &b, int kind, int sweeps, int fm) {
+                               H->begin_timed(PFC_KERNEL_SMOOTH0, l, brick_bytes(b, kind), 2 * sweeps);
+                               launch_brick64(H->stream, b, kind, sweeps, fm);
+                               H->end_timed();
+                           });
+}
+
+// The levels from l (8^3 or 6^3) down; an F-cycle's second visit included.
+static void tail64(pfc_handle *H, int l, bool fcycle) {
+    Level &A = H->lev[l], &B = H->lev[l + 1];
+    TailArgs<double> a;
+    a.op = op_of(H, l);
+    a.opc = op_of(H, l + 1);
+    a.picard = H->cfg.lin == PFC_LIN_PICARD;
+    a.nu1 = H->cfg.nu1;
+    a.nu2 = H->cfg.nu2;
+    a.fcycle = fcycle ? 1 : 0;
+    a.u = A.u;
+    a.f = cst(A.f);
+    a.ub = cst(A.ubar);
+    a.phk = A.phk;
+    a.phkc = B.phk;
+    a.lap1 = H->lap1;
+    a.lap2 = H->lap2;
+    a.lap3 = H->lap3;
+    a.minv = H->minv64;
+    a.valid = H->valid64;
+    a.iters = H->d_iters;
+    H->begin_timed(PFC_KERNEL_COARSE, l, 0.0);
+    launch_tail64(H->stream, a);
+    H->end_timed();
+}
+
 void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
     Level &A = H->lev[l];
+    if (A.tail) return tail64(H, l, fcycle);
+    if (A.brick) {
+        if (!(flags & kCyclePreDone))
+            brick_pre64(H, l, (flags & kCycleTauSweep) ? BRICK_FIRST : BRICK_PLAIN);
+        cycle64(H, l + 1, fcycle, kCycleTauSweep);
+        if (fcycle && !H->lev[l + 1].tail) cycle64(H, l + 1, false);
+        return brick_post64(H, l);
+    }
     if (l == H->nlev - 1) {
         H->begin_timed(PFC_KERNEL_COARSE, l);
         // kCycleTauSweep: the solve applies the level's tau correction first
@@ -293,11 +399,11 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
         ra.phk = A.phk;
         ra.LC = B.lay;
         ra.ubar = B.ubar;
-        ra.rr = B.f;
+        ra.rr = rhs_in(H, l + 1);
         launch_resid_tile(H->stream, RT_RESTRICT, op_of(H, l), A.rt_nz[RT_RESTRICT], ra);
     } else {
         launch_resid_restrict<double, false>(H->stream, op_of(H, l), B.lay, cst(A.u), frhs(H, l),
-                                             A.phk, nullptr, B.ubar, B.f);
+                                             A.phk, nullptr, B.ubar, rhs_in(H, l + 1));
     }
     H->end_timed();
     // with pre-sweeps a coarse level forms the tau correction in its first
@@ -309,7 +415,7 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
         launch_tau<double, false>(H->stream, op_of(H, l + 1), cst(B.ubar), B.f, B.u, B.phk,
                                   nullptr);
     cycle64(H, l + 1, fcycle, tau_sweep ? kCycleTauSweep : 0u);
-    if (fcycle) cycle64(H, l + 1, false);
+    if (fcycle && !B.tail) cycle64(H, l + 1, false);
     H->begin_timed(PFC_KERNEL_PROLONG0, l);
     launch_prolong<double>(H->stream, B.lay, A.lay, cst(B.u), cst(B.ubar), A.u, H->gate,
                            H->cfg.nu2 >= 1, A.pz[0]);
@@ -481,7 +587,23 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
         if (l + 1 < H->nlev)
             for (int t = 0; t < 2; ++t) A.pz[t] = prolong_tile_nzr(pt_slots[t], A.n / 2, A.n);
         A.fused = l < H->nlev - 1 && fused_fits(A.n);
-        if (A.fused || (l == 0 && A.rt)) {
+        const bool sweeps = cfg->nu1 >= 1 && cfg->nu1 <= kBrickMaxSweeps && cfg->nu2 >= 1 &&
+                            cfg->nu2 <= kBrickMaxSweeps;
+        A.brick = l < H->nlev - 1 && sweeps && brick_size(A.n);
+        A.tail = l > 0 && l == H->nlev - 2 && sweeps && tail_size(A.n);
+        if (A.brick && l > 0) {
+            double *fr;
+            ok = dalloc(H, &fr, 3 * A.P);
+            if (!ok) break;
+            A.fr = Tri<double>{fr, fr + A.P, fr + 2 * A.P};
+        }
+        if (A.brick && !brick_small(A.n)) {
+            double *u3;
+            ok = dalloc(H, &u3, 3 * A.P);
+            if (!ok) break;
+            A.u3 = Tri<double>{u3, u3 + A.P, u3 + 2 * A.P};
+        }
+        if (A.fused || A.brick || (l == 0 && A.rt)) {
             A.nz = fused_nz(A.n, slots);
             double *u2;
             ok = dalloc(H, &u2, 3 * A.P);
@@ -597,8 +719,10 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
     // cycle's first pre-sweep, launched before the decision; when the loop then
     // stops, that sweep's output is dropped (its input buffer is untouched).
     bool ahead = false;
+    const bool brick = h->lev[0].brick;
     {
-        const pfc_status st = resid_norm64(h, Tri<double>{nullptr, nullptr, nullptr}, &rho);
+        const pfc_status st = brick ? read_norm(h, brick_pre64(h, 0, BRICK_NORM), &rho)
+                                    : resid_norm64(h, Tri<double>{nullptr, nullptr, nullptr}, &rho);
         if (st != PFC_OK) return st;
     }
     for (;;) {
@@ -611,6 +735,13 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
         if (c == h->cfg.max_cycles) {
             status = PFC_ERR_NOT_CONVERGED;
             break;
+        }
+        if (brick) {  // every part before the descent runs ahead of its decision
+            cycle64(h, 0, h->cfg.cycle == PFC_CYCLE_F, kCyclePreDone);
+            ++c;
+            const pfc_status st = read_norm(h, brick_pre64(h, 0, BRICK_NORM), &rho);
+            if (st != PFC_OK) return st;
+            continue;
         }
         const bool split = h->split_norm && c + 1 < h->cfg.max_cycles;
         cycle64(h, 0, h->cfg.cycle == PFC_CYCLE_F,
@@ -630,6 +761,7 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
         if (st != PFC_OK) return st;
     }
     if (ahead) std::swap(h->lev[0].u, h->lev[0].u2);
+    if (brick) h->retract_ahead();
     step_end(h, phi_next, mu, omega);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(h->stream));

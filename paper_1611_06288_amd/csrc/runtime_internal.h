@@ -23,12 +23,16 @@ struct Level {
     Tri<double> u{nullptr, nullptr, nullptr};     // iterate
     Tri<double> f{nullptr, nullptr, nullptr};     // right-hand side
     Tri<double> ubar{nullptr, nullptr, nullptr};  // restricted fine iterate I u (scratch on level 0)
-    Tri<double> u2{nullptr, nullptr, nullptr};    // second iterate buffer (fused sweeps, fused correction)
+    Tri<double> u2{nullptr, nullptr, nullptr};    // second iterate buffer (fused sweeps, fused correction, bricks)
+    Tri<double> u3{nullptr, nullptr, nullptr};    // third iterate buffer (bricks)
+    Tri<double> fr{nullptr, nullptr, nullptr};    // I r of a coarse brick level (its f is f + N(I u))
     double *phk = nullptr;                        // phi^kappa on this level
     double *phs = nullptr;                        // phi* of the variable mobility (else null)
     bool phs_set = false;                         // phs holds a field
     bool fused = false;                           // smoothed by the fused red-black sweep
     int nz = 1;                                   // its plane ranges per column
+    bool brick = false;                           // one brick launch on either side of the descent
+    bool tail = false;                            // this level and the coarsest in one launch
     bool rt = false;                              // residuals by column tiles
     int rt_nz[RT_MODES] = {1, 1, 1, 1, 1};        // their plane ranges, per epilogue
     int pz[2] = {0, 0};  // plane ranges of the tiled interpolation onto this level (FP64, FP32)
@@ -39,14 +43,20 @@ struct Level32 {
     Tri<float> e{nullptr, nullptr, nullptr};     // correction iterate
     Tri<float> f{nullptr, nullptr, nullptr};     // right-hand side
     Tri<float> ebar{nullptr, nullptr, nullptr};  // restricted fine correction
+    Tri<float> e2{nullptr, nullptr, nullptr}, e3{nullptr, nullptr, nullptr};  // more iterate buffers (bricks)
+    Tri<float> fr{nullptr, nullptr, nullptr};    // I r of a coarse brick level
     float *phk = nullptr;                        // phi^kappa
     float *base = nullptr;                       // FP64 iterate's phi, rounded and restricted
 };
 
+// One timed launch: n of the launches that `kind` counts (a launch that runs
+// several sweeps counts as that many; its time and bytes are shared evenly).
 struct TimedLaunch {
     int kind;
     hipEvent_t a, b;
     double bytes;  // the launch's algorithmic HBM bytes
+    int n = 1;
+    bool ahead = false;  // launched before the loop's decision (see retract_ahead)
 };
 
 bool level_sizes(int n, std::vector<int> &out);
@@ -111,22 +121,35 @@ struct pfc_handle {
     double t_bytes[PFC_KERNEL_COUNT] = {};
 
     // bytes < 0: the kind's algorithmic bytes per finest-level launch
-    void begin_timed(int kind, int level, double bytes = -1.0);
+    void begin_timed(int kind, int level, double bytes = -1.0, int n = 1, bool ahead = false);
     void end_timed();
     void collect_timings();
+    // The step stopped: the sweeps of the last launch ahead of the decision,
+    // whose output is dropped, are taken out of the counts again.
+    void retract_ahead();
+    int ahead_kind = -1, ahead_n = 0;
+    double ahead_ms = 0, ahead_bytes = 0;
     ~pfc_handle();
 };
 
 namespace pfc {
 OpParams op_of(const pfc_handle *H, int l);
 // flags of cycle64 (the first two at the finest level)
-constexpr unsigned kCyclePreDone = 1;   // its first pre-sweep has already run (sweep64 nrm 1)
+constexpr unsigned kCyclePreDone = 1;   // its first pre-sweep has already run (sweep64 nrm 1;
+                                        // a brick level: the whole part before the descent)
 constexpr unsigned kCyclePostNorm = 2;  // its last post-sweep leaves the colour-1 norm half
 constexpr unsigned kCycleTauSweep = 8;  // (coarse level) f holds I r and the
                                         // iterate is still in ubar: the first pre-sweep (the
                                         // coarsest: its solve) forms the tau correction and
                                         // reads the old values there
 void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags = 0);
+// The part of a cycle before the descent on brick level l:
+// BRICK_PLAIN, BRICK_FIRST (a coarse level's first visit: f holds nothing yet,
+// I r is in fr and the iterate in ubar) or BRICK_NORM (finest level: also the
+// norm of the iterate, as the returned number of maxima in H->partial).  The
+// iterate stays in u, the smoothed one goes to another buffer, from where the
+// part after the descent takes it: dropping the launch's output costs nothing.
+int brick_pre64(pfc_handle *H, int l, int form);
 // Level l's right-hand side as its kernels read it.  In a time step the
 // first component of the finest level's S is phi^k itself (scheme-PFC-s1),
 // held bitwise in both f.a and phk; reading it from phk spares the kernels a

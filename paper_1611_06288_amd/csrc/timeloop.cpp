@@ -21,6 +21,11 @@
 // colour-1 half for the next replay.  A replay that stops leaves the iterate
 // in the pre-sweep's input buffer, which the sweep does not write.  Before a
 // step's first replay the colour-1 half is seeded with the whole-level norm.
+//
+// On a brick finest level the recorded unit is the whole part before the
+// descent, which also yields the norm of its input, then the decision, then
+// the descent and the part after it.  A replay that stops leaves the iterate
+// where it was: the first launch writes another buffer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,6 +83,10 @@ pfc_status record_graph(pfc_handle *H) {
         launch_stop_test(H->stream, H->partial, 2 * H->split_blocks, H->cfg.tol,
                          H->cfg.max_cycles, run_state(H));
         cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
+    } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
+        const int cnt = brick_pre64(H, 0, BRICK_NORM);
+        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles, run_state(H));
+        cycle64(H, 0, fcycle, kCyclePreDone);
     } else {
         const int cnt = enqueue_norm64(H);
         launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles,
