@@ -41,8 +41,14 @@ constexpr double kFloorQ = 0.5;
 pfc_status mixed_init(pfc_handle *H) {
     if (hipEventCreateWithFlags(&H->norm_ev, hipEventDisableTiming) != hipSuccess)
         return fail(H, PFC_ERR_HIP, "event creation failed");
+    const int slots = pair_slots(H->device, true);
     for (int l = 0; l < H->nlev; ++l) {
         Level32 &A = H->lev32[l];
+        // a pair leaves the iterate in the other buffer, a cycle (recorded
+        // once) must not: an even number of pairs per visit
+        const int pairs = H->cfg.nu1 / 2 + H->cfg.nu2 / 2;
+        A.pair = pair_fits(H->lev[l].n, true) && pairs > 0 && (pairs & 1) == 0;
+        A.pnz = pair_nz(H->lev[l].n, slots);
         const size_t P = H->lev[l].P;
         float *e, *f, *eb;
         const bool ok = dalloc(H, &e, 3 * P) && dalloc(H, &f, 3 * P) && dalloc(H, &eb, 3 * P) &&
@@ -51,11 +57,16 @@ pfc_status mixed_init(pfc_handle *H) {
         A.e = Tri<float>{e, e + P, e + 2 * P};
         A.f = Tri<float>{f, f + P, f + 2 * P};
         A.ebar = Tri<float>{eb, eb + P, eb + 2 * P};
-        if (H->lev[l].brick) {
-            float *e2, *fr;
-            if (!dalloc(H, &e2, 3 * P) || !dalloc(H, &fr, 3 * P))
+        if (H->lev[l].brick || A.pair) {
+            float *e2;
+            if (!dalloc(H, &e2, 3 * P))
                 return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
             A.e2 = Tri<float>{e2, e2 + P, e2 + 2 * P};
+        }
+        if (H->lev[l].brick) {
+            float *fr;
+            if (!dalloc(H, &fr, 3 * P))
+                return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
             A.fr = Tri<float>{fr, fr + P, fr + 2 * P};
             if (!brick_small(H->lev[l].n)) {
                 float *e3;
@@ -90,6 +101,26 @@ static void sweep32(pfc_handle *H, int l, bool tau = false) {
             launch_smooth<float, true>(H->stream, op, colour, 0, A.e, cst(A.f), A.phk, A.base);
         H->end_timed();
     }
+}
+
+// The sweeps of one side of the descent, in pairs where the level takes two per
+// launch; tau: on I e = ebar, the first forming the tau correction.
+static void sweeps32(pfc_handle *H, int l, int count, bool tau = false) {
+    Level32 &A = H->lev32[l];
+    int s = 0;
+    for (; A.pair && s + 1 < count; s += 2) {
+        const bool t = tau && s == 0;
+        const OpParams op = op_of(H, l);
+        if (t)
+            launch_tau<float, true>(H->stream, op, cst(A.ebar), A.f, Tri<float>{nullptr, nullptr, nullptr},
+                                    A.phk, A.base);
+        H->begin_timed(PFC_KERNEL_SMOOTH0, l, 40.0 * (double)H->lev[l].P, 4);  // counted as half-sweeps
+        launch_sweep_pair32(H->stream, op, A.pnz, t ? cst(A.ebar) : cst(A.e), A.e2, cst(A.f), A.phk, A.base,
+                            s + 2 < count);
+        H->end_timed();
+        std::swap(A.e, A.e2);
+    }
+    for (; s < count; ++s) sweep32(H, l, tau && s == 0);
 }
 
 // Where the restriction onto level l leaves I r.
@@ -179,7 +210,7 @@ static void cycle32(pfc_handle *H, int l, bool fcycle, bool tau = false) {
     }
     Level32 &B = H->lev32[l + 1];
     const Lay &LB = H->lev[l + 1].lay;
-    for (int s = 0; s < H->cfg.nu1; ++s) sweep32(H, l, tau && s == 0);
+    sweeps32(H, l, H->cfg.nu1, tau);
     H->begin_timed(PFC_KERNEL_RESIDUAL0, l);
     if (H->lev[l].rt) {
         ResidTileArgs ra;
@@ -207,7 +238,7 @@ static void cycle32(pfc_handle *H, int l, bool fcycle, bool tau = false) {
     launch_prolong<float>(H->stream, LB, H->lev[l].lay, cst(B.e), cst(B.ebar), A.e, nullptr,
                           H->cfg.nu2 >= 1, H->lev[l].pz[1]);
     H->end_timed();
-    for (int s = 0; s < H->cfg.nu2; ++s) sweep32(H, l);
+    sweeps32(H, l, H->cfg.nu2);
 }
 
 // One FP32 cycle recorded as a graph on the handle's own stream (its

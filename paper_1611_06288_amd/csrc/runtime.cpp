@@ -14,6 +14,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -155,7 +156,7 @@ void invalidate_coarse(pfc_handle *H) {
 
 // ------------------------------------------------------------ timing
 
-void pfc_handle::begin_timed(int kind, int level, double bytes, int n, bool ahead) {
+void pfc_handle::begin_timed(int kind, int level, double bytes, int n, bool ahead, int kind2) {
     cur_event = -1;
     if (!timing || kind < 0) return;
     if (kind != PFC_KERNEL_COARSE && level != 0) return;
@@ -174,7 +175,7 @@ void pfc_handle::begin_timed(int kind, int level, double bytes, int n, bool ahea
     }
     (void)hipEventRecord(a, stream);
     pending.push_back(
-        TimedLaunch{kind, a, b, bytes >= 0.0 ? bytes : algorithmic_bytes(this, kind), n, ahead});
+        TimedLaunch{kind, a, b, bytes >= 0.0 ? bytes : algorithmic_bytes(this, kind), n, ahead, kind2});
     cur_event = (int)pending.size() - 1;
 }
 
@@ -188,15 +189,20 @@ void pfc_handle::collect_timings() {
     for (auto &t : pending) {
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, t.a, t.b) == hipSuccess) {
-            t_count[t.kind] += t.n;
-            t_ms[t.kind] += ms;
-            t_bytes[t.kind] += t.bytes;
+            const bool two = t.kind2 >= 0;
+            const double dms = two ? 0.5 * ms : ms, db = two ? 0.5 * t.bytes : t.bytes;
+            for (const int k : {t.kind, t.kind2}) {
+                if (k < 0) continue;
+                t_count[k] += t.n;
+                t_ms[k] += dms;
+                t_bytes[k] += db;
+            }
             if (t.ahead) {
                 if (ahead_kind < 0) ahead_n = 0, ahead_ms = 0, ahead_bytes = 0;
-                ahead_kind = t.kind;
+                ahead_kind = two ? t.kind2 : t.kind;
                 ahead_n += t.n;
-                ahead_ms += ms;
-                ahead_bytes += t.bytes;
+                ahead_ms += dms;
+                ahead_bytes += db;
             }
         }
         pool.push_back(t.a);
@@ -249,7 +255,7 @@ void sweep64(pfc_handle *H, int l, int nrm, bool then_sweep, bool tau) {
     if (A.fused) {  // one pass, then the two iterate buffers trade places
         if (!H->split_norm || l != 0) nrm = 0;
         unsigned long long *part =
-            nrm == 1 ? H->partial : (nrm == 2 ? H->partial + H->split_blocks : nullptr);
+            nrm == 1 ? H->partial : (nrm == 2 ? H->partial + H->split_pre : nullptr);
         const bool skip0 = then_sweep && nrm != 2;
         const int kind = nrm == 1 ? PFC_KERNEL_SWEEP_NORM0 : PFC_KERNEL_SMOOTH0;
         // the colour-0 mu, omega writes left out: 8 B/pt fewer
@@ -283,6 +289,55 @@ void sweep64(pfc_handle *H, int l, int nrm, bool then_sweep, bool tau) {
                                          nullptr);
         H->end_timed();
     }
+}
+
+// Two sweeps in one launch; nrm, then_sweep as sweep64's (nrm 1: of the first,
+// 2: of the second).  tau: on I u, the right-hand side taking the tau correction
+// in a launch before it.
+static void pair64(pfc_handle *H, int l, int nrm, bool then_sweep, bool tau = false) {
+    Level &A = H->lev[l];
+    if (tau)
+        launch_tau<double, false>(H->stream, op_of(H, l), cst(A.ubar), A.f,
+                                  Tri<double>{nullptr, nullptr, nullptr}, A.phk, nullptr);
+    if (!H->split_norm || l != 0) nrm = 0;
+    const Tri<const double> f = frhs(H, l);
+    unsigned long long *part =
+        nrm == 1 ? H->partial : (nrm == 2 ? H->partial + H->split_pre : nullptr);
+    const bool skip0 = then_sweep && nrm != 2;
+    // one sweep's bytes for both: the fused sweep's, plus what the norm reads
+    const double bytes = algorithmic_bytes(H, nrm == 1 ? PFC_KERNEL_SWEEP_NORM0 : PFC_KERNEL_SMOOTH0) -
+                         (skip0 ? 8.0 * (double)A.P : 0.0);
+    if (nrm == 1) {
+        H->ahead_kind = -1;
+        H->begin_timed(PFC_KERNEL_SWEEP_NORM0, l, bytes, 1, true, PFC_KERNEL_SMOOTH0);
+    } else {
+        H->begin_timed(PFC_KERNEL_SMOOTH0, l, bytes, 2);
+    }
+    launch_sweep_pair64(H->stream, op_of(H, l), H->cfg.lin == PFC_LIN_PICARD, A.pnz,
+                        tau ? cst(A.ubar) : cst(A.u), A.u2, f,
+                        A.phk, nrm, part, skip0);
+    H->end_timed();
+    std::swap(A.u, A.u2);
+}
+
+void sweeps64(pfc_handle *H, int l, int from, int count, int nrm, bool tau) {
+    for (int s = from; s < count;) {
+        const bool two = H->lev[l].pair && s + 1 < count;
+        const int e = s + (two ? 2 : 1);
+        const int q = (nrm & 1) && s == from ? 1 : (nrm & 2) && e == count ? 2 : 0;
+        if (two)
+            pair64(H, l, q, e < count, tau && s == 0);
+        else
+            sweep64(H, l, q, e < count, tau && s == 0);
+        s = e;
+    }
+}
+
+void ahead64(pfc_handle *H) {
+    if (ahead_sweeps(H) == 2)
+        pair64(H, 0, 1, H->cfg.nu1 > 2);
+    else
+        sweep64(H, 0, 1, H->cfg.nu1 >= 2);
 }
 
 // Where the restriction onto level l leaves I r.
@@ -389,8 +444,7 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
         return;
     }
     Level &B = H->lev[l + 1];
-    for (int s = (flags & kCyclePreDone) ? 1 : 0; s < H->cfg.nu1; ++s)
-        sweep64(H, l, 0, s + 1 < H->cfg.nu1, s == 0 && (flags & kCycleTauSweep));
+    sweeps64(H, l, (flags & kCyclePreDone) ? ahead_sweeps(H) : 0, H->cfg.nu1, 0, flags & kCycleTauSweep);
     H->begin_timed(PFC_KERNEL_RESIDUAL0, l);
     if (A.rt) {
         ResidTileArgs ra;
@@ -420,9 +474,7 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
     launch_prolong<double>(H->stream, B.lay, A.lay, cst(B.u), cst(B.ubar), A.u, H->gate,
                            H->cfg.nu2 >= 1, A.pz[0]);
     H->end_timed();
-    for (int s = 0; s < H->cfg.nu2; ++s)
-        sweep64(H, l, (flags & kCyclePostNorm) && s == H->cfg.nu2 - 1 ? 2 : 0,
-                s + 1 < H->cfg.nu2);
+    sweeps64(H, l, 0, H->cfg.nu2, (flags & kCyclePostNorm) ? 2 : 0);
 }
 
 void restrict_phk(pfc_handle *H) {
@@ -563,6 +615,7 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
     if (hipGetDevice(&device) != hipSuccess) device = 0;
     const bool mob = cfg->mobility == PFC_MOBILITY_QUADRATIC;
     const int slots = fused_slots(device, mob);
+    const int p_slots = pair_slots(device, false);
     int rt_slots[RT_MODES];
     for (int m = 0; m < RT_MODES; ++m) rt_slots[m] = resid_tile_slots(device, m, mob);
     const int pt_slots[2] = {prolong_tile_slots(device, false), prolong_tile_slots(device, true)};
@@ -587,6 +640,11 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
         if (l + 1 < H->nlev)
             for (int t = 0; t < 2; ++t) A.pz[t] = prolong_tile_nzr(pt_slots[t], A.n / 2, A.n);
         A.fused = l < H->nlev - 1 && fused_fits(A.n);
+        // (a cycle recorded as a graph needs an even number of launches, each of
+        // which exchanges the iterate buffers: pairs must not make it odd)
+        A.pair = A.fused && !mob && pair_fits(A.n, false);
+        A.pair = A.pair && ((sweep_launches(H, l) & 1) == 0 || ((cfg->nu1 + cfg->nu2) & 1));
+        A.pnz = pair_nz(A.n, p_slots);
         const bool sweeps = cfg->nu1 >= 1 && cfg->nu1 <= kBrickMaxSweeps && cfg->nu2 >= 1 &&
                             cfg->nu2 <= kBrickMaxSweeps;
         A.brick = l < H->nlev - 1 && sweeps && brick_size(A.n);
@@ -614,9 +672,12 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
     ok = ok && dalloc(H, &H->partial, (size_t)3 * kMaxReduceBlocks + 16);
     if (ok) {  // the split stop test (the graph loop seeds it behind both halves)
         const Level &A = H->lev[0];
-        H->split_blocks = A.fused ? fused_blocks(A.n, A.nz) : 0;
-        H->split_norm = A.fused && cfg->nu1 >= 1 && cfg->nu2 >= 1 &&
-                        cfg->precision == PFC_FP64 && H->split_blocks <= kMaxReduceBlocks;
+        const int one = A.fused ? fused_blocks(A.n, A.nz) : 0;
+        const int two = A.pair ? pair_blocks(A.n, A.pnz) : 0;
+        H->split_pre = ahead_sweeps(H) == 2 ? two : one;
+        H->split_post = A.pair && cfg->nu2 >= 2 && (cfg->nu2 & 1) == 0 ? two : one;
+        H->split_norm = A.fused && cfg->nu1 >= 1 && cfg->nu2 >= 1 && cfg->precision == PFC_FP64 &&
+                        std::max(H->split_pre, H->split_post) <= kMaxReduceBlocks;
     }
     ok = ok && dalloc(H, &H->d_scal, 16) && dalloc(H, &H->d_iters, 4);
     ok = ok && dalloc(H, &H->energy_part, (size_t)6 * kMaxReduceBlocks + 16);
@@ -749,11 +810,11 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
         ++c;
         pfc_status st;
         if (split) {
-            // the first pre-sweep of the next cycle; a second pre-sweep follows it
-            // when nu1 >= 2 (and if the loop stops its output is dropped)
-            sweep64(h, 0, 1, h->cfg.nu1 >= 2);
+            // the first pre-sweeps of the next cycle (if the loop stops their
+            // output is dropped)
+            ahead64(h);
             ahead = true;
-            st = read_norm(h, 2 * h->split_blocks, &rho);
+            st = read_norm(h, h->split_pre + h->split_post, &rho);
         } else {
             ahead = false;
             st = resid_norm64(h, Tri<double>{nullptr, nullptr, nullptr}, &rho);
@@ -761,7 +822,7 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
         if (st != PFC_OK) return st;
     }
     if (ahead) std::swap(h->lev[0].u, h->lev[0].u2);
-    if (brick) h->retract_ahead();
+    if (brick || (ahead && ahead_sweeps(h) == 2)) h->retract_ahead();
     step_end(h, phi_next, mu, omega);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(h->stream));

@@ -31,6 +31,8 @@ struct Level {
     bool phs_set = false;                         // phs holds a field
     bool fused = false;                           // smoothed by the fused red-black sweep
     int nz = 1;                                   // its plane ranges per column
+    bool pair = false;                            // two sweeps in a row take one launch (sweep_pair.h)
+    int pnz = 1;                                  // its plane ranges per column
     bool brick = false;                           // one brick launch on either side of the descent
     bool tail = false;                            // this level and the coarsest in one launch
     bool rt = false;                              // residuals by column tiles
@@ -43,8 +45,10 @@ struct Level32 {
     Tri<float> e{nullptr, nullptr, nullptr};     // correction iterate
     Tri<float> f{nullptr, nullptr, nullptr};     // right-hand side
     Tri<float> ebar{nullptr, nullptr, nullptr};  // restricted fine correction
-    Tri<float> e2{nullptr, nullptr, nullptr}, e3{nullptr, nullptr, nullptr};  // more iterate buffers (bricks)
+    Tri<float> e2{nullptr, nullptr, nullptr}, e3{nullptr, nullptr, nullptr};  // more iterate buffers (bricks, pairs)
     Tri<float> fr{nullptr, nullptr, nullptr};    // I r of a coarse brick level
+    bool pair = false;                           // two sweeps in a row take one launch (sweep_pair.h)
+    int pnz = 1;                                 // its plane ranges per column
     float *phk = nullptr;                        // phi^kappa
     float *base = nullptr;                       // FP64 iterate's phi, rounded and restricted
 };
@@ -57,6 +61,7 @@ struct TimedLaunch {
     double bytes;  // the launch's algorithmic HBM bytes
     int n = 1;
     bool ahead = false;  // launched before the loop's decision (see retract_ahead)
+    int kind2 = -1;      // the launch's second sweep counts there; half its time and bytes
 };
 
 bool level_sizes(int n, std::vector<int> &out);
@@ -86,16 +91,16 @@ struct pfc_handle {
     double *energy_part = nullptr;
     // stop test split over the finest level's fused sweeps (FP64, M = 1): the
     // last post-sweep of a cycle leaves the colour-1 half of the norm in
-    // partial[split_blocks .. 2 split_blocks), the next cycle's first
-    // pre-sweep, run ahead of the decision, the colour-0 half in
-    // partial[0 .. split_blocks)
+    // partial[split_pre .. split_pre + split_post), the next cycle's first
+    // pre-sweep (with the second, where two take one launch), run ahead of
+    // the decision, the colour-0 half in partial[0 .. split_pre)
     bool split_norm = false;
     // Set by a time step's set-up: the finest level's f.a holds phi^k, a copy
     // of phk (the first component of S is phi^k itself), so the finest-level
     // kernels read phk in its place (see frhs).  Cleared by the entry points
     // that load a caller's right-hand side into the finest level.
     bool f1_phk = false;
-    int split_blocks = 0;
+    int split_pre = 0, split_post = 0;
     // graph-driven time loop (pfc_run)
     const int *gate = nullptr;            // cycle gate, set only while its graph is recorded
     hipStream_t run_stream = nullptr;     // the loop's own stream (capturable)
@@ -121,7 +126,8 @@ struct pfc_handle {
     double t_bytes[PFC_KERNEL_COUNT] = {};
 
     // bytes < 0: the kind's algorithmic bytes per finest-level launch
-    void begin_timed(int kind, int level, double bytes = -1.0, int n = 1, bool ahead = false);
+    void begin_timed(int kind, int level, double bytes = -1.0, int n = 1, bool ahead = false,
+                     int kind2 = -1);
     void end_timed();
     void collect_timings();
     // The step stopped: the sweeps of the last launch ahead of the decision,
@@ -135,7 +141,7 @@ struct pfc_handle {
 namespace pfc {
 OpParams op_of(const pfc_handle *H, int l);
 // flags of cycle64 (the first two at the finest level)
-constexpr unsigned kCyclePreDone = 1;   // its first pre-sweep has already run (sweep64 nrm 1;
+constexpr unsigned kCyclePreDone = 1;   // its first pre-sweeps have already run (ahead64;
                                         // a brick level: the whole part before the descent)
 constexpr unsigned kCyclePostNorm = 2;  // its last post-sweep leaves the colour-1 norm half
 constexpr unsigned kCycleTauSweep = 8;  // (coarse level) f holds I r and the
@@ -169,6 +175,20 @@ inline Tri<const double> frhs(const pfc_handle *H, int l) {
 // becomes the iterate).
 void sweep64(pfc_handle *H, int l, int nrm = 0, bool then_sweep = false,
              bool tau = false);
+// Sweeps from .. count - 1 of one side of the descent, in pairs where the level
+// takes two per launch.  nrm: bit 0 asks the first for the colour-0 half of the
+// norm of its input, bit 1 the last for the colour-1 half of its output; tau:
+// sweep 0 forms the tau correction.
+void sweeps64(pfc_handle *H, int l, int from, int count, int nrm = 0, bool tau = false);
+// The pre-sweeps that run ahead of the loop's decision (split_norm): the first,
+// or the first two where they take one launch.  One exchange of the iterate
+// buffers, so exchanging them back drops the launch.
+inline int sweep_launches(const pfc_handle *H, int l) {  // a cycle's, both sides of the descent
+    const int c = H->lev[l].pair ? 1 : 0;
+    return ((H->cfg.nu1 + c) >> c) + ((H->cfg.nu2 + c) >> c);
+}
+inline int ahead_sweeps(const pfc_handle *H) { return H->lev[0].pair && H->cfg.nu1 >= 2 ? 2 : 1; }
+void ahead64(pfc_handle *H);
 void restrict_phk(pfc_handle *H);
 pfc_status resid_norm64(pfc_handle *H, Tri<double> r, double *out);
 int enqueue_norm64(pfc_handle *H, unsigned long long *dst = nullptr);

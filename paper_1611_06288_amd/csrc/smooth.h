@@ -18,28 +18,51 @@ namespace pfc {
 // c is the linearised slope of the cubic term; eliminating omega and mu gives
 // phi = (r1 - A r2 + A B r3) / (1 + A (c + B Dd)).
 // One thread per point of colour `colour` (colour-split storage only).
+// The level's coefficients in that solve.
+struct PointCoef {
+    double h2inv, tau, lin_c, w3, A, AB, B, Dd, BD;
+    int fo;
+    __device__ __forceinline__ explicit PointCoef(const OpParams &op)
+        : h2inv(op.h2inv), tau(op.tau), lin_c(lin_of(op)), w3(w3_of(op)), A(6.0 * op.tau * op.h2inv),
+          B(6.0 * op.h2inv), Dd((op.fo ? 6.0 : 3.0) * op.h2inv), fo(op.fo) {
+        AB = A * B;
+        BD = B * Dd;
+    }
+    // into scalar registers: a kernel that is short of vector registers would
+    // otherwise keep these values, the same in every lane, in eighteen of them
+    __device__ __forceinline__ void to_scalar() {
+        for (double *v : {&h2inv, &tau, &lin_c, &w3, &A, &AB, &B, &Dd, &BD}) *v = lane_value(*v, 0);
+    }
+};
+
+template <bool DELTA>
+__device__ __forceinline__ void point_solve(const PointCoef &q, int picard, double phin, double a,
+                                            double b, double f1, double f2, double f3, double smu,
+                                            double som, double sphi, double &phi, double &mu,
+                                            double &om) {
+    double c, r2;
+    if (!DELTA && picard) {  // second order: 1/4(phin^2 + a^2) phi; first order: phin^2 phi
+        const double qq = q.fo ? phin * phin : 0.25 * (phin * phin + a * a);
+        c = qq + q.lin_c;
+        r2 = f2 + som * q.h2inv + (q.fo ? 0.0 : qq * a);
+    } else {
+        const double gp = dg_of<DELTA>(q.fo, phin, a, b);
+        c = gp + q.lin_c;
+        r2 = f2 + som * q.h2inv + (g_of<DELTA>(q.fo, phin, a, b) - gp * phin);
+    }
+    const double r1 = f1 + q.tau * smu * q.h2inv;
+    const double r3 = f3 + q.w3 * sphi * q.h2inv;
+    phi = (r1 - q.A * r2 + q.AB * r3) / (1.0 + q.A * (c + q.BD));
+    om = r3 - q.Dd * phi;
+    mu = r2 + c * phi - q.B * om;
+}
+
 template <bool DELTA>
 __device__ __forceinline__ void point_solve(const OpParams &op, int picard, double phin, double a,
                                             double b, double f1, double f2, double f3, double smu,
                                             double som, double sphi, double &phi, double &mu,
                                             double &om) {
-    const double h2inv = op.h2inv, tau = op.tau, lin_c = lin_of(op);
-    double c, r2;
-    if (!DELTA && picard) {  // second order: 1/4(phin^2 + a^2) phi; first order: phin^2 phi
-        const double qq = op.fo ? phin * phin : 0.25 * (phin * phin + a * a);
-        c = qq + lin_c;
-        r2 = f2 + som * h2inv + (op.fo ? 0.0 : qq * a);
-    } else {
-        const double gp = dg_of<DELTA>(op.fo, phin, a, b);
-        c = gp + lin_c;
-        r2 = f2 + som * h2inv + (g_of<DELTA>(op.fo, phin, a, b) - gp * phin);
-    }
-    const double r1 = f1 + tau * smu * h2inv;
-    const double r3 = f3 + w3_of(op) * sphi * h2inv;
-    const double A = 6.0 * tau * h2inv, B = 6.0 * h2inv, Dd = (op.fo ? 6.0 : 3.0) * h2inv;
-    phi = (r1 - A * r2 + A * B * r3) / (1.0 + A * (c + B * Dd));
-    om = r3 - Dd * phi;
-    mu = r2 + c * phi - B * om;
+    point_solve<DELTA>(PointCoef(op), picard, phin, a, b, f1, f2, f3, smu, som, sphi, phi, mu, om);
 }
 
 // Pointwise solve with variable mobility: the first equation becomes

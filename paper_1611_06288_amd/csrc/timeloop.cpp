@@ -43,13 +43,13 @@ RunState run_state(pfc_handle *H) {
 }
 
 // The recorded cycle assumes the level iterates it was recorded with; levels
-// smoothed by the fused sweep trade their two buffers once per sweep, which
-// leaves them in place over a cycle only for an even sweep count.
+// smoothed by the fused sweep trade their two buffers once per launch, which
+// leaves them in place over a cycle (an F-cycle visits the coarse ones again)
+// only for an even number of launches.
 bool graph_usable(const pfc_handle *H) {
     if (H->cfg.precision != PFC_FP64) return false;
-    if (((H->cfg.nu1 + H->cfg.nu2) & 1) == 0) return true;
     for (int l = 0; l < H->nlev; ++l)
-        if (H->lev[l].fused) return false;
+        if (H->lev[l].fused && (sweep_launches(H, l) & 1)) return false;
     return true;
 }
 
@@ -79,8 +79,8 @@ pfc_status record_graph(pfc_handle *H) {
     H->gate = H->d_run;  // every launch below reads the active flag
     const bool fcycle = H->cfg.cycle == PFC_CYCLE_F;
     if (H->split_norm) {
-        sweep64(H, 0, 1, H->cfg.nu1 >= 2);
-        launch_stop_test(H->stream, H->partial, 2 * H->split_blocks, H->cfg.tol,
+        ahead64(H);
+        launch_stop_test(H->stream, H->partial, H->split_pre + H->split_post, H->cfg.tol,
                          H->cfg.max_cycles, run_state(H));
         cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
     } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
@@ -109,9 +109,9 @@ pfc_status graph_step(pfc_handle *H, const double *prev, const double *cur, doub
     step_begin(H, prev, cur, mu, om);
     launch_run_reset(H->stream, run_state(H));
     if (H->split_norm) {
-        unsigned long long *whole = H->partial + 2 * H->split_blocks;
+        unsigned long long *whole = H->partial + H->split_pre + H->split_post;
         const int cnt = enqueue_norm64(H, whole);
-        launch_norm_seed(H->stream, whole, cnt, H->partial + H->split_blocks, H->split_blocks);
+        launch_norm_seed(H->stream, whole, cnt, H->partial + H->split_pre, H->split_post);
     }
     HIP_TRY(H, hipGetLastError());
     if (!graph_current(H)) {
