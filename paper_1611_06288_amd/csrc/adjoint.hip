@@ -22,7 +22,7 @@
 //     (I - tau D Lap - tau/2 Lap^3) lambda1 = b1 + D b2 + 1/2 Lap(b3 + Lap b2).
 #include <cmath>
 
-#include "device_common.h"
+#include "coarse.h"
 #include "runtime_internal.h"
 
 namespace pfc {
@@ -133,76 +133,16 @@ __global__ __launch_bounds__(kBlock) void k_adj_resid_restrict(OpParams op, Lay 
     }
 }
 
-// Exact solve on the coarsest level (natural layout, P <= 64), one wavefront.
-// minv caches (I - tau D Lap - tau/2 Lap^3)^{-1} while *valid is set.
 __global__ __launch_bounds__(64) void k_adj_coarse(OpParams op, Tri<double> lam,
                                                    Tri<const double> b,
                                                    const double *__restrict__ D,
                                                    const double *__restrict__ lap1,
                                                    const double *__restrict__ lap3, double *minv,
                                                    int *valid) {
-    __shared__ double A[64 * 64];
-    __shared__ double vec[64];
-    __shared__ int perm[64];
-    const int n = op.lay.n, P = n * n * n;
-    const int p = threadIdx.x;
-    const bool act = p < P;
-    int nb[6] = {0, 0, 0, 0, 0, 0};
-    if (act) {
-        const int i = p % n, j = (p / n) % n, k = p / (n * n);
-        nb[0] = (k * n + j) * n + wrap_p(i, n);
-        nb[1] = (k * n + j) * n + wrap_m(i, n);
-        nb[2] = (k * n + wrap_p(j, n)) * n + i;
-        nb[3] = (k * n + wrap_m(j, n)) * n + i;
-        nb[4] = (wrap_p(k, n) * n + j) * n + i;
-        nb[5] = (wrap_m(k, n) * n + j) * n + i;
-    }
-    auto lap_lds = [&](double own) -> double {
-        return ((vec[nb[0]] + vec[nb[1]]) + (vec[nb[2]] + vec[nb[3]]) + (vec[nb[4]] + vec[nb[5]]) -
-                6.0 * own) * op.h2inv;
-    };
-    const double d = act ? D[p] : 0.0;
-    const double b1 = act ? b.a[p] : 0.0, b2 = act ? b.b[p] : 0.0, b3 = act ? b.c[p] : 0.0;
-    if (!*valid) {
-        if (act)
-            for (int q = 0; q < P; ++q) {
-                const int o = q * P + p;
-                A[o] = (q == p ? 1.0 : 0.0) - op.tau * d * lap1[o] - 0.5 * op.tau * lap3[o];
-            }
-        __syncthreads();
-        gj_invert(A, P, perm);
-        if (act)
-            for (int q = 0; q < P; ++q) minv[q * P + p] = A[q * P + p];
-        __syncthreads();
-    }
-    // rhs = b1 + D b2 + 1/2 Lap(b3 + Lap b2)
-    vec[p] = b2;
-    __syncthreads();
-    const double lb2 = act ? lap_lds(b2) : 0.0;
-    __syncthreads();
-    vec[p] = b3 + lb2;
-    __syncthreads();
-    const double rhs = b1 + d * b2 + 0.5 * (act ? lap_lds(b3 + lb2) : 0.0);
-    __syncthreads();
-    vec[p] = rhs;
-    __syncthreads();
-    double l1 = 0.0;
-    if (act)
-        for (int q = 0; q < P; ++q) l1 += minv[q * P + p] * vec[q];
-    __syncthreads();
-    vec[p] = l1;
-    __syncthreads();
-    const double l2 = b2 + op.tau * (act ? lap_lds(l1) : 0.0);
-    __syncthreads();
-    vec[p] = l2;
-    __syncthreads();
-    const double l3 = b3 + (act ? lap_lds(l2) : 0.0);
-    if (act) {
-        lam.a[p] = l1;
-        lam.b[p] = l2;
-        lam.c[p] = l3;
-    }
-    if (p == 0) *valid = 1;
+    __shared__ CoarseShared sm;
+    const bool cached = coarse_load_inverse<64>(minv, valid, sm);
+    wave_sync();
+    adj_coarse_body(op, lam, b, D, lap1, lap3, minv, cached, valid, sm);
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill(double *p, size_t count, double v) {
@@ -289,8 +229,70 @@ static void adj_sweep(pfc_handle *H, int l) {
                            colour, A.u, cst(A.f), (const double *)A.phk);
 }
 
-static void adj_cycle(pfc_handle *H, int l, bool fcycle) {
+// The part of a cycle before the descent on brick level l (as brick_pre64).
+// BRICK_FIRST: a coarse level's first visit, from zero.
+static int adj_brick_pre(pfc_handle *H, int l, int form) {
     Level &A = H->lev[l];
+    BrickArgs<double> a;
+    a.op = op_of(H, l);
+    a.f = cst(A.f);
+    a.phk = A.phk;
+    a.LC = H->lev[l + 1].lay;
+    a.fo = A.f;  // the right-hand side stays what it is
+    a.cr = H->lev[l + 1].f;
+    a.part = H->partial;
+    brick_run_pre<double>(a, H->cfg.nu1, cst(A.u), A.u2, A.u3, form,
+                          [&](const BrickArgs<double> &b, int kind, int sweeps, int fm) {
+                              launch_brick_adj(H->stream, b, kind, sweeps, fm);
+                          });
+    return brick_blocks(A.n);
+}
+
+static void adj_brick_post(pfc_handle *H, int l) {
+    Level &A = H->lev[l];
+    BrickArgs<double> a;
+    a.op = op_of(H, l);
+    a.f = cst(A.f);
+    a.phk = A.phk;
+    a.LC = H->lev[l + 1].lay;
+    a.v = cst(H->lev[l + 1].u);
+    brick_run_post<double>(a, H->cfg.nu1, H->cfg.nu2, A.u, A.u2, A.u3,
+                           [&](const BrickArgs<double> &b, int kind, int sweeps, int fm) {
+                               launch_brick_adj(H->stream, b, kind, sweeps, fm);
+                           });
+}
+
+static void adj_tail(pfc_handle *H, int l, bool fcycle) {
+    Level &A = H->lev[l];
+    TailArgs<double> a;
+    a.op = op_of(H, l);
+    a.opc = op_of(H, l + 1);
+    a.nu1 = H->cfg.nu1;
+    a.nu2 = H->cfg.nu2;
+    a.fcycle = fcycle ? 1 : 0;
+    a.u = A.u;
+    a.f = cst(A.f);
+    a.phk = A.phk;
+    a.phkc = H->lev[l + 1].phk;
+    a.lap1 = H->lap1;
+    a.lap3 = H->lap3;
+    a.minv = H->minv_adj;
+    a.valid = H->valid_adj;
+    launch_tail_adj(H->stream, a);
+}
+
+// first: a coarse level's first visit, its right-hand side new and its iterate
+// to start from zero (clear already on a level without bricks); done: the part
+// before the descent has already run.
+static void adj_cycle(pfc_handle *H, int l, bool fcycle, bool first, bool done = false) {
+    Level &A = H->lev[l];
+    if (A.tail) return adj_tail(H, l, fcycle);
+    if (A.brick) {
+        if (!done) adj_brick_pre(H, l, first ? BRICK_FIRST : BRICK_PLAIN);
+        adj_cycle(H, l + 1, fcycle, true);
+        if (fcycle && !H->lev[l + 1].tail) adj_cycle(H, l + 1, false, false);
+        return adj_brick_post(H, l);
+    }
     if (l == H->nlev - 1) {
         hipLaunchKernelGGL(k_adj_coarse, dim3(1), dim3(64), 0, H->stream, op_of(H, l), A.u, cst(A.f),
                            (const double *)A.phk, (const double *)H->lap1,
@@ -301,16 +303,19 @@ static void adj_cycle(pfc_handle *H, int l, bool fcycle) {
     for (int s = 0; s < H->cfg.nu1; ++s) adj_sweep(H, l);
     hipLaunchKernelGGL(k_adj_resid_restrict, dim3(blocks_for(8 * B.P)), dim3(kBlock), 0, H->stream,
                        op_of(H, l), B.lay, cst(A.u), cst(A.f), (const double *)A.phk, B.f, B.u);
-    adj_cycle(H, l + 1, fcycle);
-    if (fcycle) adj_cycle(H, l + 1, false);
+    adj_cycle(H, l + 1, fcycle, true);
+    if (fcycle && !B.tail) adj_cycle(H, l + 1, false, false);
     launch_prolong<double>(H->stream, B.lay, A.lay, cst(B.u),
                            Tri<const double>{nullptr, nullptr, nullptr}, A.u, nullptr, false,
                            A.pz[0]);
     for (int s = 0; s < H->cfg.nu2; ++s) adj_sweep(H, l);
 }
 
+// The norm of the residual; on a brick level by the next cycle's launches before
+// the descent, ahead of the loop's decision (they leave the iterate alone).
 static pfc_status adj_norm(pfc_handle *H, double *out) {
     Level &A = H->lev[0];
+    if (A.brick) return read_norm(H, adj_brick_pre(H, 0, BRICK_NORM), out);
     const unsigned blocks = reduce_blocks(A.P);
     hipLaunchKernelGGL(k_adj_resid_max, dim3(blocks), dim3(kBlock), 0, H->stream, op_of(H, 0),
                        cst(A.u), cst(A.f), (const double *)A.phk, H->partial);
@@ -346,7 +351,7 @@ pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi
             status = PFC_ERR_NOT_CONVERGED;
             break;
         }
-        adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F);
+        adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
         ++c;
         st = adj_norm(H, &rho);
         if (st != PFC_OK) return st;

@@ -33,8 +33,6 @@
 
 namespace pfc {
 
-enum { BP_FAS = 0, BP_ADJ = 1 };  // the scheme's operator; its adjoint J^T
-
 // One point's six neighbours in a brick's LDS arrays (other colour).
 template <typename G>
 struct BrickNbr {

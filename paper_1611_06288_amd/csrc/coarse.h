@@ -271,4 +271,76 @@ __device__ __forceinline__ void coarse_body(const OpParams &op, Tri<T> u, Tri<co
     }
 }
 
+// The adjoint's exact solve on the coarsest level (as coarse_body: one
+// wavefront, lane p owning point p): with lambda2 = b2 + tau Lap lambda1 and
+// lambda3 = b3 + Lap lambda2 eliminated,
+//   (I - tau D Lap - tau/2 Lap^3) lambda1 = b1 + D b2 + 1/2 Lap(b3 + Lap b2).
+// minv keeps the inverse of that matrix while *valid is set; it is in sm.A when
+// `cached`.
+__device__ __forceinline__ void adj_coarse_body(const OpParams &op, Tri<double> lam,
+                                                Tri<const double> b, const double *__restrict__ D,
+                                                const double *__restrict__ lap1,
+                                                const double *__restrict__ lap3, double *minv,
+                                                bool cached, int *valid, CoarseShared &sm) {
+    double *A = sm.A, *vec = sm.vec;
+    const int n = op.lay.n, P = n * n * n;
+    const int p = threadIdx.x;
+    const bool act = p < P;
+    int nb[6] = {0, 0, 0, 0, 0, 0};
+    if (act) {
+        const int i = p % n, j = (p / n) % n, k = p / (n * n);
+        nb[0] = (k * n + j) * n + wrap_p(i, n);
+        nb[1] = (k * n + j) * n + wrap_m(i, n);
+        nb[2] = (k * n + wrap_p(j, n)) * n + i;
+        nb[3] = (k * n + wrap_m(j, n)) * n + i;
+        nb[4] = (wrap_p(k, n) * n + j) * n + i;
+        nb[5] = (wrap_m(k, n) * n + j) * n + i;
+    }
+    auto lap_lds = [&](double own) -> double {  // of vec[]
+        return ((vec[nb[0]] + vec[nb[1]]) + (vec[nb[2]] + vec[nb[3]]) + (vec[nb[4]] + vec[nb[5]]) -
+                6.0 * own) * op.h2inv;
+    };
+    const double d = act ? D[p] : 0.0;
+    const double b1 = act ? b.a[p] : 0.0, b2 = act ? b.b[p] : 0.0, b3 = act ? b.c[p] : 0.0;
+    if (!cached) {
+        if (act)
+            for (int q = 0; q < P; ++q) {
+                const int o = q * P + p;
+                A[o] = (q == p ? 1.0 : 0.0) - op.tau * d * lap1[o] - 0.5 * op.tau * lap3[o];
+            }
+        wave_sync();
+        gj_invert(A, P, sm.perm);
+        if (act)
+            for (int q = 0; q < P; ++q) minv[q * P + p] = A[q * P + p];
+        wave_sync();
+    }
+    vec[p] = b2;
+    wave_sync();
+    const double lb2 = act ? lap_lds(b2) : 0.0;
+    wave_sync();
+    vec[p] = b3 + lb2;
+    wave_sync();
+    const double rhs = b1 + d * b2 + 0.5 * (act ? lap_lds(b3 + lb2) : 0.0);
+    wave_sync();
+    vec[p] = rhs;
+    wave_sync();
+    double l1 = 0.0;
+    if (act)
+        for (int q = 0; q < P; ++q) l1 += A[q * P + p] * vec[q];
+    wave_sync();
+    vec[p] = l1;
+    wave_sync();
+    const double l2 = b2 + op.tau * (act ? lap_lds(l1) : 0.0);
+    wave_sync();
+    vec[p] = l2;
+    wave_sync();
+    const double l3 = b3 + (act ? lap_lds(l2) : 0.0);
+    if (act) {
+        lam.a[p] = l1;
+        lam.b[p] = l2;
+        lam.c[p] = l3;
+    }
+    if (p == 0) *valid = 1;
+}
+
 }  // namespace pfc

@@ -138,6 +138,7 @@ constexpr int kPairMinN = 128, kPairMinN32 = 256;
 
 // ---- brick launches (brick.h): one level's part of a cycle on either side of
 // the descent, for levels of 12^3 to 96^3 ----
+enum { BP_FAS = 0, BP_ADJ = 1 };  // the scheme's operator; its adjoint J^T
 enum { BRICK_PRE = 0, BRICK_SWEEP = 1, BRICK_POST = 2 };  // kinds
 enum { BRICK_PLAIN = 0, BRICK_FIRST = 1, BRICK_NORM = 2 };  // forms of the first two
 template <typename T>
@@ -223,6 +224,9 @@ struct TailArgs {
 inline bool tail_size(int n) { return n == 8 || n == 6; }
 void launch_tail64(hipStream_t s, const TailArgs<double> &a);
 void launch_tail32(hipStream_t s, const TailArgs<float> &a);
+// The adjoint's: f is b, phk and phkc the diagonal D, the iterate starts at zero
+// (ub unused).
+void launch_tail_adj(hipStream_t s, const TailArgs<double> &a);
 
 // Residual of a large level by z-marching column tiles (residual.hip), with
 // one of five epilogues.

@@ -19,8 +19,11 @@ namespace pfc {
 // N: points per axis of the upper level (8 or 6).  A thread owns the x-pair of
 // points (2I + a, 2J + b, 2K + zz), one of each colour; the four threads of a
 // coarse cell are a quad of lanes.
-template <typename T, bool DELTA, bool MOB, int N>
+// PH: the scheme's cycle, or the adjoint's linear one (f = b, phk = D; the
+// iterate starts at zero and the coarse correction is the coarse iterate).
+template <typename T, int PH, bool DELTA, bool MOB, int N>
 struct Tail {
+    static constexpr bool ADJ = PH == BP_ADJ;
     static constexpr int HN = N / 2, HC = N * N * HN, NC = HN, PC = NC * NC * NC;
     static constexpr int kActive = 4 * PC, kThreads = (kActive + 63) / 64 * 64;
     static constexpr int NF = MOB ? 4 : 3;
@@ -95,7 +98,14 @@ struct Tail {
             const double phin = (double)sm.u[0][c][p.q], k = (double)ak[c];
             const double f0 = (double)f[c][0], f1 = (double)f[c][1], f2 = (double)f[c][2];
             double phi, mu, om;
-            if constexpr (MOB) {
+            if constexpr (ADJ) {
+                const double s3[3] = {sum(0, c, p), sum(1, c, p), sum(2, c, p)};
+                double l[3];
+                adj_point_solve(a.op, k, f0, f1, f2, s3, l);
+                phi = l[0];
+                mu = l[1];
+                om = l[2];
+            } else if constexpr (MOB) {
                 const double pc = (double)sm.u[3][c][p.q];
                 double msum = 0.0, smm = 0.0;
 #pragma unroll
@@ -121,7 +131,7 @@ struct Tail {
     // the first the iterate starts at I u and f takes the tau correction.  The
     // loops stay loops (the code is fetched by this one workgroup alone).
     __device__ __forceinline__ void cycles(bool cached) {
-        if (act)
+        if (act && !ADJ)
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 double ls[3], w[3], nv[3];
@@ -157,6 +167,11 @@ struct Tail {
     // the coarsest level's tau correction (starting its iterate at I u) and solves
     __device__ __forceinline__ void coarsest(int solves, bool cached) {
         const Tri<T> cu{sm.cu[0], sm.cu[1], sm.cu[2]}, cf{sm.cf[0], sm.cf[1], sm.cf[2]};
+        if constexpr (ADJ) {  // linear: a second solve would repeat the first
+            adj_coarse_body(a.opc, cu, cst(cf), a.phkc, a.lap1, a.lap3, a.minv, cached, a.valid, sm.cs);
+            wave_sync();
+            return;
+        }
         const Tri<const T> cb{sm.cb[0], sm.cb[1], sm.cb[2]};
         tau_body<T, DELTA, MOB>(a.opc, cb, cf, cu, a.phkc, a.basec, threadIdx.x);
         wave_sync();
@@ -176,8 +191,13 @@ struct Tail {
         for (int c = 0; c < 2; ++c) {
             double ls[3];
             laps(c, pt(c), ls, w[c]);
-            resid_from_lap<DELTA>(a.op, ls, w[c][0], w[c][1], w[c][2], (double)f[c][0], (double)f[c][1],
-                                  (double)f[c][2], (double)ak[c], (double)bb[c], r[c]);
+            if constexpr (ADJ)
+                adj_resid_from_lap(a.op, ls, w[c], (double)f[c][0], (double)f[c][1], (double)f[c][2],
+                                   (double)ak[c], r[c]);
+            else
+                resid_from_lap<DELTA>(a.op, ls, w[c][0], w[c][1], w[c][2], (double)f[c][0],
+                                      (double)f[c][1], (double)f[c][2], (double)ak[c], (double)bb[c],
+                                      r[c]);
         }
         const int o = (K * NC + J) * NC + I;
         const bool c1 = ((b + zz) & 1) != 0;  // the pair's even-x point is colour 1
@@ -217,7 +237,7 @@ struct Tail {
         for (int fl = 0; fl < 3; ++fl) {
             auto e = [&](int x, int y, int z) {
                 const int o = (z * NC + y) * NC + x;
-                return (double)(T)((double)sm.cu[fl][o] - (double)sm.cb[fl][o]);
+                return ADJ ? (double)sm.cu[fl][o] : (double)(T)((double)sm.cu[fl][o] - (double)sm.cb[fl][o]);
             };
             auto wt = [&](int x) {
                 return 0.75 * (0.75 * e(x, J, K) + 0.25 * e(x, J1, K)) +
@@ -238,7 +258,12 @@ struct Tail {
         for (int c = 0; c < 2; ++c) {
             const Pt p = pt(c);
             const unsigned g = (unsigned)(c * HC + p.q);  // the level's colour-split storage
-            const T ub[3] = {a.ub.a[g], a.ub.b[g], a.ub.c[g]};
+            T ub[3] = {(T)0, (T)0, (T)0};
+            if constexpr (!ADJ) {
+                ub[0] = a.ub.a[g];
+                ub[1] = a.ub.b[g];
+                ub[2] = a.ub.c[g];
+            }
             f[c][0] = a.f.a[g];
             f[c][1] = a.f.b[g];
             f[c][2] = a.f.c[g];
