@@ -42,6 +42,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_D(Lay lay, double eps, const dou
 __global__ __launch_bounds__(kBlock) void k_adj_smooth(OpParams op, int colour, Tri<double> lam,
                                                        Tri<const double> b,
                                                        const double *__restrict__ D) {
+    if (gate_closed(op.gate)) return;
     const Lay &L = op.lay;
     const int n = L.n, hn = n >> 1;
     const unsigned H = (unsigned)((size_t)n * n * n / 2);
@@ -80,6 +81,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_resid_max(OpParams op, Tri<const
                                                           Tri<const double> b,
                                                           const double *__restrict__ D,
                                                           unsigned long long *partial) {
+    if (gate_closed(op.gate)) return;
     const Lay &L = op.lay;
     const unsigned total = (unsigned)npts(L);
     unsigned long long mx = 0;
@@ -105,6 +107,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_resid_restrict(OpParams op, Lay 
                                                                Tri<const double> b,
                                                                const double *__restrict__ D,
                                                                Tri<double> bc, Tri<double> lamc) {
+    if (gate_closed(op.gate)) return;
     const unsigned g = xcd_block() * kBlock + threadIdx.x;
     const unsigned tn = g >> 3;
     const int ch = (int)(g & 7u);
@@ -140,6 +143,7 @@ __global__ __launch_bounds__(64) void k_adj_coarse(OpParams op, Tri<double> lam,
                                                    const double *__restrict__ lap3, double *minv,
                                                    int *valid) {
     __shared__ CoarseShared sm;
+    if (gate_closed(op.gate)) return;
     const bool cached = coarse_load_inverse<64>(minv, valid, sm);
     wave_sync();
     adj_coarse_body(op, lam, b, D, lap1, lap3, minv, cached, valid, sm);
@@ -306,20 +310,21 @@ static void adj_cycle(pfc_handle *H, int l, bool fcycle, bool first, bool done =
     adj_cycle(H, l + 1, fcycle, true);
     if (fcycle && !B.tail) adj_cycle(H, l + 1, false, false);
     launch_prolong<double>(H->stream, B.lay, A.lay, cst(B.u),
-                           Tri<const double>{nullptr, nullptr, nullptr}, A.u, nullptr, false,
+                           Tri<const double>{nullptr, nullptr, nullptr}, A.u, H->gate, false,
                            A.pz[0]);
     for (int s = 0; s < H->cfg.nu2; ++s) adj_sweep(H, l);
 }
 
 // The norm of the residual; on a brick level by the next cycle's launches before
 // the descent, ahead of the loop's decision (they leave the iterate alone).
-static pfc_status adj_norm(pfc_handle *H, double *out) {
+// Returns the number of maxima in H->partial.
+static int adj_norm(pfc_handle *H) {
     Level &A = H->lev[0];
-    if (A.brick) return read_norm(H, adj_brick_pre(H, 0, BRICK_NORM), out);
+    if (A.brick) return adj_brick_pre(H, 0, BRICK_NORM);
     const unsigned blocks = reduce_blocks(A.P);
     hipLaunchKernelGGL(k_adj_resid_max, dim3(blocks), dim3(kBlock), 0, H->stream, op_of(H, 0),
                        cst(A.u), cst(A.f), (const double *)A.phk, H->partial);
-    return read_norm(H, (int)blocks, out);
+    return (int)blocks;
 }
 
 pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi_cur,
@@ -339,26 +344,24 @@ pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi
     fill(H->stream, A.u.a, 3 * P, 0.0);
     (void)hipMemsetAsync(H->valid_adj, 0, sizeof(int), H->stream);
     HIP_TRY(H, hipGetLastError());
-    double bnorm = 0.0, rho = 0.0;
-    pfc_status st = adj_norm(H, &bnorm);
+    double bnorm = 0.0;
+    int parts = adj_norm(H);
+    pfc_status st = read_norm(H, parts, &bnorm);
     if (st != PFC_OK) return st;
     if (!std::isfinite(bnorm)) return fail(H, PFC_ERR_NONFINITE, "gbar_next is not finite");
     int c = 0;
     pfc_status status = PFC_OK;
-    rho = bnorm;
-    while (bnorm > 0.0 && rho > adj_tol * bnorm) {
-        if (c == H->cfg.max_cycles) {
-            status = PFC_ERR_NOT_CONVERGED;
-            break;
-        }
-        adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
-        ++c;
-        st = adj_norm(H, &rho);
+    if (bnorm > 0.0) {  // the first unit tests |b| itself
+        RunHost r{};
+        const double tol = adj_tol * bnorm;
+        st = run_units(H, tol, [&](int slot) {
+            launch_stop_test(H->stream, H->partial, parts, tol, H->cfg.max_cycles, run_state(H, slot));
+            adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
+            parts = adj_norm(H);
+        }, &r);
         if (st != PFC_OK) return st;
-        if (!std::isfinite(rho)) {
-            status = PFC_ERR_NONFINITE;
-            break;
-        }
+        c = r.cycles;
+        status = r.status;
     }
     if (status == PFC_OK || status == PFC_ERR_NOT_CONVERGED) {
         // lambda back to natural order (level-0 scratch), then accumulate

@@ -196,19 +196,16 @@ __global__ __launch_bounds__(kBlock) void k_stop_test(const unsigned long long *
     m = block_max_u64(m);
     if (threadIdx.x != 0) return;
     const double r = __longlong_as_double((long long)m);
+    const int status = !isfinite(r) ? 3 : (!(r <= tol) && c == max_cycles ? 2 : 0);  // PFC_ERR_*
+    const bool go = status == 0 && !(r <= tol);
     if (c == 0) *st.res0 = r;
     *st.res = r;
-    if (!isfinite(r)) {
-        *st.status = 3;  // PFC_ERR_NONFINITE
-        *st.active = 0;
-    } else if (r <= tol) {
-        *st.active = 0;
-    } else if (c == max_cycles) {
-        *st.status = 2;  // PFC_ERR_NOT_CONVERGED
-        *st.active = 0;
-    } else {
+    *st.status = status;
+    if (go)
         *st.cycles = c + 1;
-    }
+    else
+        *st.active = 0;
+    if (st.host) *st.host = RunHost{go ? 1 : 0, go ? c + 1 : c, status, 0, c == 0 ? r : *st.res0, r};
 }
 
 void launch_stop_test(hipStream_t s, const unsigned long long *partial, int count, double tol,

@@ -322,9 +322,7 @@ static pfc_status mixed_step_on(pfc_handle *H, const double *phi_prev, const dou
         // base on every level and their zero start, queued ahead of the
         // host's wait so that the device works while the host decides
         // (wasted once per step, after the last defect pass)
-        launch_max_final(H->stream, H->partial, cnt, H->d_scal);
-        HIP_TRY(H, hipMemcpyAsync(H->h_pin, H->d_scal, sizeof(double), hipMemcpyDeviceToHost,
-                                  H->stream));
+        launch_max_final(H->stream, H->partial, cnt, H->h_pin);
         HIP_TRY(H, hipEventRecord(H->norm_ev, H->stream));
         for (int l = 0; l + 1 < H->nlev; ++l)
             launch_restrict<float>(H->stream, H->lev[l].lay, H->lev[l + 1].lay, H->lev32[l].base,

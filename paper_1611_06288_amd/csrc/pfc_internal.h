@@ -299,12 +299,19 @@ void launch_norm_seed(hipStream_t s, const unsigned long long *partial, int coun
 // replayed graph of cycles needs no host round trip.  active: cycles still
 // wanted (the gate of the cycle kernels); cycles: cycles started; status: a
 // pfc_status; res0/res: first and latest norm.
+// host (may be null): pinned memory that takes the state when a test of an
+// active step has decided.
+struct RunHost {
+    int active, cycles, status, unused;
+    double res0, res;
+};
 struct RunState {
     int *active;
     int *cycles;
     int *status;
     double *res0;
     double *res;
+    RunHost *host = nullptr;
 };
 void launch_run_reset(hipStream_t s, RunState st);
 void launch_stop_test(hipStream_t s, const unsigned long long *partial, int count, double tol,

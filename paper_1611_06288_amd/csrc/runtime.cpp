@@ -232,6 +232,8 @@ pfc_handle::~pfc_handle() {
     if (run_graph) (void)hipGraphDestroy(run_graph);
     if (run_ev) (void)hipEventDestroy(run_ev);
     if (norm_ev) (void)hipEventDestroy(norm_ev);
+    for (hipEvent_t e : unit_ev)
+        if (e) (void)hipEventDestroy(e);
     if (run_stream) (void)hipStreamDestroy(run_stream);
     for (void *p : allocs) (void)hipFree(p);
     if (h_pin) (void)hipHostFree(h_pin);
@@ -494,10 +496,8 @@ static void restrict_phs(pfc_handle *H, int from) {
 static bool mobility_on(const pfc_handle *H) { return H->cfg.mobility == PFC_MOBILITY_QUADRATIC; }
 
 pfc_status read_norm(pfc_handle *H, int partials, double *out) {
-    launch_max_final(H->stream, H->partial, partials, H->d_scal);
+    launch_max_final(H->stream, H->partial, partials, H->h_pin);  // straight to the host
     HIP_TRY(H, hipGetLastError());
-    HIP_TRY(H, hipMemcpyAsync(H->h_pin, H->d_scal, sizeof(double), hipMemcpyDeviceToHost,
-                              H->stream));
     HIP_TRY(H, hipStreamSynchronize(H->stream));
     H->collect_timings();
     *out = H->h_pin[0];
@@ -679,7 +679,7 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
         H->split_norm = A.fused && cfg->nu1 >= 1 && cfg->nu2 >= 1 && cfg->precision == PFC_FP64 &&
                         std::max(H->split_pre, H->split_post) <= kMaxReduceBlocks;
     }
-    ok = ok && dalloc(H, &H->d_scal, 16) && dalloc(H, &H->d_iters, 4);
+    ok = ok && dalloc(H, &H->d_iters, 4) && dalloc(H, &H->d_run, 4) && dalloc(H, &H->d_runres, 2);
     ok = ok && dalloc(H, &H->energy_part, (size_t)6 * kMaxReduceBlocks + 16);
     ok = ok && dalloc(H, &H->minv64, 64 * 64) && dalloc(H, &H->minv32, 64 * 64) &&
          dalloc(H, &H->valid64, 4) && dalloc(H, &H->valid32, 4) &&
@@ -767,10 +767,37 @@ pfc_status pfc_step(pfc_handle *h, const double *phi_prev, const double *phi_cur
 }  // extern "C"
 
 namespace pfc {
-// One FP64 time step with the cycle loop on the host (one 8-byte read-back
-// per cycle).
+static void step_info(pfc_step_info *info, int cycles, int status, double res0, double res) {
+    if (!info) return;
+    info->cycles = cycles;
+    info->status = status;
+    info->res0 = res0;
+    info->res_final = res;
+}
+
+// One FP64 time step, the cycle loop in units whose decisions the device takes.
+static pfc_status step_units(pfc_handle *h, const double *phi_prev, const double *phi_cur,
+                             double *phi_next, double *mu, double *omega, pfc_step_info *info) {
+    step_begin(h, phi_prev, phi_cur, mu, omega);
+    step_unit_seed(h);
+    RunHost r{};
+    const pfc_status st = run_units(h, h->cfg.tol, [h](int slot) { step_unit(h, slot); }, &r);
+    if (st != PFC_OK) return st;
+    step_end(h, phi_next, mu, omega);
+    HIP_TRY(h, hipGetLastError());
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    step_info(info, r.cycles, r.status, r.res0, r.res);
+    if (r.status != PFC_OK) fail(h, r.status, pfc_status_string(r.status));
+    return r.status;
+}
+
+// One FP64 time step.  The loop below decides on the host, with one 8-byte
+// read-back per cycle: per-kernel timing counts its launches, and units whose
+// iterates change buffers cannot follow each other unseen.
 pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, double *phi_next,
                   double *mu, double *omega, pfc_step_info *info) {
+    if (!h->timing && units_usable(h))
+        return step_units(h, phi_prev, phi_cur, phi_next, mu, omega, info);
     step_begin(h, phi_prev, phi_cur, mu, omega);
     HIP_TRY(h, hipGetLastError());
     int c = 0;
@@ -826,12 +853,7 @@ pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, 
     step_end(h, phi_next, mu, omega);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    if (info) {
-        info->cycles = c;
-        info->status = status;
-        info->res0 = rho0;
-        info->res_final = rho;
-    }
+    step_info(info, c, status, rho0, rho);
     if (status != PFC_OK) fail(h, status, pfc_status_string(status));
     return status;
 }
@@ -866,10 +888,8 @@ pfc_status pfc_energy(pfc_handle *h, const double *phi, const double *phi_prev, 
     if (!phi || !out) return fail(h, PFC_ERR_INVALID_ARG, "NULL pointer");
     const Level &A = h->lev[0];
     launch_energy(h->stream, make_lay(A.n, false), A.h, h->cfg.eps, phi, phi_prev, h->energy_part,
-                  h->d_scal);
+                  h->h_pin);
     HIP_TRY(h, hipGetLastError());
-    HIP_TRY(h, hipMemcpyAsync(h->h_pin, h->d_scal, 3 * sizeof(double), hipMemcpyDeviceToHost,
-                              h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     out[0] = h->h_pin[0];
     out[1] = h->h_pin[1];

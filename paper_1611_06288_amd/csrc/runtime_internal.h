@@ -3,10 +3,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <string>
 #include <vector>
 
 #include "pfc.h"
+
 #include "pfc_internal.h"
 
 namespace pfc {
@@ -80,7 +82,6 @@ struct pfc_handle {
     pfc::Level32 lev32[pfc::kMaxLevels];
     std::vector<void *> allocs;
     unsigned long long *partial = nullptr;
-    double *d_scal = nullptr;
     int *d_iters = nullptr;
     double *h_pin = nullptr;
     double *lap1 = nullptr, *lap2 = nullptr, *lap3 = nullptr;
@@ -106,6 +107,7 @@ struct pfc_handle {
     hipStream_t run_stream = nullptr;     // the loop's own stream (capturable)
     hipEvent_t run_ev = nullptr;
     hipEvent_t norm_ev = nullptr;         // the mixed form's norm copied to the host
+    hipEvent_t unit_ev[2] = {nullptr, nullptr};  // units of a host-driven loop (run_units)
     int *d_run = nullptr;                 // active, cycles, status of the current step
     double *d_runres = nullptr;           // res0, res of the current step
     hipGraph_t run_graph = nullptr;       // norm, stop test, one gated cycle
@@ -196,6 +198,30 @@ pfc_status read_norm(pfc_handle *H, int partials, double *out);
 pfc_status mixed_init(pfc_handle *H);
 pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, double *phi_next,
                   double *mu, double *omega, pfc_step_info *info);
+// The device state of a cycle loop; its decisions reach h_pin through slot 0 or 1.
+inline RunHost *run_host(const pfc_handle *H, int slot) {
+    return reinterpret_cast<RunHost *>(H->h_pin + 16 + 8 * slot);
+}
+inline RunState run_state(pfc_handle *H, int slot = 0) {
+    return RunState{H->d_run,        H->d_run + 1,    H->d_run + 2, H->d_runres,
+                    H->d_runres + 1, run_host(H, slot)};
+}
+// A cycle loop driven by the host, the decisions on the device: `unit`
+// enqueues the stop test (with run_state(H, slot)) and one cycle with the norm
+// after or before it, every launch gated on the test.  Unit i + 1 is enqueued
+// before the host looks at unit i's test, so the device does not wait for the
+// host between cycles (a 32^3 step waited 12-25 us of every 78 us cycle), unless
+// the norms so far say that unit i stops: a unit behind that one does nothing,
+// but takes 4 us a launch.  tol: the test's.  out: the last decision.
+template <typename Unit>
+pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out);
+pfc_status unit_events(pfc_handle *H);
+// The unit of a time step's loop (pfc_step, and recorded as pfc_run's graph),
+// what it needs before the first one, and whether the level iterates are back
+// in their buffers after one, so that units can follow each other unseen.
+void step_unit(pfc_handle *H, int slot);
+void step_unit_seed(pfc_handle *H);
+bool units_usable(const pfc_handle *H);
 // The handle's own non-blocking stream (created on first use): recorded
 // graphs need a capturable stream.  own_stream_enter makes it follow the
 // caller's stream and returns that stream; own_stream_leave makes the caller's
@@ -228,3 +254,43 @@ pfc_status hip_fail(pfc_handle *H, hipError_t e, const char *what);
         hipError_t e_ = (expr);                                           \
         if (e_ != hipSuccess) return pfc::hip_fail((H), e_, #expr);       \
     } while (0)
+
+namespace pfc {
+template <typename Unit>
+pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out) {
+    const pfc_status st = unit_events(H);
+    if (st != PFC_OK) return st;
+    struct Gate {  // set while the units are enqueued
+        pfc_handle *H;
+        explicit Gate(pfc_handle *h) : H(h) { H->gate = H->d_run; }
+        ~Gate() { H->gate = nullptr; }
+    } gate(H);
+    launch_run_reset(H->stream, run_state(H));
+    auto enqueue = [&](int i) -> pfc_status {
+        unit(i & 1);
+        HIP_TRY(H, hipGetLastError());
+        HIP_TRY(H, hipEventRecord(H->unit_ev[i & 1], H->stream));
+        return PFC_OK;
+    };
+    pfc_status e = enqueue(0);
+    if (e != PFC_OK) return e;
+    double res = 0.0, next = INFINITY;  // the last norm known, the next one at its contraction
+    bool ahead = false;
+    for (int i = 0;; ++i) {
+        // unit i is enqueued; the next one too unless i is expected to stop
+        ahead = next > tol;
+        if (ahead && (e = enqueue(i + 1)) != PFC_OK) return e;
+        HIP_TRY(H, hipEventSynchronize(H->unit_ev[i & 1]));
+        const RunHost r = *run_host(H, i & 1);
+        if (!r.active) {
+            *out = r;
+            return PFC_OK;
+        }
+        if (i > H->cfg.max_cycles + 2)
+            return fail(H, PFC_ERR_HIP, "cycle loop: the device stop test did not end it");
+        next = i > 0 ? r.res * (r.res / res) : INFINITY;
+        res = r.res;
+        if (!ahead && (e = enqueue(i + 1)) != PFC_OK) return e;
+    }
+}
+}  // namespace pfc

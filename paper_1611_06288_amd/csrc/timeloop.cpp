@@ -7,7 +7,7 @@
 // device memory (active, cycles, status, first and latest norm) and every
 // kernel of the cycle is gated on `active`, so a replay after convergence
 // does nothing.  A step launches the graph as many times as the previous step
-// needed cycles, reads the 24-byte state back once, and launches one more
+// needed cycles, reads the state the last test left in pinned memory, and launches one more
 // replay at a time only while the step is still active.  The sequence of
 // operations a step performs is therefore exactly that of pfc_step (same
 // kernels, same order, same decisions), so results agree bit for bit, while
@@ -36,22 +36,51 @@
 
 using namespace pfc;
 
-namespace {
-
-RunState run_state(pfc_handle *H) {
-    return RunState{H->d_run, H->d_run + 1, H->d_run + 2, H->d_runres, H->d_runres + 1};
-}
-
-// The recorded cycle assumes the level iterates it was recorded with; levels
-// smoothed by the fused sweep trade their two buffers once per launch, which
-// leaves them in place over a cycle (an F-cycle visits the coarse ones again)
-// only for an even number of launches.
-bool graph_usable(const pfc_handle *H) {
-    if (H->cfg.precision != PFC_FP64) return false;
+namespace pfc {
+// Levels smoothed by the fused sweep trade their two buffers once per launch,
+// which leaves them in place over a cycle (an F-cycle visits the coarse ones
+// again) only for an even number of launches.
+bool units_usable(const pfc_handle *H) {
     for (int l = 0; l < H->nlev; ++l)
         if (H->lev[l].fused && (sweep_launches(H, l) & 1)) return false;
     return true;
 }
+
+void step_unit(pfc_handle *H, int slot) {
+    const bool fcycle = H->cfg.cycle == PFC_CYCLE_F;
+    if (H->split_norm) {
+        ahead64(H);
+        launch_stop_test(H->stream, H->partial, H->split_pre + H->split_post, H->cfg.tol,
+                         H->cfg.max_cycles, run_state(H, slot));
+        cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
+    } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
+        const int cnt = brick_pre64(H, 0, BRICK_NORM);
+        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles, run_state(H, slot));
+        cycle64(H, 0, fcycle, kCyclePreDone);
+    } else {
+        const int cnt = enqueue_norm64(H);
+        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles,
+                         run_state(H, slot));
+        cycle64(H, 0, fcycle);
+    }
+}
+
+void step_unit_seed(pfc_handle *H) {
+    if (H->split_norm) {
+        unsigned long long *whole = H->partial + H->split_pre + H->split_post;
+        const int cnt = enqueue_norm64(H, whole);
+        launch_norm_seed(H->stream, whole, cnt, H->partial + H->split_pre, H->split_post);
+    }
+}
+
+pfc_status unit_events(pfc_handle *H) {
+    for (hipEvent_t &e : H->unit_ev)
+        if (!e) HIP_TRY(H, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    return PFC_OK;
+}
+}  // namespace pfc
+
+namespace {
 
 bool graph_current(const pfc_handle *H) {
     if (!H->run_exec) return false;
@@ -77,22 +106,7 @@ pfc_status record_graph(pfc_handle *H) {
         return hip_fail(H, e, "hipStreamBeginCapture");
     }
     H->gate = H->d_run;  // every launch below reads the active flag
-    const bool fcycle = H->cfg.cycle == PFC_CYCLE_F;
-    if (H->split_norm) {
-        ahead64(H);
-        launch_stop_test(H->stream, H->partial, H->split_pre + H->split_post, H->cfg.tol,
-                         H->cfg.max_cycles, run_state(H));
-        cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
-    } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
-        const int cnt = brick_pre64(H, 0, BRICK_NORM);
-        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles, run_state(H));
-        cycle64(H, 0, fcycle, kCyclePreDone);
-    } else {
-        const int cnt = enqueue_norm64(H);
-        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles,
-                         run_state(H));
-        cycle64(H, 0, fcycle);
-    }
+    step_unit(H, 0);
     H->gate = nullptr;
     H->timing = timing;
     e = hipStreamEndCapture(H->stream, &H->run_graph);
@@ -108,34 +122,26 @@ pfc_status graph_step(pfc_handle *H, const double *prev, const double *cur, doub
                       double *mu, double *om, pfc_step_info *info) {
     step_begin(H, prev, cur, mu, om);
     launch_run_reset(H->stream, run_state(H));
-    if (H->split_norm) {
-        unsigned long long *whole = H->partial + H->split_pre + H->split_post;
-        const int cnt = enqueue_norm64(H, whole);
-        launch_norm_seed(H->stream, whole, cnt, H->partial + H->split_pre, H->split_post);
-    }
+    step_unit_seed(H);
     HIP_TRY(H, hipGetLastError());
     if (!graph_current(H)) {
         const pfc_status st = record_graph(H);
         if (st != PFC_OK) return st;
     }
-    int *hs = reinterpret_cast<int *>(H->h_pin + 16);  // active, cycles, status
-    double *hr = H->h_pin + 20;                         // res0, res
+    const RunHost *hs = run_host(H, 0);
     int launches = std::max(1, H->last_cycles);
     // a step ends after at most max_cycles + 1 stop tests
     for (int total = 0;;) {
         for (int i = 0; i < launches; ++i) HIP_TRY(H, hipGraphLaunch(H->run_exec, H->stream));
         total += launches;
-        HIP_TRY(H, hipMemcpyAsync(hs, H->d_run, 3 * sizeof(int), hipMemcpyDeviceToHost, H->stream));
-        HIP_TRY(H, hipMemcpyAsync(hr, H->d_runres, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                                  H->stream));
         HIP_TRY(H, hipStreamSynchronize(H->stream));
-        if (hs[0] == 0) break;
+        if (!hs->active) break;
         if (total > H->cfg.max_cycles + 1)
             return fail(H, PFC_ERR_HIP, "time loop: the device stop test did not end the step");
         launches = 1;
     }
-    const int cycles = hs[1], status = hs[2];
-    const double res0 = hr[0], res = hr[1];
+    const int cycles = hs->cycles, status = hs->status;
+    const double res0 = hs->res0, res = hs->res;
     step_end(H, next, mu, om);
     HIP_TRY(H, hipGetLastError());
     H->last_cycles = cycles;
@@ -183,8 +189,7 @@ extern "C" pfc_status pfc_run(pfc_handle *h, double *phi_prev, double *phi_cur, 
     if (steps < 0) return fail(h, PFC_ERR_INVALID_ARG, "steps must be >= 0");
     if (steps == 0) return PFC_OK;
     if (!h->spare) {
-        if (!dalloc(h, &h->spare, h->lev[0].P) || !dalloc(h, &h->d_run, 4) ||
-            !dalloc(h, &h->d_runres, 2))
+        if (!dalloc(h, &h->spare, h->lev[0].P))
             return fail(h, PFC_ERR_OOM, "time-loop buffers");
     }
     // the loop's stream follows the caller's, and the caller's follows it at the end
@@ -193,7 +198,7 @@ extern "C" pfc_status pfc_run(pfc_handle *h, double *phi_prev, double *phi_cur, 
         const pfc_status st = own_stream_enter(h, &user);
         if (st != PFC_OK) return st;
     }
-    const bool graph = graph_usable(h);
+    const bool graph = h->cfg.precision == PFC_FP64 && units_usable(h);
     double *buf[3] = {phi_prev, phi_cur, h->spare};
     int ip = 0, ic = 1, in = 2;
     pfc_status status = PFC_OK;
