@@ -822,75 +822,214 @@ int energy_blocks(int n) { return (int)reduce_blocks((size_t)n * n * n); }
 // Per-block sums of phi^4, phi^2, (D phi)^2 on the cell's three forward faces
 // (so every face of the periodic grid is counted once), (Lap phi)^2, the same
 // face sum for phi - phi_prev, and phi.  Scaled by h^3 in the final pass.
+// Part b holds points 256 b .. 256 b + 255 of every pass of 256 * parts points.
+struct EnergySums {
+    double s[6] = {0, 0, 0, 0, 0, 0};
+    // a point's value, its neighbours xp, xm, yp, ym, zp, zm; phi_prev at c, xp, yp, zp
+    template <bool PREV>
+    __device__ __forceinline__ void add(double v, const double (&a)[6], const double (&b)[4], double hinv,
+                                        double h2inv) {
+        const double v2 = v * v;
+        s[0] += v2 * v2;
+        s[1] += v2;
+        s[5] += v;
+        const double dx = (a[0] - v) * hinv, dy = (a[2] - v) * hinv, dz = (a[4] - v) * hinv;
+        s[2] += dx * dx + dy * dy + dz * dz;
+        const double l = ((a[0] + a[1]) + (a[2] + a[3]) + (a[4] + a[5]) - 6.0 * v) * h2inv;
+        s[3] += l * l;
+        if constexpr (PREV) {
+            const double w = v - b[0];
+            const double ex = (a[0] - b[1] - w) * hinv;
+            const double ey = (a[2] - b[2] - w) * hinv;
+            const double ez = (a[4] - b[3] - w) * hinv;
+            s[4] += ex * ex + ey * ey + ez * ez;
+        }
+    }
+    // the binary tree over the block's threads (128 apart, 64, 32 ... 1): the first
+    // two steps by the waves, one sum each, the others across lanes
+    __device__ __forceinline__ void reduce(double (&red)[6][kBlock], double *part, unsigned parts,
+                                           unsigned blk) const {
+        for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = s[c];
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        for (int c = threadIdx.x >> 6; c < 6; c += kBlock / 64) {
+            double v = (red[c][lane] + red[c][lane + 128]) + (red[c][lane + 64] + red[c][lane + 192]);
+            for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
+            if (lane == 0) part[(size_t)c * parts + blk] = v;
+        }
+        __syncthreads();
+    }
+};
+
+template <bool PREV>
 __global__ __launch_bounds__(kBlock) void k_energy_part(Lay L, double hinv, double h2inv,
                                                         const double *__restrict__ phi,
                                                         const double *__restrict__ prev,
                                                         double *__restrict__ part) {
     __shared__ double red[6][kBlock];
-    double s[6] = {0, 0, 0, 0, 0, 0};
-    const unsigned total = (unsigned)npts(L);
-    for (unsigned t = blockIdx.x * kBlock + threadIdx.x; t < total; t += gridDim.x * kBlock) {
+    EnergySums e;
+    const unsigned total = (unsigned)npts(L), blk = xcd_block();
+    for (unsigned t = blk * kBlock + threadIdx.x; t < total; t += gridDim.x * kBlock) {
         int i, j, k;
         decode(L, t, i, j, k);
         const Off q = offs(L, i, j, k);
-        const double v = phi[q.c];
-        const double v2 = v * v;
-        s[0] += v2 * v2;
-        s[1] += v2;
-        s[5] += v;
-        const double dx = (phi[q.xp] - v) * hinv, dy = (phi[q.yp] - v) * hinv,
-                     dz = (phi[q.zp] - v) * hinv;
-        s[2] += dx * dx + dy * dy + dz * dz;
-        const double l = (nsum(phi, q) - 6.0 * v) * h2inv;
-        s[3] += l * l;
-        if (prev) {
-            const double w = v - prev[q.c];
-            const double ex = (phi[q.xp] - prev[q.xp] - w) * hinv;
-            const double ey = (phi[q.yp] - prev[q.yp] - w) * hinv;
-            const double ez = (phi[q.zp] - prev[q.zp] - w) * hinv;
-            s[4] += ex * ex + ey * ey + ez * ez;
+        const double a[6] = {phi[q.xp], phi[q.xm], phi[q.yp], phi[q.ym], phi[q.zp], phi[q.zm]};
+        double b[4] = {0, 0, 0, 0};
+        if constexpr (PREV) {
+            b[0] = prev[q.c];
+            b[1] = prev[q.xp];
+            b[2] = prev[q.yp];
+            b[3] = prev[q.zp];
         }
+        e.add<PREV>(phi[q.c], a, b, hinv, h2inv);
     }
-    for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 6; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 6) part[(size_t)blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
+    e.reduce(red, part, gridDim.x, blk);
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_final(const double *__restrict__ part, int count,
-                                                         double h, double eps,
-                                                         double *__restrict__ out) {
+// The same parts on large levels, kEZ of them per workgroup: those of one x-y
+// position on consecutive planes, so that a thread walks in z and keeps the
+// planes' values in registers, two steps' loads ahead.  One part per workgroup
+// fetches a plane once for each of the planes that need it (the passes of a
+// 256^3 level lie 64 planes apart and an XCD's L2 does not hold them).  Bound by
+// memory, 16 bytes per point and half of it again at the ends of four planes (8
+// planes: fewer bytes, 2 waves per SIMD, 118 us).  A call of pfc_energy, 21 us of
+// it launches and the wait: 256^3 152 -> 107 us, 384^3 540 -> 398, 128^3 47 -> 40.
+// Sums and their order are the same.
+constexpr int kEZ = 4;
+template <bool PREV>
+__global__ __launch_bounds__(kBlock) void k_energy_march(Lay L, double hinv, double h2inv,
+                                                         const double *__restrict__ phi,
+                                                         const double *__restrict__ prev,
+                                                         double *__restrict__ part, unsigned parts) {
     __shared__ double red[6][kBlock];
-    double s[6] = {0, 0, 0, 0, 0, 0};
-    for (int b = threadIdx.x; b < count; b += kBlock)
-        for (int c = 0; c < 6; ++c) s[c] += part[(size_t)b * 6 + c];
-    for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = s[c];
+    EnergySums e[kEZ];
+    const int n = L.n;
+    const unsigned un = (unsigned)n, plane = un * un, total = plane * un, stride = parts * kBlock;
+    const unsigned pp = plane / kBlock;  // parts per plane
+    const unsigned w = xcd_block(), g = w / pp, b0 = g * kEZ * pp + (w - g * pp);
+    for (unsigned m = 0; m < total; m += stride) {
+        const unsigned t0 = m + b0 * kBlock + threadIdx.x;
+        if (t0 >= total) break;
+        int i, j, k;
+        decode(L, t0, i, j, k);
+        const unsigned xp = (unsigned)j * un + (unsigned)wrap_p(i, n), xm = (unsigned)j * un + (unsigned)wrap_m(i, n);
+        const unsigned yp = (unsigned)wrap_p(j, n) * un + (unsigned)i, ym = (unsigned)wrap_m(j, n) * un + (unsigned)i;
+        const unsigned c = (unsigned)j * un + (unsigned)i;
+        double lo = phi[(unsigned)wrap_m(k, n) * plane + c], v = phi[(unsigned)k * plane + c];
+        double pv = PREV ? prev[(unsigned)k * plane + c] : 0.0;
+        // the loads of step z: xp, xm, yp, ym of its plane, zp; of phi_prev xp, yp, zp
+        struct Step {
+            double a[5], b[3];
+        };
+        auto load = [&](int z) {
+            int kz = k + z;
+            if (kz >= n) kz -= n;
+            const unsigned o = (unsigned)kz * plane, oz = (unsigned)wrap_p(kz, n) * plane + c;
+            Step q;
+            q.a[0] = phi[o + xp];
+            q.a[1] = phi[o + xm];
+            q.a[2] = phi[o + yp];
+            q.a[3] = phi[o + ym];
+            q.a[4] = phi[oz];
+            q.b[0] = PREV ? prev[o + xp] : 0.0;
+            q.b[1] = PREV ? prev[o + yp] : 0.0;
+            q.b[2] = PREV ? prev[oz] : 0.0;
+            return q;
+        };
+        auto step = [&](int z, const Step &q) {
+            const double a[6] = {q.a[0], q.a[1], q.a[2], q.a[3], q.a[4], lo};
+            const double b[4] = {pv, q.b[0], q.b[1], q.b[2]};
+            e[z].template add<PREV>(v, a, b, hinv, h2inv);
+            lo = v;
+            v = q.a[4];
+            pv = q.b[2];
+        };
+        const unsigned last = b0 + (kEZ - 1) * pp;
+        if (last < parts && m + last * kBlock < total) {  // two steps' loads ahead
+            Step q0 = load(0), q1 = load(1);
+#pragma unroll
+            for (int z = 0; z < kEZ; ++z) {
+                const Step q = q0;
+                q0 = q1;
+                if (z + 2 < kEZ) q1 = load(z + 2);
+                step(z, q);
+            }
+        } else {
+#pragma unroll
+            for (int z = 0; z < kEZ; ++z) {
+                const unsigned bz = b0 + z * pp;
+                if (bz >= parts || m + bz * kBlock >= total) break;  // (the same for the whole block)
+                step(z, load(z));
+            }
+        }
+    }
+#pragma unroll
+    for (int z = 0; z < kEZ; ++z) {
+        const unsigned bz = b0 + z * pp;
+        if (bz < parts) e[z].reduce(red, part, parts, bz);
+    }
+}
+
+// The blocks' sums of one quantity per workgroup: thread t adds blocks t, t + 256,
+// ... in turn (16 loads in flight), then the tree.
+__global__ __launch_bounds__(kBlock) void k_energy_sum(const double *__restrict__ part, int count,
+                                                       double *__restrict__ sums) {
+    __shared__ double red[kBlock];
+    const double *p = part + (size_t)blockIdx.x * count;
+    double s = 0.0;
+    constexpr int kAhead = 16;
+    for (int b0 = threadIdx.x; b0 < count; b0 += kAhead * kBlock) {
+        double v[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) v[i] = p[min(b0 + i * kBlock, count - 1)];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (b0 + i * kBlock < count) s += v[i];
+    }
+    red[threadIdx.x] = s;
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int c = 0; c < 6; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        double v = (red[lane] + red[lane + 128]) + (red[lane + 64] + red[lane + 192]);
+        for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
+        if (lane == 0) sums[blockIdx.x] = v;
     }
-    if (threadIdx.x == 0) {
-        const double h3 = h * h * h;
-        const double F = h3 * (0.25 * red[0][0] + 0.5 * (1.0 - eps) * red[1][0] - red[2][0] +
-                               0.5 * red[3][0]);
-        out[0] = F;
-        out[1] = F + 0.5 * h3 * red[4][0];
-        out[2] = h3 * red[5][0];
+}
+
+__global__ void k_energy_out(const double *__restrict__ sums, double h, double eps,
+                             double *__restrict__ out) {
+    if (threadIdx.x == 0) energy_out(sums, h, eps, out);
+}
+
+template <bool PREV>
+static void energy_part(hipStream_t s, const Lay &nat, double h, const double *phi,
+                        const double *phi_prev, double *part, int parts) {
+    const unsigned un = (unsigned)nat.n;
+    if (un >= 128 && un % 16 == 0) {  // whole parts per plane; enough workgroups
+        const unsigned pp = un * un / kBlock, groups = ((unsigned)parts + kEZ * pp - 1) / (kEZ * pp);
+        hipLaunchKernelGGL(k_energy_march<PREV>, dim3(groups * pp), dim3(kBlock), 0, s, nat, 1.0 / h,
+                           1.0 / (h * h), phi, phi_prev, part, (unsigned)parts);
+        return;
     }
+    hipLaunchKernelGGL(k_energy_part<PREV>, dim3((unsigned)parts), dim3(kBlock), 0, s, nat, 1.0 / h,
+                       1.0 / (h * h), phi, phi_prev, part);
+}
+
+void launch_energy_sums(hipStream_t s, const Lay &nat, double h, const double *phi,
+                        const double *phi_prev, double *partial, double *sums6) {
+    const int blocks = energy_blocks(nat.n);
+    if (phi_prev)
+        energy_part<true>(s, nat, h, phi, phi_prev, partial, blocks);
+    else
+        energy_part<false>(s, nat, h, phi, phi_prev, partial, blocks);
+    hipLaunchKernelGGL(k_energy_sum, dim3(6), dim3(kBlock), 0, s, partial, blocks, sums6);
 }
 
 void launch_energy(hipStream_t s, const Lay &nat, double h, double eps, const double *phi,
                    const double *phi_prev, double *partial, double *out3) {
-    const int blocks = energy_blocks(nat.n);
-    hipLaunchKernelGGL(k_energy_part, dim3(blocks), dim3(kBlock), 0, s, nat, 1.0 / h, 1.0 / (h * h),
-                       phi, phi_prev, partial);
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kBlock), 0, s, partial, blocks, h, eps, out3);
+    double *sums = partial + (size_t)6 * energy_blocks(nat.n);
+    launch_energy_sums(s, nat, h, phi, phi_prev, partial, sums);
+    hipLaunchKernelGGL(k_energy_out, dim3(1), dim3(64), 0, s, (const double *)sums, h, eps, out3);
 }
 
 // ------------------------------------------------ mixed-precision helpers

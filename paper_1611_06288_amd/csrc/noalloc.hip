@@ -22,8 +22,8 @@
 namespace {
 
 // k_energy_part leaves 6 sums per workgroup and launches at most
-// kMaxReduceBlocks workgroups, whatever n is.
-constexpr size_t kScratchDoubles = (size_t)pfc::kMaxReduceBlocks * 6;
+// kMaxReduceBlocks workgroups, whatever n is; their totals follow.
+constexpr size_t kScratchDoubles = (size_t)(pfc::kMaxReduceBlocks + 1) * 6;
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) double scratch[kScratchDoubles];
@@ -69,13 +69,13 @@ extern "C" pfc_status pfc_energy_static(int32_t n, double L, double eps, const d
     if (!(L > 0) || !std::isfinite(L) || !std::isfinite(eps))
         return fail(nullptr, PFC_ERR_INVALID_ARG, "pfc_energy_static: L must be > 0, eps finite");
     if (!phi || !out3) return fail(nullptr, PFC_ERR_INVALID_ARG, "pfc_energy_static: NULL pointer");
-    if ((size_t)energy_blocks(n) * 6 > kScratchDoubles)
+    if (((size_t)energy_blocks(n) + 1) * 6 > kScratchDoubles)
         return fail(nullptr, PFC_ERR_INVALID_ARG, "pfc_energy_static: scratch too small");
     std::string why;
     double *part = scratch_on_current_device(why);
     if (!part) return fail(nullptr, PFC_ERR_HIP, "pfc_energy_static: " + why);
     const double h = L / n;
-    // Every partial that k_energy_final reads is written first by
+    // Every partial that k_energy_sum reads is written first by
     // k_energy_part in the same call: nothing needs clearing.
     launch_energy(static_cast<hipStream_t>(stream), make_lay(n, false), h, eps, phi, phi_prev, part,
                   out3);

@@ -346,8 +346,20 @@ void launch_to_lay(hipStream_t s, const Lay &lay, const S *src, D *dst, int coun
 template <typename S, typename D>
 void launch_from_lay(hipStream_t s, const Lay &lay, const S *src, D *dst, int count);
 
-// Energy on natural-layout fields: per-block sums, then a fixed-order final sum.
+// Energy on natural-layout fields: per-block sums (partial: 6 energy_blocks(n) + 6
+// doubles), then fixed-order final sums of phi^4, phi^2, |D phi|^2, (Lap phi)^2,
+// |D(phi - phi_prev)|^2 and phi, to device or pinned memory; launch_energy goes on
+// to out3 (energy, modified energy, mass) on the device.
 int energy_blocks(int n);
+__host__ __device__ inline void energy_out(const double *sums, double h, double eps, double *out) {
+    const double h3 = h * h * h;
+    const double F = h3 * (0.25 * sums[0] + 0.5 * (1.0 - eps) * sums[1] - sums[2] + 0.5 * sums[3]);
+    out[0] = F;
+    out[1] = F + 0.5 * h3 * sums[4];
+    out[2] = h3 * sums[5];
+}
+void launch_energy_sums(hipStream_t s, const Lay &nat, double h, const double *phi,
+                        const double *phi_prev, double *partial, double *sums6);
 void launch_energy(hipStream_t s, const Lay &nat, double h, double eps, const double *phi,
                    const double *phi_prev, double *partial, double *out3);
 

@@ -887,13 +887,10 @@ pfc_status pfc_energy(pfc_handle *h, const double *phi, const double *phi_prev, 
     if (!h) return PFC_ERR_INVALID_ARG;
     if (!phi || !out) return fail(h, PFC_ERR_INVALID_ARG, "NULL pointer");
     const Level &A = h->lev[0];
-    launch_energy(h->stream, make_lay(A.n, false), A.h, h->cfg.eps, phi, phi_prev, h->energy_part,
-                  h->h_pin);
+    launch_energy_sums(h->stream, make_lay(A.n, false), A.h, phi, phi_prev, h->energy_part, h->h_pin);
     HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    out[0] = h->h_pin[0];
-    out[1] = h->h_pin[1];
-    out[2] = h->h_pin[2];
+    energy_out(h->h_pin, A.h, h->cfg.eps, out);
     return PFC_OK;
 }
 
