@@ -28,7 +28,10 @@
 // the inputs stay in registers between the sweeps (122-128 VGPRs; without the
 // coefficients in scalar registers they spill).  Two sweeps, two fused sweeps ->
 // this: 512^3 3.9 -> 2.4 ms, 256^3 479 -> 297 us, 192^3 195 -> 138, 128^3 54 -> 50
-// (halo planes: half of the steps); FP32 at 256^3 327 (half-sweeps) -> 259.
+// (halo planes: half of the steps); FP32 at 256^3 327 (half-sweeps) -> 252.  The
+// FP32 pair is bound by its FP64 arithmetic (VALU 68% busy), so its LDS planes hold
+// the rounded values as FP64, converted once by their writer and not by each
+// reader (259 -> 252 us; the LDS has the room).
 #pragma once
 
 #include "device_common.h"
@@ -87,34 +90,34 @@ struct PairArgs {
 };
 
 // One buffer as a thread sees it: its own slot and its neighbours'.
-template <typename T, int B>
+template <int B>
 struct PairSlot {
     using P = PairBuf<B>;
-    T *q;  // own x-pair, field 0, plane slot 0
-    __device__ __forceinline__ T *at(int slot) const { return q + slot * 3 * P::N; }
-    __device__ __forceinline__ void put(int slot, const T (&v)[3]) const {
-        T *w = at(slot);
+    double *q;  // own x-pair, field 0, plane slot 0
+    __device__ __forceinline__ double *at(int slot) const { return q + slot * 3 * P::N; }
+    __device__ __forceinline__ void put(int slot, const double (&v)[3]) const {
+        double *w = at(slot);
         w[0] = v[0];
         w[P::N] = v[1];
         w[2 * P::N] = v[2];
     }
-    __device__ __forceinline__ void get(int slot, T (&v)[3]) const {
-        const T *w = at(slot);
+    __device__ __forceinline__ void get(int slot, double (&v)[3]) const {
+        const double *w = at(slot);
         v[0] = w[0];
         v[1] = w[P::N];
         v[2] = w[2 * P::N];
     }
     // neighbour sums of the three fields: x and y from the plane in `slot`, z
     // given; s: x parity of the point
-    __device__ __forceinline__ void sums(int slot, int s, const T (&zp)[3], const T (&zm)[3],
+    __device__ __forceinline__ void sums(int slot, int s, const double (&zp)[3], const double (&zm)[3],
                                          double (&out)[3]) const {
-        const T *w = at(slot);
-        const T *wx = w + (s ? 1 : -1);
+        const double *w = at(slot);
+        const double *wx = w + (s ? 1 : -1);
 #pragma unroll
         for (int fl = 0; fl < 3; ++fl)
-            out[fl] = ((double)w[fl * P::N] + (double)wx[fl * P::N]) +
-                      ((double)w[fl * P::N + P::W] + (double)w[fl * P::N - P::W]) +
-                      ((double)zp[fl] + (double)zm[fl]);
+            out[fl] = (w[fl * P::N] + wx[fl * P::N]) +
+                      (w[fl * P::N + P::W] + w[fl * P::N - P::W]) +
+                      (zp[fl] + zm[fl]);
     }
 };
 

@@ -13,7 +13,7 @@ __device__ constexpr PairList kPairList = pair_list();
 // (with the last one's).  PK1: f.a is phi^k itself, loaded once.
 template <typename T, bool DELTA, int NRM, bool PK1>
 __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
-    __shared__ T lds[kPairLds];
+    __shared__ double lds[kPairLds];
     __shared__ unsigned long long wmax[kPT / 64];
     if (gate_closed(a.op.gate)) return;
     constexpr int NI = (PK1 ? 3 : 4) + (DELTA ? 1 : 0);  // phi^k, f2, f3 (, f1) (, base)
@@ -41,18 +41,18 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
     };
     auto gidx = [&](int c, int q) { return (c ? H : 0u) + (unsigned)wn(q) * plane + g0; };
 
-    T *const l0 = lds, *const l1 = l0 + 6 * PairBuf<0>::N, *const l2 = l1 + 6 * PairBuf<1>::N,
+    double *const l0 = lds, *const l1 = l0 + 6 * PairBuf<0>::N, *const l2 = l1 + 6 * PairBuf<1>::N,
             *const l3 = l2 + 6 * PairBuf<2>::N;
     // A thread whose pair lies outside a buffer never touches it: clamp its slot
-    auto own = [&](auto buf, T *l) {
+    auto own = [&](auto buf, double *l) {
         using P = decltype(buf);
         const int r = min(max(row - P::Y, 0), P::R - 1), c = min(max(mx - P::X, 0), P::W - 1);
         return l + r * P::W + c;
     };
-    const PairSlot<T, 0> o1{own(PairBuf<0>{}, l0)};  // old colour 1
-    const PairSlot<T, 1> a0{own(PairBuf<1>{}, l1)};  // first sweep
-    const PairSlot<T, 2> a1{own(PairBuf<2>{}, l2)};
-    const PairSlot<T, 3> b0{own(PairBuf<3>{}, l3)};  // second sweep, colour 0
+    const PairSlot<0> o1{own(PairBuf<0>{}, l0)};  // old colour 1
+    const PairSlot<1> a0{own(PairBuf<1>{}, l1)};  // first sweep
+    const PairSlot<2> a1{own(PairBuf<2>{}, l2)};
+    const PairSlot<3> b0{own(PairBuf<3>{}, l3)};  // second sweep, colour 0
 
     PointCoef co(a.op);
     co.to_scalar();
@@ -88,38 +88,38 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
         }
         if (dist(1, p - 1) <= 2) load_in(1, p - 1, in1[0]);
     };
-    auto solve = [&](T ph, const T (&v)[NI], const double (&s)[3], T (&o)[3]) {
+    auto solve = [&](double ph, const T (&v)[NI], const double (&s)[3], double (&o)[3]) {
         double x, y2, w;
-        point_solve<DELTA>(co, a.picard, (double)ph, (double)v[0], DELTA ? (double)v[NI - 1] : 0.0,
+        point_solve<DELTA>(co, a.picard, ph, (double)v[0], DELTA ? (double)v[NI - 1] : 0.0,
                            (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], s[1], s[2], s[0], x,
                            y2, w);
-        o[0] = (T)x;
+        o[0] = (T)x;  // rounded to the level's type
         o[1] = (T)y2;
         o[2] = (T)w;
     };
     unsigned long long nrm = 0;
-    auto norm = [&](const T (&w)[3], const T (&v)[NI], const double (&s)[3]) {
+    auto norm = [&](const double (&w)[3], const T (&v)[NI], const double (&s)[3]) {
         const double h2inv = a.op.h2inv;
-        const double ls[3] = {(s[0] - 6.0 * (double)w[0]) * h2inv, (s[1] - 6.0 * (double)w[1]) * h2inv,
-                              (s[2] - 6.0 * (double)w[2]) * h2inv};
+        const double ls[3] = {(s[0] - 6.0 * w[0]) * h2inv, (s[1] - 6.0 * w[1]) * h2inv,
+                              (s[2] - 6.0 * w[2]) * h2inv};
         double r[3];
-        resid_from_lap<false>(a.op, ls, (double)w[0], (double)w[1], (double)w[2],
+        resid_from_lap<false>(a.op, ls, w[0], w[1], w[2],
                               (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], (double)v[0], 0.0, r);
         nrm = umax(nrm, umax(abs_bits(r[0]), umax(abs_bits(r[1]), abs_bits(r[2]))));
     };
-    auto store = [&](int c, int q, const T (&v)[3], bool all) {
+    auto store = [&](int c, int q, const double (&v)[3], bool all) {
         const unsigned g = gidx(c, q);
         if (a.stream) {
-            __builtin_nontemporal_store(v[0], &a.o.a[g]);
+            __builtin_nontemporal_store((T)v[0], &a.o.a[g]);
             if (all) {
-                __builtin_nontemporal_store(v[1], &a.o.b[g]);
-                __builtin_nontemporal_store(v[2], &a.o.c[g]);
+                __builtin_nontemporal_store((T)v[1], &a.o.b[g]);
+                __builtin_nontemporal_store((T)v[2], &a.o.c[g]);
             }
         } else {
-            a.o.a[g] = v[0];
+            a.o.a[g] = (T)v[0];
             if (all) {
-                a.o.b[g] = v[1];
-                a.o.c[g] = v[2];
+                a.o.b[g] = (T)v[1];
+                a.o.c[g] = (T)v[2];
             }
         }
     };
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
     for (int p = z0 - 4; p <= z1 + 3; ++p) {
         const int k = p & 1;  // LDS slot of planes p, p-2, p-4
         // a value's lower z-neighbour is taken from the slot it replaces
-        T c1[3], lo[3], v[3], w[3], w0[3] = {phin[0], phin[1], phin[2]};
+        double c1[3], lo[3], v[3], w[3], w0[3] = {phin[0], phin[1], phin[2]};
         o1.get(k, lo);  // old colour 1, plane p-2
         if (dist(1, p) <= 4) {
             c1[0] = c1n[0];
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
         load_c1(p + 1);
         load_points(p);
         const int da = dist(0, p - 1), db = dist(1, p - 2), dc = dist(0, p - 3), dd = dist(1, p - 4);
-        T oldb = lo[0];  // old phi of plane p-2
+        const double oldb = lo[0];  // old phi of plane p-2
         if (da <= 3) {
             double s[3];
             o1.sums(k ^ 1, parity(0, p - 1), c1, lo, s);
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
         }
         a0.get(k ^ 1, lo);  // colour 0, plane p-3
         if (da <= 3) a0.put(k ^ 1, v);
-        const T oldc = lo[0];
+        const double oldc = lo[0];
         if (db <= 2) {
             double s[3];
             a0.sums(k, parity(1, p - 2), v, lo, s);
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kPT, 4) void k_sweep_pair(PairArgs<T> a) {
         }
         a1.get(k, lo);  // colour 1, plane p-4
         if (db <= 2) a1.put(k, w);
-        const T oldd = lo[0];
+        const double oldd = lo[0];
         if (dc <= 1) {
             double s[3];
             a1.sums(k ^ 1, parity(0, p - 3), w, lo, s);
