@@ -15,6 +15,7 @@
 #include <cmath>
 #include <cstdio>
 #include <fstream>
+#include <functional>
 #include <map>
 #include <sstream>
 #include <string>
@@ -55,6 +56,15 @@ struct pfc_batch {
     // finest size a multiple of kBPX), 1 << ptile_zi coarse planes per tile
     bool ptile = false;
     int ptile_zi = 2;
+    // the finest depth's sweeps two per launch (sweep_pair.h), the stop test's
+    // norm in halves: the pre-sweeps go from u to u2 ahead of the decision, the
+    // rest of the cycle's finest phases work on u2 and the post-sweeps go back
+    bool pair = false;
+    PairArgs<double> *d_pre = nullptr, *d_post = nullptr;
+    PairTile *d_tiles = nullptr;
+    int n_tiles = 0;
+    unsigned long long *halves = nullptr;  // n_tiles maxima of the pre-sweeps, n_tiles of the post-sweeps
+    BState pst{};                          // st with an instance's blocks in those
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool graph_ready = false;
@@ -156,6 +166,77 @@ pfc_status bfail(pfc_batch *B, pfc_status s, const std::string &m) {
     return s;
 }
 
+// Segments, tiles and norm blocks of the paired sweeps.
+bool pair_tables(pfc_batch *B) {
+    const size_t n = (size_t)B->count;
+    std::vector<PairArgs<double>> pre(n), post(n);
+    for (size_t i = 0; i < n; ++i) {
+        pfc_handle *h = B->inst[i];
+        const Level &A = h->lev[0];
+        PairArgs<double> a;
+        a.op = op_of(h, 0);
+        a.op.gate = B->st.active + i;
+        a.picard = B->cfg.lin == PFC_LIN_PICARD;
+        a.f = Tri<const double>{A.phk, A.f.b, A.f.c};
+        a.phk = A.phk;
+        a.u = cst(A.u);
+        a.o = A.u2;
+        pre[i] = a;
+        a.u = cst(A.u2);
+        a.o = A.u;
+        post[i] = a;
+    }
+    // Planes per tile: the ones whose launch is estimated to end first, a tile of
+    // z planes taking z + 5 steps (its halo planes thin out) on the first resident
+    // workgroup that is free, the longest first.
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const int slots = std::max(1, batch_pair_slots(dev));
+    std::vector<PairTile> tiles;
+    long best = -1;
+    for (int zmax : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
+        std::vector<PairTile> v;
+        for (size_t i = 0; i < n; ++i)
+            for (PairTile t : batch_pair_tiles(B->inst[i]->lev[0].n, zmax)) {
+                t.seg = (int)i;
+                t.slot = (unsigned)v.size();
+                v.push_back(t);
+            }
+        std::stable_sort(v.begin(), v.end(),
+                         [](const PairTile &a, const PairTile &b) { return a.z1 - a.z0 > b.z1 - b.z0; });
+        std::vector<long> heap((size_t)slots, 0);  // min-heap of the slots' ends
+        long end = 0;
+        for (const PairTile &t : v) {
+            std::pop_heap(heap.begin(), heap.end(), std::greater<long>());
+            heap.back() += t.z1 - t.z0 + 5;
+            end = std::max(end, heap.back());
+            std::push_heap(heap.begin(), heap.end(), std::greater<long>());
+        }
+        if (best < 0 || end < best) {
+            best = end;
+            tiles.swap(v);
+        }
+    }
+    std::vector<unsigned> first(n, 0), blocks(n, 0);
+    for (const PairTile &t : tiles) ++blocks[(size_t)t.seg];
+    for (size_t i = 1; i < n; ++i) first[i] = first[i - 1] + blocks[i - 1];
+    B->n_tiles = (int)tiles.size();
+    unsigned *pf = nullptr, *pb = nullptr;
+    const bool ok =
+        balloc(B, &B->d_pre, n) && balloc(B, &B->d_post, n) && balloc(B, &B->d_tiles, tiles.size()) &&
+        balloc(B, &B->halves, 2 * tiles.size()) && balloc(B, &pf, n) && balloc(B, &pb, n) &&
+        hipMemcpy(B->d_pre, pre.data(), n * sizeof(pre[0]), hipMemcpyHostToDevice) == hipSuccess &&
+        hipMemcpy(B->d_post, post.data(), n * sizeof(post[0]), hipMemcpyHostToDevice) == hipSuccess &&
+        hipMemcpy(B->d_tiles, tiles.data(), tiles.size() * sizeof(tiles[0]), hipMemcpyHostToDevice) ==
+            hipSuccess &&
+        hipMemcpy(pf, first.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess &&
+        hipMemcpy(pb, blocks.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess;
+    B->pst = B->st;
+    B->pst.norm_first = pf;
+    B->pst.norm_blocks = pb;
+    return ok;
+}
+
 // One cycle of every active instance, aligned by depth from the finest level.
 // tau: the levels at depth d still hold I r in f and I u in ubar (the middle
 // levels' first pre-sweep, the coarsest levels' solve launch forms the tau
@@ -172,7 +253,9 @@ void bcycle(pfc_batch *B, int d, bool fcycle, bool tau = false) {
     auto sweep = [&](int flags) {
         for (int c = 0; c < 2; ++c) phase(B, BK_SMOOTH, mid, B->d_mid[d], c, picard | pk1 | flags);
     };
-    for (int q = 0; q < B->cfg.nu1; ++q) sweep(q == 0 && tau ? 4 : 0);
+    const bool pair = d == 0 && B->pair;
+    if (!pair)
+        for (int q = 0; q < B->cfg.nu1; ++q) sweep(q == 0 && tau ? 4 : 0);
     phase(B, BK_RR, mid, B->d_mid[d], 0, 0);
     // with pre-sweeps the next depth's levels form the tau correction
     // themselves: the middle ones in their first sweep, the coarsest ones in
@@ -188,10 +271,20 @@ void bcycle(pfc_batch *B, int d, bool fcycle, bool tau = false) {
         phase(B, BK_ERR, mid, B->d_mid[d], 0, 0);
         phase(B, BK_PROLONG, mid, B->d_mid[d], B->cfg.nu2 >= 1 ? 1 : 0, 0);
     }
-    for (int q = 0; q < B->cfg.nu2; ++q) sweep(0);
+    if (pair)
+        launch_batch_pair(s, 2, B->d_post, B->d_tiles, B->n_tiles, B->halves + B->n_tiles);
+    else
+        for (int q = 0; q < B->cfg.nu2; ++q) sweep(0);
 }
 
 void record_cycle(pfc_batch *B) {
+    if (B->pair) {
+        launch_batch_pair(B->stream, 1, B->d_pre, B->d_tiles, B->n_tiles, B->halves);
+        launch_batch_update(B->stream, B->d_norm, B->n_norm, B->halves, B->halves + B->n_tiles, B->pst,
+                            B->cfg.tol, B->cfg.max_cycles);
+        bcycle(B, 0, B->cfg.cycle == PFC_CYCLE_F);
+        return;
+    }
     launch_batch_norm(B->stream, B->d_norm, B->n_norm, B->norm_blocks, B->partial, B->st, B->cfg.tol,
                       B->cfg.max_cycles);
     bcycle(B, 0, B->cfg.cycle == PFC_CYCLE_F);
@@ -221,6 +314,9 @@ pfc_status run_step(pfc_batch *B, pfc_step_info *infos_step) {
     const hipStream_t s = B->stream;
     for (int i = 0; i < B->count; ++i) step_begin(B->inst[i], B->prev[i], B->cur[i], B->mu[i], B->om[i]);
     launch_batch_reset(s, B->st, B->count, B->d_valid);
+    if (B->pair)  // what the post-sweeps before the first pre-sweeps would have left
+        launch_batch_seed(s, B->d_norm, B->n_norm, B->norm_blocks, B->partial, B->st, B->pst,
+                          B->halves + B->n_tiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return bfail(B, PFC_ERR_HIP, hipGetErrorString(e));
     if (!B->graph_ready) {
@@ -353,6 +449,13 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
     }
     B->st.norm_first = nf;
     B->st.norm_blocks = nbk;
+    // V(2,2) or F(2,2) on instances of 32^3 and larger: a cycle of 2 to 64 of
+    // them (0.5 to 20 million points) takes 0.73 to 0.95 of the half-sweeps' time,
+    // 20.1 million points 3.42 -> 2.50 ms, 0.92 million 412 -> 376 us.
+    B->pair = cfgs[0].nu1 == 2 && cfgs[0].nu2 == 2 &&
+              std::all_of(B->inst.begin(), B->inst.end(), [](const pfc_handle *h) {
+                  return batch_pair_fits(h->lev[0].n) && h->lev[0].u2.a;
+              });
     // segment lists by depth
     B->h_all.resize(B->maxdepth);
     B->h_mid.resize(B->maxdepth);
@@ -361,7 +464,9 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
         for (int l = 0; l < nlev[i]; ++l) {
             const BSeg g = make_seg(B->inst[i], l, i, B->st.active + i);
             B->h_all[l].push_back(g);
-            (l + 1 < nlev[i] ? B->h_mid[l] : B->h_bot[l]).push_back(g);
+            BSeg m = g;
+            if (l == 0 && B->pair) m.u = B->inst[i]->lev[0].u2;
+            (l + 1 < nlev[i] ? B->h_mid[l] : B->h_bot[l]).push_back(m);
         }
     auto upload = [&](const std::vector<BSeg> &v, BSeg **d) -> bool {
         if (v.empty()) {
@@ -414,6 +519,7 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
          hipHostMalloc((void **)&B->h_num, n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_stats, 2 * n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_res, 2 * n * sizeof(double), 0) == hipSuccess;
+    if (ok && B->pair) ok = pair_tables(B);
     if (!ok) {
         delete B;
         return bfail(nullptr, PFC_ERR_OOM, "allocation of batch tables failed");
@@ -520,7 +626,9 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
         b->slots[kind] = ps ? (unsigned)batch_phase_slots(kind, th, dev) : 0u;
     };
     for (int kind = 0; kind < 5; ++kind) {
-        const std::string key = sig.str() + "|" + kind_name[kind];
+        // paired sweeps leave the half-sweeps to the coarser depths
+        const bool coarse = kind == BK_SMOOTH && b->pair;
+        const std::string key = sig.str() + "|" + kind_name[kind] + (coarse ? "_coarse" : "");
         auto it = cache.find(key);
         bool ps;
         int th, sh;
@@ -528,10 +636,18 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
             apply(kind, ps, th, sh);
             continue;
         }
-        const int d = kind == BK_TAU ? 1 : 0;
-        if (d >= b->maxdepth || b->h_mid[0].empty()) continue;
-        const auto &segs = kind == BK_TAU ? b->h_all[1] : b->h_mid[0];
-        BSeg *dsegs = kind == BK_TAU ? b->d_all[1] : b->d_mid[0];
+        // every depth that runs the phase: a shape that suits the finest alone can
+        // cost the small ones, which are many, as much as it gains
+        struct List {
+            const std::vector<BSeg> *h;
+            BSeg *d;
+        };
+        std::vector<List> lists;
+        for (int d = kind == BK_TAU || coarse ? 1 : 0; d < b->maxdepth; ++d) {
+            const auto &h = kind == BK_TAU ? b->h_all[d] : b->h_mid[d];
+            if (!h.empty()) lists.push_back(List{&h, kind == BK_TAU ? b->d_all[d] : b->d_mid[d]});
+        }
+        if (lists.empty()) continue;
         float best = 1e30f;
         int best_code = 256 * 100 + 2;
         // the interpolation is timed in the form the cycle runs
@@ -543,18 +659,27 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
                 for (int sp = 0; sp < kShapes; ++sp) {
                     if ((kTileMin << (sp % kWOpts)) < thr) continue;
                     if (kind == BK_ERR && sp >= kWOpts) continue;  // one plane: Z is moot
-                    const unsigned nt = tiles_of(segs, kind, sp);
                     auto run = [&](int rep) {
-                        launch_batch(b->stream, kind, dsegs, (int)segs.size(), nt, sp, thr, sl,
-                                     kind == BK_PROLONG ? pflag : rep & 1, 0);
+                        for (const List &l : lists)
+                            launch_batch(b->stream, kind, l.d, (int)l.h->size(), tiles_of(*l.h, kind, sp),
+                                         sp, thr, sl, kind == BK_PROLONG ? pflag : rep & 1, 0);
                     };
-                    for (int rep = 0; rep < 2; ++rep) run(rep);
-                    (void)hipEventRecord(t0, b->stream);
-                    for (int rep = 0; rep < 6; ++rep) run(rep);
-                    (void)hipEventRecord(t1, b->stream);
-                    if (hipEventSynchronize(t1) != hipSuccess) break;
-                    float ms = 0.f;
-                    (void)hipEventElapsedTime(&ms, t0, t1);
+                    auto timed = [&](int reps) {  // < 0 on error
+                        (void)hipEventRecord(t0, b->stream);
+                        for (int rep = 0; rep < reps; ++rep) run(rep);
+                        (void)hipEventRecord(t1, b->stream);
+                        float t = -1.f;
+                        if (hipEventSynchronize(t1) != hipSuccess) return -1.f;
+                        (void)hipEventElapsedTime(&t, t0, t1);
+                        return t;
+                    };
+                    // two unmeasured runs unless the second shows that this is no candidate
+                    run(0);
+                    float ms = timed(1);
+                    if (ms < 0.f) break;
+                    if (6.f * ms > 1.5f * best) continue;
+                    ms = timed(6);
+                    if (ms < 0.f) break;
                     if (ms < best) {
                         best = ms;
                         best_code = persistent * 100000 + thr * 100 + sp;

@@ -1259,14 +1259,16 @@ __global__ __launch_bounds__(kBlock) void kb_norm(const BSeg *segs, int nseg,
 // finished if the norm is at most tol (or not finite, or max_cycles cycles
 // were done), otherwise one more cycle is counted.
 __global__ __launch_bounds__(kBlock) void kb_update(const BSeg *segs, int nseg,
-                                                    const unsigned long long *partial, BState st,
+                                                    const unsigned long long *partial,
+                                                    const unsigned long long *second, BState st,
                                                     double tol, int max_cycles) {
     const int s = blockIdx.x;
     if (s >= nseg) return;
     const int i = segs[s].inst;
     const unsigned b0 = st.norm_first[s], b1 = b0 + st.norm_blocks[s];
     unsigned long long m = 0;
-    for (unsigned b = b0 + threadIdx.x; b < b1; b += kBlock) m = umax(m, partial[b]);
+    for (unsigned b = b0 + threadIdx.x; b < b1; b += kBlock)
+        m = umax(m, second ? umax(partial[b], second[b]) : partial[b]);
     m = block_max_u64(m);
     if (threadIdx.x != 0 || !st.active[i]) return;
     const double r = __longlong_as_double((long long)m);
@@ -1283,6 +1285,17 @@ __global__ __launch_bounds__(kBlock) void kb_update(const BSeg *segs, int nseg,
     } else {
         st.cycles[i] += 1;
     }
+}
+
+__global__ __launch_bounds__(kBlock) void kb_seed(const unsigned long long *partial, BState st,
+                                                  BState pst, unsigned long long *second) {
+    const int s = blockIdx.x;
+    const unsigned b0 = st.norm_first[s], b1 = b0 + st.norm_blocks[s];
+    unsigned long long m = 0;
+    for (unsigned b = b0 + threadIdx.x; b < b1; b += kBlock) m = umax(m, partial[b]);
+    m = block_max_u64(m);
+    const unsigned p0 = pst.norm_first[s], p1 = p0 + pst.norm_blocks[s];
+    for (unsigned b = p0 + threadIdx.x; b < p1; b += kBlock) second[b] = b == p0 ? m : 0ull;
 }
 
 // Batched column-tiled interpolation: the tile of k_prolong_tile for one
@@ -1493,8 +1506,20 @@ void launch_batch_coarse(hipStream_t s, const BSeg *segs, int nseg, int tau) {
 void launch_batch_norm(hipStream_t s, const BSeg *segs, int nseg, unsigned ntiles,
                        unsigned long long *partial, BState st, double tol, int max_cycles) {
     hipLaunchKernelGGL(kb_norm, dim3(std::max(ntiles, 1u)), dim3(kBlock), 0, s, segs, nseg, partial);
-    hipLaunchKernelGGL(kb_update, dim3(nseg), dim3(kBlock), 0, s, segs, nseg,
-                       (const unsigned long long *)partial, st, tol, max_cycles);
+    launch_batch_update(s, segs, nseg, partial, nullptr, st, tol, max_cycles);
+}
+
+void launch_batch_update(hipStream_t s, const BSeg *segs, int nseg, const unsigned long long *part,
+                         const unsigned long long *second, BState st, double tol, int max_cycles) {
+    hipLaunchKernelGGL(kb_update, dim3(nseg), dim3(kBlock), 0, s, segs, nseg, part, second, st, tol,
+                       max_cycles);
+}
+
+void launch_batch_seed(hipStream_t s, const BSeg *segs, int nseg, unsigned ntiles,
+                       unsigned long long *partial, BState st, BState pst, unsigned long long *second) {
+    hipLaunchKernelGGL(kb_norm, dim3(std::max(ntiles, 1u)), dim3(kBlock), 0, s, segs, nseg, partial);
+    hipLaunchKernelGGL(kb_seed, dim3(nseg), dim3(kBlock), 0, s, (const unsigned long long *)partial, st,
+                       pst, second);
 }
 
 void launch_batch_reset(hipStream_t s, BState st, int count, int **valid) {

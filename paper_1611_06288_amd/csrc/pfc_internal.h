@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace pfc {
 
 // Three grid functions (phi, mu, omega) of one level.
@@ -118,6 +120,18 @@ bool fused_fits(int n);           // n admits the fused sweep's column tiling
 int fused_slots(int device, bool mob = false);      // resident fused-sweep workgroups on the device (0 on error)
 int fused_nz(int n, int slots);   // plane ranges per column for a level of size n
 constexpr int kFusedMinN = 128;  // smaller levels use the half-sweeps
+
+// One level's two sweeps in one pass (sweep_pair.h).
+template <typename T>
+struct PairArgs {
+    OpParams op;
+    int picard = 0, nz = 1, skip0 = 0;
+    int stream = 0;  // stores past the caches
+    Tri<const T> u{nullptr, nullptr, nullptr}, f{nullptr, nullptr, nullptr};
+    Tri<T> o{nullptr, nullptr, nullptr};
+    const T *phk = nullptr, *base = nullptr;
+    unsigned long long *part = nullptr;
+};
 
 // Two full red-black sweeps in one pass (sweep_pair.h), bitwise two fused sweeps;
 // arguments as launch_sweep_fused, M = 1 only.  The level is cut into pair_nz
@@ -428,6 +442,29 @@ int batch_phase_slots(int kind, int threads, int device);
 void launch_batch_coarse(hipStream_t s, const BSeg *segs, int nseg, int tau);
 void launch_batch_norm(hipStream_t s, const BSeg *segs, int nseg, unsigned ntiles,
                        unsigned long long *partial, BState st, double tol, int max_cycles);
+// The same test on the two halves that the batched pairs leave, part[b] and
+// second[b] for the blocks b of an instance (st.norm_first, st.norm_blocks).
+void launch_batch_update(hipStream_t s, const BSeg *segs, int nseg, const unsigned long long *part,
+                         const unsigned long long *second, BState st, double tol, int max_cycles);
+// The whole-level norm of every instance (partial as launch_batch_norm's, the
+// blocks by st) into the first of its blocks in second (by pst), zeros in the others.
+void launch_batch_seed(hipStream_t s, const BSeg *segs, int nseg, unsigned ntiles,
+                       unsigned long long *partial, BState st, BState pst, unsigned long long *second);
+// Two sweeps of every instance's finest level in one launch: a column of planes
+// [z0, z1) per workgroup, the box at (x0, y0) px points wide, the norm half (1, 2
+// as launch_sweep_pair64) to part[slot].  The gate in a seg's op is its instance's
+// active flag.
+struct PairTile {
+    int seg, x0, y0, px, z0, z1;
+    unsigned slot;
+    int unused;
+};
+bool batch_pair_fits(int n);
+int batch_pair_slots(int device);
+// Tiles of one level at most zmax planes long (seg and slots to be filled in).
+std::vector<PairTile> batch_pair_tiles(int n, int zmax);
+void launch_batch_pair(hipStream_t s, int nrm, const PairArgs<double> *segs, const PairTile *tiles,
+                       int ntiles, unsigned long long *part);
 void launch_batch_reset(hipStream_t s, BState st, int count, int **valid);
 // Column-tiled interpolation of the batched form (fine levels whose size is a
 // multiple of kBPX): a kBPX x 8 fine column and 1 << zi coarse planes of one

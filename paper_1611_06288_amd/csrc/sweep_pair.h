@@ -23,8 +23,8 @@
 // Why: a sweep is bound by memory (64 B per point against 65 operations), and
 // two in one pass move 64 B per point once.  What is left above that are the
 // halo's second reads, which the L2 catches in part: the box is as large as the
-// LDS admits (141 of 160 KB in FP64; 32 x 16 boxes, two workgroups per CU, take
-// 350 us at 256^3 for the 301 of 64 x 16), a workgroup runs fourteen waves, and
+// LDS admits (141 of 160 KB; 32 x 16 boxes, two workgroups per CU, take 350 us at
+// 256^3 for the 301 of 64 x 16; the ensembles' levels need them), a workgroup runs fourteen waves, and
 // the inputs stay in registers between the sweeps (122-128 VGPRs; without the
 // coefficients in scalar registers they spill).  Two sweeps, two fused sweeps ->
 // this: 512^3 3.9 -> 2.4 ms, 256^3 479 -> 297 us, 192^3 195 -> 138, 128^3 54 -> 50
@@ -39,60 +39,56 @@
 
 namespace pfc {
 
-constexpr int kPX = 64, kPY = 16;               // box
-constexpr int kPH = 4;                          // halo
-constexpr int kPW = kPX / 2 + kPH;              // x-pairs with the halo
-constexpr int kPR = kPY + 2 * kPH;              // rows with the halo
-constexpr int kPT = 896;                        // threads
+constexpr int kPH = 4;  // halo
 
-// The x-pairs by the distance of their nearer point to the box, the box first,
-// so that a half-sweep's idle lanes fill whole waves.  Entry: pair | row << 8.
-struct PairList {
-    unsigned short e[kPT];
-    int n;
-};
-constexpr int pair_dx(int x) { return x < kPH ? kPH - x : (x >= kPH + kPX ? x - (kPH + kPX - 1) : 0); }
-constexpr int pair_dy(int r) { return r < kPH ? kPH - r : (r >= kPH + kPY ? r - (kPH + kPY - 1) : 0); }
-constexpr PairList pair_list() {
-    PairList l{};
-    for (int d = 0; d <= kPH; ++d)
-        for (int r = 0; r < kPR; ++r)
-            for (int m = 0; m < kPW; ++m) {
-                const int a = pair_dx(2 * m), b = pair_dx(2 * m + 1);
-                if (pair_dy(r) + (a < b ? a : b) == d) l.e[l.n++] = (unsigned short)(m | r << 8);
-            }
-    for (int i = l.n; i < kPT; ++i) l.e[i] = 0xffff;
-    return l;
-}
-static_assert(pair_list().n <= kPT, "one thread per x-pair");
+template <int PX, int PY, int TH>
+struct PairGeo {
+    static constexpr int kX = PX, kY = PY, kThreads = TH;  // box, threads
+    static constexpr int kW = PX / 2 + kPH;                // x-pairs with the halo
+    static constexpr int kR = PY + 2 * kPH;                // rows with the halo
 
-// LDS planes of the values a half-sweep reads: old colour 1, colour 0 and
-// colour 1 of the first sweep, colour 0 of the second.  Buffer B holds the
-// points up to distance 4 - B.
-template <int B>
-struct PairBuf {
-    static constexpr int X = B / 2;               // first pair, first row
-    static constexpr int Y = B;
-    static constexpr int W = kPW - 2 * X, R = kPR - 2 * Y;
-    static constexpr int N = W * R;               // of one field and plane
+    // distance of a local coordinate to the box's extent b
+    __host__ __device__ static constexpr int excess(int v, int b) {
+        return v < kPH ? kPH - v : (v >= kPH + b ? v - (kPH + b - 1) : 0);
+    }
+    // The x-pairs by the distance of their nearer point to the box, the box
+    // first, so that a half-sweep's idle lanes fill whole waves.
+    // Entry: pair | row << 8.
+    struct List {
+        unsigned short e[TH];
+        int n;
+    };
+    static constexpr List list() {
+        List l{};
+        for (int d = 0; d <= kPH; ++d)
+            for (int r = 0; r < kR; ++r)
+                for (int m = 0; m < kW; ++m) {
+                    const int a = excess(2 * m, PX), b = excess(2 * m + 1, PX);
+                    if (excess(r, PY) + (a < b ? a : b) == d) l.e[l.n++] = (unsigned short)(m | r << 8);
+                }
+        for (int i = l.n; i < TH; ++i) l.e[i] = 0xffff;
+        return l;
+    }
+    // LDS planes of the values a half-sweep reads: old colour 1, colour 0 and
+    // colour 1 of the first sweep, colour 0 of the second.  Buffer B holds the
+    // points up to distance 4 - B.
+    template <int B>
+    struct Buf {
+        static constexpr int X = B / 2, Y = B;  // first pair, first row
+        static constexpr int W = kW - 2 * X, R = kR - 2 * Y;
+        static constexpr int N = W * R;  // of one field and plane
+    };
+    static constexpr int kLds = 6 * (Buf<0>::N + Buf<1>::N + Buf<2>::N + Buf<3>::N);
 };
-constexpr int kPairLds = 6 * (PairBuf<0>::N + PairBuf<1>::N + PairBuf<2>::N + PairBuf<3>::N);
+using PairWide = PairGeo<64, 16, 896>;   // one workgroup per CU
+using PairSmall = PairGeo<32, 16, 512>;  // two
 
-template <typename T>
-struct PairArgs {
-    OpParams op;
-    int picard = 0, nz = 1, skip0 = 0;
-    int stream = 0;  // stores past the caches
-    Tri<const T> u, f;
-    Tri<T> o;
-    const T *phk = nullptr, *base = nullptr;
-    unsigned long long *part = nullptr;
-};
+template <typename G>
+__device__ constexpr typename G::List kPairList = G::list();
 
 // One buffer as a thread sees it: its own slot and its neighbours'.
-template <int B>
+template <typename P>
 struct PairSlot {
-    using P = PairBuf<B>;
     double *q;  // own x-pair, field 0, plane slot 0
     __device__ __forceinline__ double *at(int slot) const { return q + slot * 3 * P::N; }
     __device__ __forceinline__ void put(int slot, const double (&v)[3]) const {
@@ -120,5 +116,181 @@ struct PairSlot {
                       (zp[fl] + zm[fl]);
     }
 };
+
+// NRM: as the fused sweep's, half of the stop-test norm: 1 over the colour-0 points of the input (formed with the
+// first half-sweep's neighbour sums), 2 over the colour-1 points of the output
+// (with the last one's).  PK1: f.a is phi^k itself, loaded once.
+// One workgroup's column: the box at (x0, y0), px points wide (the whole box or
+// its left part), planes [z0, z1).  Returns the thread's share of the norm.
+template <typename G, typename T, bool DELTA, int NRM, bool PK1>
+__device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, int x0, int y0, int px,
+                                                          int z0, int z1, double *lds) {
+    constexpr int NI = (PK1 ? 3 : 4) + (DELTA ? 1 : 0);  // phi^k, f2, f3 (, f1) (, base)
+    const int n = a.op.lay.n, hn = n >> 1;
+    const unsigned un = (unsigned)n, uhn = (unsigned)hn, plane = un * uhn, H = un * plane;
+    const unsigned e = kPairList<G>.e[threadIdx.x];
+    const bool act = e != 0xffffu;
+    const int mx = act ? (int)(e & 255u) : kPH, row = act ? (int)(e >> 8) : kPH;
+    auto wn = [n](int v) { return v < 0 ? v + n : (v >= n ? v - n : v); };
+    const int y = y0 - kPH + row;
+    const int m = x0 / 2 - kPH / 2 + mx;
+    const unsigned g0 = (unsigned)wn(y) * uhn + (unsigned)(m < 0 ? m + hn : (m >= hn ? m - hn : m));
+    // distance to the box in x and y of the pair's two points
+    const int d0 = act ? G::excess(row, G::kY) + G::excess(2 * mx, px) : 64;
+    const int d1 = act ? G::excess(row, G::kY) + G::excess(2 * mx + 1, px) : 64;
+    auto parity = [y](int c, int q) { return (c + y + q) & 1; };
+    // steps of the chain left at the point of colour c of plane q
+    auto dist = [&](int c, int q) {
+        const int dz = q < z0 ? z0 - q : (q >= z1 ? q - z1 + 1 : 0);
+        return (parity(c, q) ? d1 : d0) + dz;
+    };
+    auto gidx = [&](int c, int q) { return (c ? H : 0u) + (unsigned)wn(q) * plane + g0; };
+
+    using B0 = typename G::template Buf<0>;
+    using B1 = typename G::template Buf<1>;
+    using B2 = typename G::template Buf<2>;
+    using B3 = typename G::template Buf<3>;
+    double *const l0 = lds, *const l1 = l0 + 6 * B0::N, *const l2 = l1 + 6 * B1::N, *const l3 = l2 + 6 * B2::N;
+    // A thread whose pair lies outside a buffer never touches it: clamp its slot
+    auto own = [&](auto buf, double *l) {
+        using P = decltype(buf);
+        const int r = min(max(row - P::Y, 0), P::R - 1), c = min(max(mx - P::X, 0), P::W - 1);
+        return l + r * P::W + c;
+    };
+    const PairSlot<B0> o1{own(B0{}, l0)};  // old colour 1
+    const PairSlot<B1> a0{own(B1{}, l1)};  // first sweep
+    const PairSlot<B2> a1{own(B2{}, l2)};
+    const PairSlot<B3> b0{own(B3{}, l3)};  // second sweep, colour 0
+
+    PointCoef co(a.op);
+    co.to_scalar();
+    T c1n[3];              // old colour 1 of the next plane
+    T phin[3];             // old phi (NRM = 1: mu, omega) of the next colour-0 point
+    T in0[4][NI], in1[4][NI];  // inputs of colour 0 at planes p, p-1 .. p-3, of colour 1 a plane lower
+    auto load_in = [&](int c, int q, T (&v)[NI]) {
+        const unsigned g = gidx(c, q);
+        v[0] = a.phk[g];
+        v[1] = a.f.b[g];
+        v[2] = a.f.c[g];
+        if constexpr (!PK1) v[3] = a.f.a[g];
+        if constexpr (DELTA) v[NI - 1] = a.base[g];
+    };
+    auto load_c1 = [&](int q) {
+        if (dist(1, q) <= 4) {
+            const unsigned g = gidx(1, q);
+            c1n[0] = a.u.a[g];
+            c1n[1] = a.u.b[g];
+            c1n[2] = a.u.c[g];
+        }
+    };
+    auto load_points = [&](int p) {  // what step p + 1 relaxes first: colour 0 of p, colour 1 of p - 1
+        const int d = dist(0, p);
+        if (d <= 3) {
+            const unsigned g = gidx(0, p);
+            phin[0] = a.u.a[g];
+            if (NRM == 1 && d == 0) {
+                phin[1] = a.u.b[g];
+                phin[2] = a.u.c[g];
+            }
+            load_in(0, p, in0[0]);
+        }
+        if (dist(1, p - 1) <= 2) load_in(1, p - 1, in1[0]);
+    };
+    auto solve = [&](double ph, const T (&v)[NI], const double (&s)[3], double (&o)[3]) {
+        double x, y2, w;
+        point_solve<DELTA>(co, a.picard, ph, (double)v[0], DELTA ? (double)v[NI - 1] : 0.0,
+                           (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], s[1], s[2], s[0], x,
+                           y2, w);
+        o[0] = (T)x;  // rounded to the level's type
+        o[1] = (T)y2;
+        o[2] = (T)w;
+    };
+    unsigned long long nrm = 0;
+    auto norm = [&](const double (&w)[3], const T (&v)[NI], const double (&s)[3]) {
+        const double h2inv = a.op.h2inv;
+        const double ls[3] = {(s[0] - 6.0 * w[0]) * h2inv, (s[1] - 6.0 * w[1]) * h2inv,
+                              (s[2] - 6.0 * w[2]) * h2inv};
+        double r[3];
+        resid_from_lap<false>(a.op, ls, w[0], w[1], w[2],
+                              (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], (double)v[0], 0.0, r);
+        nrm = umax(nrm, umax(abs_bits(r[0]), umax(abs_bits(r[1]), abs_bits(r[2]))));
+    };
+    auto store = [&](int c, int q, const double (&v)[3], bool all) {
+        const unsigned g = gidx(c, q);
+        if (a.stream) {
+            __builtin_nontemporal_store((T)v[0], &a.o.a[g]);
+            if (all) {
+                __builtin_nontemporal_store((T)v[1], &a.o.b[g]);
+                __builtin_nontemporal_store((T)v[2], &a.o.c[g]);
+            }
+        } else {
+            a.o.a[g] = (T)v[0];
+            if (all) {
+                a.o.b[g] = (T)v[1];
+                a.o.c[g] = (T)v[2];
+            }
+        }
+    };
+
+    load_c1(z0 - 4);
+    for (int p = z0 - 4; p <= z1 + 3; ++p) {
+        const int k = p & 1;  // LDS slot of planes p, p-2, p-4
+        // a value's lower z-neighbour is taken from the slot it replaces
+        double c1[3], lo[3], v[3], w[3], w0[3] = {phin[0], phin[1], phin[2]};
+        o1.get(k, lo);  // old colour 1, plane p-2
+        if (dist(1, p) <= 4) {
+            c1[0] = c1n[0];
+            c1[1] = c1n[1];
+            c1[2] = c1n[2];
+            o1.put(k, c1);
+        }
+#pragma unroll
+        for (int i = 3; i > 0; --i)
+#pragma unroll
+            for (int t = 0; t < NI; ++t) {
+                in0[i][t] = in0[i - 1][t];
+                in1[i][t] = in1[i - 1][t];
+            }
+        load_c1(p + 1);
+        load_points(p);
+        const int da = dist(0, p - 1), db = dist(1, p - 2), dc = dist(0, p - 3), dd = dist(1, p - 4);
+        const double oldb = lo[0];  // old phi of plane p-2
+        if (da <= 3) {
+            double s[3];
+            o1.sums(k ^ 1, parity(0, p - 1), c1, lo, s);
+            if constexpr (NRM == 1)
+                if (da == 0) norm(w0, in0[1], s);
+            solve(w0[0], in0[1], s, v);
+        }
+        a0.get(k ^ 1, lo);  // colour 0, plane p-3
+        if (da <= 3) a0.put(k ^ 1, v);
+        const double oldc = lo[0];
+        if (db <= 2) {
+            double s[3];
+            a0.sums(k, parity(1, p - 2), v, lo, s);
+            solve(oldb, in1[1], s, w);
+        }
+        a1.get(k, lo);  // colour 1, plane p-4
+        if (db <= 2) a1.put(k, w);
+        const double oldd = lo[0];
+        if (dc <= 1) {
+            double s[3];
+            a1.sums(k ^ 1, parity(0, p - 3), w, lo, s);
+            solve(oldc, in0[3], s, v);
+            if (dc == 0) store(0, p - 3, v, !a.skip0);
+        }
+        b0.get(k ^ 1, lo);  // second colour 0, plane p-5
+        if (dc <= 1) b0.put(k ^ 1, v);
+        if (dd <= 0) {
+            double s[3];
+            b0.sums(k, parity(1, p - 4), v, lo, s);
+            solve(oldd, in1[3], s, w);
+            if constexpr (NRM == 2) norm(w, in1[3], s);
+            store(1, p - 4, w, true);
+        }
+        __syncthreads();
+    }
+    return nrm;
+}
 
 }  // namespace pfc
