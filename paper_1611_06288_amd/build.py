@@ -19,7 +19,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
 SOURCES = ["brick.hip", "brick_mob.hip", "brick_f32.hip", "brick_adj.hip", "kernels.hip", "smooth.hip",
-           "sweep_pair.hip",
+           "sweep_pair.hip", "setup.hip",
            "residual.hip", "tail.hip", "runtime.cpp", "mixed.cpp", "timeloop.cpp", "adjoint.hip",
            "batch.cpp", "noalloc.hip"]
 

@@ -68,6 +68,15 @@ struct pfc_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool graph_ready = false;
+    // set-up and end of a step in one launch each: per instance its fields, of
+    // whose phi buffers rot, rot + 1, rot + 2 (mod 3) are prev, cur and nxt
+    BatchIO *d_io = nullptr;
+    BlockRef *d_io_blocks = nullptr;
+    unsigned io_blocks = 0;
+    int rot = 0;
+    std::vector<RestrictSeg *> d_rs;  // per depth: its phi^k to the next
+    std::vector<BlockRef *> d_rs_blocks;
+    std::vector<unsigned> rs_blocks;
     std::vector<void *> allocs;
     std::string err;
     ~pfc_batch();
@@ -310,9 +319,67 @@ pfc_status capture(pfc_batch *B) {
     return PFC_OK;
 }
 
+// Tables of the set-up and end launches (instances of n = 4, whose only level is
+// in natural order, leave them empty: those batches go instance by instance).
+bool io_tables(pfc_batch *B) {
+    for (auto *h : B->inst)
+        if (!h->lev[0].lay.split) return true;
+    auto upload = [&](const auto &v, auto **d) {
+        return balloc(B, d, v.size()) &&
+               hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice) == hipSuccess;
+    };
+    auto add = [](std::vector<BlockRef> &v, int seg, size_t items) {
+        for (size_t b = 0; b * kBlock < items; ++b) v.push_back(BlockRef{seg, (unsigned)b});
+    };
+    std::vector<BatchIO> io;
+    std::vector<BlockRef> blocks;
+    for (int i = 0; i < B->count; ++i) {
+        const Level &A = B->inst[i]->lev[0];
+        io.push_back(BatchIO{op_of(B->inst[i], 0), {B->prev[i], B->cur[i], B->nxt[i]}, B->mu[i], B->om[i],
+                             A.f, A.u, A.phk});
+        add(blocks, i, A.P / 2);
+    }
+    bool ok = upload(io, &B->d_io) && upload(blocks, &B->d_io_blocks);
+    B->io_blocks = (unsigned)blocks.size();
+    for (int d = 0; d + 1 < B->maxdepth && ok; ++d) {
+        std::vector<RestrictSeg> segs;
+        blocks.clear();
+        for (auto *h : B->inst)
+            if (d + 1 < h->nlev) {
+                const Level &A = h->lev[d], &C = h->lev[d + 1];
+                add(blocks, (int)segs.size(), C.P);
+                segs.push_back(RestrictSeg{A.lay, C.lay, A.phk, C.phk});
+            }
+        RestrictSeg *ds = nullptr;
+        BlockRef *db = nullptr;
+        ok = upload(segs, &ds) && upload(blocks, &db);
+        B->d_rs.push_back(ds);
+        B->d_rs_blocks.push_back(db);
+        B->rs_blocks.push_back((unsigned)blocks.size());
+    }
+    return ok;
+}
+
+void steps_begin(pfc_batch *B) {
+    if (!B->d_io) {
+        for (int i = 0; i < B->count; ++i) step_begin(B->inst[i], B->prev[i], B->cur[i], B->mu[i], B->om[i]);
+        return;
+    }
+    launch_batch_begin(B->stream, B->d_io, B->d_io_blocks, B->io_blocks, B->rot, (B->rot + 1) % 3);
+    for (size_t d = 0; d < B->d_rs.size(); ++d)
+        launch_batch_restrict(B->stream, B->d_rs[d], B->d_rs_blocks[d], B->rs_blocks[d]);
+}
+
+void steps_end(pfc_batch *B) {
+    if (!B->d_io)
+        for (int i = 0; i < B->count; ++i) step_end(B->inst[i], B->nxt[i], B->mu[i], B->om[i]);
+    else
+        launch_batch_end(B->stream, B->d_io, B->d_io_blocks, B->io_blocks, (B->rot + 2) % 3);
+}
+
 pfc_status run_step(pfc_batch *B, pfc_step_info *infos_step) {
     const hipStream_t s = B->stream;
-    for (int i = 0; i < B->count; ++i) step_begin(B->inst[i], B->prev[i], B->cur[i], B->mu[i], B->om[i]);
+    steps_begin(B);
     launch_batch_reset(s, B->st, B->count, B->d_valid);
     if (B->pair)  // what the post-sweeps before the first pre-sweeps would have left
         launch_batch_seed(s, B->d_norm, B->n_norm, B->norm_blocks, B->partial, B->st, B->pst,
@@ -331,7 +398,7 @@ pfc_status run_step(pfc_batch *B, pfc_step_info *infos_step) {
         if (e != hipSuccess) return bfail(B, PFC_ERR_HIP, std::string("batched cycle: ") + hipGetErrorString(e));
         if (std::none_of(B->h_num, B->h_num + B->count, [](int a) { return a != 0; })) break;
     }
-    for (int i = 0; i < B->count; ++i) step_end(B->inst[i], B->nxt[i], B->mu[i], B->om[i]);
+    steps_end(B);
     const size_t n = (size_t)B->count;
     e = hipMemcpyAsync(B->h_stats, B->st.cycles, n * sizeof(int), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(B->h_stats + n, B->st.status, n * sizeof(int), hipMemcpyDeviceToHost, s);
@@ -351,6 +418,7 @@ pfc_status run_step(pfc_batch *B, pfc_step_info *infos_step) {
         std::swap(B->prev[i], B->nxt[i]);   // nxt <- old prev (spare)
         std::swap(B->prev[i], B->cur[i]);   // prev <- old cur, cur <- new phi
     }
+    B->rot = (B->rot + 1) % 3;
     return worst;
 }
 
@@ -520,6 +588,7 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
          hipHostMalloc((void **)&B->h_stats, 2 * n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_res, 2 * n * sizeof(double), 0) == hipSuccess;
     if (ok && B->pair) ok = pair_tables(B);
+    ok = ok && io_tables(B);
     if (!ok) {
         delete B;
         return bfail(nullptr, PFC_ERR_OOM, "allocation of batch tables failed");
@@ -606,7 +675,7 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
     int dev = 0;
     (void)hipGetDevice(&dev);
     // make the working buffers hold a sane state to time on
-    for (int i = 0; i < b->count; ++i) step_begin(b->inst[i], b->prev[i], b->cur[i], b->mu[i], b->om[i]);
+    steps_begin(b);
     launch_batch_reset(b->stream, b->st, b->count, b->d_valid);
     hipEvent_t t0, t1;
     (void)hipEventCreate(&t0);

@@ -353,6 +353,12 @@ void launch_source(hipStream_t s, const OpParams &op, const double *phk, const d
 void launch_init_guess(hipStream_t s, const OpParams &nat, const double *phi0, double *mu,
                        double *om);
 
+// A time step's set-up on a colour-split finest level (setup.hip): source, starting
+// iterate and phi^k from the natural-layout fields; and its iterate back to them.
+void launch_step_begin(hipStream_t s, const OpParams &op, const double *cur, const double *prev,
+                       const double *mu, const double *om, Tri<double> f, Tri<double> u, double *phk);
+void launch_step_end(hipStream_t s, const Lay &L, Tri<double> u, double *phi, double *mu, double *om);
+
 // Layout conversion of `count` consecutive fields between natural and `lay`
 // (with a type cast).
 template <typename S, typename D>
@@ -466,6 +472,29 @@ std::vector<PairTile> batch_pair_tiles(int n, int zmax);
 void launch_batch_pair(hipStream_t s, int nrm, const PairArgs<double> *segs, const PairTile *tiles,
                        int ntiles, unsigned long long *part);
 void launch_batch_reset(hipStream_t s, BState st, int count, int **valid);
+// Set-up and end of a step of every instance (setup.hip).  p: an instance's three
+// phi buffers, of which ip, ic, in are the previous, the current and the next; a
+// workgroup takes block blk of instance or segment seg.
+struct BatchIO {
+    OpParams op;
+    double *p[3];
+    double *mu, *om;
+    Tri<double> f, u;
+    double *phk;
+};
+struct BlockRef {
+    int seg;
+    unsigned blk;
+};
+struct RestrictSeg {
+    Lay fine, coarse;
+    const double *from;
+    double *to;
+};
+void launch_batch_begin(hipStream_t s, const BatchIO *io, const BlockRef *blocks, unsigned count, int ip,
+                        int ic);
+void launch_batch_end(hipStream_t s, const BatchIO *io, const BlockRef *blocks, unsigned count, int in);
+void launch_batch_restrict(hipStream_t s, const RestrictSeg *segs, const BlockRef *blocks, unsigned count);
 // Column-tiled interpolation of the batched form (fine levels whose size is a
 // multiple of kBPX): a kBPX x 8 fine column and 1 << zi coarse planes of one
 // instance per workgroup, the coarse error formed while staged (no

@@ -561,9 +561,13 @@ void step_begin(pfc_handle *H, const double *phi_prev, const double *phi_cur, co
     // previous step: the chord iteration rebuilds it wherever an update
     // contracts by less than 4x, so a stale inverse costs iterations, never
     // accuracy (each solve still runs to its 1e-14 update bound).
-    launch_source(H->stream, op_of(H, 0), phi_cur, phi_prev, A.f);
-    to_level0(H, phi_cur, mu, omega);
-    launch_to_lay<double, double>(H->stream, A.lay, phi_cur, A.phk, 1);
+    if (A.lay.split) {
+        launch_step_begin(H->stream, op_of(H, 0), phi_cur, phi_prev, mu, omega, A.f, A.u, A.phk);
+    } else {  // n = 4: the finest level is the coarsest
+        launch_source(H->stream, op_of(H, 0), phi_cur, phi_prev, A.f);
+        to_level0(H, phi_cur, mu, omega);
+        launch_to_lay<double, double>(H->stream, A.lay, phi_cur, A.phk, 1);
+    }
     H->f1_phk = true;  // f.a and phk now hold the same phi^k
     restrict_phk(H);
     if (mobility_on(H)) {
@@ -572,7 +576,10 @@ void step_begin(pfc_handle *H, const double *phi_prev, const double *phi_cur, co
     }
 }
 void step_end(pfc_handle *H, double *phi_next, double *mu, double *omega) {
-    from_level0(H, phi_next, mu, omega);
+    if (H->lev[0].lay.split)
+        launch_step_end(H->stream, H->lev[0].lay, H->lev[0].u, phi_next, mu, omega);
+    else
+        from_level0(H, phi_next, mu, omega);
 }
 }  // namespace pfc
 
