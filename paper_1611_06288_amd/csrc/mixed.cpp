@@ -41,14 +41,14 @@ constexpr double kFloorQ = 0.5;
 pfc_status mixed_init(pfc_handle *H) {
     if (hipEventCreateWithFlags(&H->norm_ev, hipEventDisableTiming) != hipSuccess)
         return fail(H, PFC_ERR_HIP, "event creation failed");
-    const int slots = pair_slots(H->device, true);
+    const int slots = pair_slots(H->device, PAIR_FP32);
     for (int l = 0; l < H->nlev; ++l) {
         Level32 &A = H->lev32[l];
         // a pair leaves the iterate in the other buffer, a cycle (recorded
         // once) must not: an even number of pairs per visit
         const int pairs = H->cfg.nu1 / 2 + H->cfg.nu2 / 2;
         A.pair = pair_fits(H->lev[l].n, true) && pairs > 0 && (pairs & 1) == 0;
-        A.pnz = pair_nz(H->lev[l].n, slots);
+        A.pnz = pair_nz(H->lev[l].n, slots, PAIR_FP32);
         const size_t P = H->lev[l].P;
         float *e, *f, *eb;
         const bool ok = dalloc(H, &e, 3 * P) && dalloc(H, &f, 3 * P) && dalloc(H, &eb, 3 * P) &&

@@ -134,7 +134,7 @@ struct PairArgs {
 };
 
 // Two full red-black sweeps in one pass (sweep_pair.h), bitwise two fused sweeps;
-// arguments as launch_sweep_fused, M = 1 only.  The level is cut into pair_nz
+// arguments as launch_sweep_fused.  The level is cut into pair_nz
 // plane ranges.
 void launch_sweep_pair64(hipStream_t s, const OpParams &op, int picard, int nz, Tri<const double> uin,
                          Tri<double> uout, Tri<const double> f, const double *phk, int nrm = 0,
@@ -142,9 +142,10 @@ void launch_sweep_pair64(hipStream_t s, const OpParams &op, int picard, int nz, 
 void launch_sweep_pair32(hipStream_t s, const OpParams &op, int nz, Tri<const float> ein, Tri<float> eout,
                          Tri<const float> f, const float *phk, const float *base, bool skip0 = false);
 bool pair_fits(int n, bool fp32);
-int pair_slots(int device, bool fp32);  // resident workgroups on the device (0 on error)
-int pair_nz(int n, int slots);
-int pair_blocks(int n, int nz);  // workgroups of one launch
+enum { PAIR_FP64 = 0, PAIR_FP32 = 1, PAIR_MOB = 2 };  // forms
+int pair_slots(int device, int form);  // resident workgroups on the device (0 on error)
+int pair_nz(int n, int slots, int form);
+int pair_blocks(int n, int nz, int form);  // workgroups of one launch
 // Smallest levels: FP64 at 128^3 two fused sweeps 54-57 us, the pair 50; an FP32
 // step of 24 cycles at 128^3 in half-sweeps 5.63 ms, in pairs 5.93, at 192^3 13.8 and
 // 14.1 (its operands sit in the last-level cache), at 256^3 29.9 and 26.0.

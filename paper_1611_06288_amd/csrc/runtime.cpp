@@ -622,7 +622,7 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
     if (hipGetDevice(&device) != hipSuccess) device = 0;
     const bool mob = cfg->mobility == PFC_MOBILITY_QUADRATIC;
     const int slots = fused_slots(device, mob);
-    const int p_slots = pair_slots(device, false);
+    const int p_form = mob ? PAIR_MOB : PAIR_FP64, p_slots = pair_slots(device, p_form);
     int rt_slots[RT_MODES];
     for (int m = 0; m < RT_MODES; ++m) rt_slots[m] = resid_tile_slots(device, m, mob);
     const int pt_slots[2] = {prolong_tile_slots(device, false), prolong_tile_slots(device, true)};
@@ -649,9 +649,9 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
         A.fused = l < H->nlev - 1 && fused_fits(A.n);
         // (a cycle recorded as a graph needs an even number of launches, each of
         // which exchanges the iterate buffers: pairs must not make it odd)
-        A.pair = A.fused && !mob && pair_fits(A.n, false);
+        A.pair = A.fused && pair_fits(A.n, false);
         A.pair = A.pair && ((sweep_launches(H, l) & 1) == 0 || ((cfg->nu1 + cfg->nu2) & 1));
-        A.pnz = pair_nz(A.n, p_slots);
+        A.pnz = pair_nz(A.n, p_slots, p_form);
         const bool sweeps = cfg->nu1 >= 1 && cfg->nu1 <= kBrickMaxSweeps && cfg->nu2 >= 1 &&
                             cfg->nu2 <= kBrickMaxSweeps;
         A.brick = l < H->nlev - 1 && sweeps && brick_size(A.n);
@@ -680,7 +680,7 @@ pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
     if (ok) {  // the split stop test (the graph loop seeds it behind both halves)
         const Level &A = H->lev[0];
         const int one = A.fused ? fused_blocks(A.n, A.nz) : 0;
-        const int two = A.pair ? pair_blocks(A.n, A.pnz) : 0;
+        const int two = A.pair ? pair_blocks(A.n, A.pnz, p_form) : 0;
         H->split_pre = ahead_sweeps(H) == 2 ? two : one;
         H->split_post = A.pair && cfg->nu2 >= 2 && (cfg->nu2 & 1) == 0 ? two : one;
         H->split_norm = A.fused && cfg->nu1 >= 1 && cfg->nu2 >= 1 && cfg->precision == PFC_FP64 &&

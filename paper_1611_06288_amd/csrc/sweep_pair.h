@@ -32,6 +32,12 @@
 // FP32 pair is bound by its FP64 arithmetic (VALU 68% busy), so its LDS planes hold
 // the rounded values as FP64, converted once by their writer and not by each
 // reader (259 -> 252 us; the LDS has the room).
+//
+// Variable mobility: phi* rides along as a fourth field (read only) and the mu sum
+// becomes the face-mobility sum of the flux form.  Four fields of the wide box do
+// not fit the LDS, so its box is 32 x 16 (103 KB, one workgroup of eight waves per
+// CU, 144-160 VGPRs).  Two fused sweeps -> this: 256^3 654 -> 484 us, 192^3 367 ->
+// 242, 128^3 84 -> 76.
 #pragma once
 
 #include "device_common.h"
@@ -78,7 +84,9 @@ struct PairGeo {
         static constexpr int W = kW - 2 * X, R = kR - 2 * Y;
         static constexpr int N = W * R;  // of one field and plane
     };
-    static constexpr int kLds = 6 * (Buf<0>::N + Buf<1>::N + Buf<2>::N + Buf<3>::N);
+    static constexpr int lds(int fields) {  // doubles
+        return 2 * fields * (Buf<0>::N + Buf<1>::N + Buf<2>::N + Buf<3>::N);
+    }
 };
 using PairWide = PairGeo<64, 16, 896>;   // one workgroup per CU
 using PairSmall = PairGeo<32, 16, 512>;  // two
@@ -87,25 +95,23 @@ template <typename G>
 __device__ constexpr typename G::List kPairList = G::list();
 
 // One buffer as a thread sees it: its own slot and its neighbours'.
-template <typename P>
+template <typename P, int NF>
 struct PairSlot {
     double *q;  // own x-pair, field 0, plane slot 0
-    __device__ __forceinline__ double *at(int slot) const { return q + slot * 3 * P::N; }
-    __device__ __forceinline__ void put(int slot, const double (&v)[3]) const {
+    __device__ __forceinline__ double *at(int slot) const { return q + slot * NF * P::N; }
+    __device__ __forceinline__ void put(int slot, const double (&v)[NF]) const {
         double *w = at(slot);
-        w[0] = v[0];
-        w[P::N] = v[1];
-        w[2 * P::N] = v[2];
+#pragma unroll
+        for (int fl = 0; fl < NF; ++fl) w[fl * P::N] = v[fl];
     }
-    __device__ __forceinline__ void get(int slot, double (&v)[3]) const {
+    __device__ __forceinline__ void get(int slot, double (&v)[NF]) const {
         const double *w = at(slot);
-        v[0] = w[0];
-        v[1] = w[P::N];
-        v[2] = w[2 * P::N];
+#pragma unroll
+        for (int fl = 0; fl < NF; ++fl) v[fl] = w[fl * P::N];
     }
     // neighbour sums of the three fields: x and y from the plane in `slot`, z
     // given; s: x parity of the point
-    __device__ __forceinline__ void sums(int slot, int s, const double (&zp)[3], const double (&zm)[3],
+    __device__ __forceinline__ void sums(int slot, int s, const double (&zp)[NF], const double (&zm)[NF],
                                          double (&out)[3]) const {
         const double *w = at(slot);
         const double *wx = w + (s ? 1 : -1);
@@ -115,6 +121,24 @@ struct PairSlot {
                       (w[fl * P::N + P::W] + w[fl * P::N - P::W]) +
                       (zp[fl] + zm[fl]);
     }
+    // mobilities of the point's faces xp, xm, yp, ym, zp, zm (phi*: field 3; own
+    // value pc) and mu beyond them
+    __device__ __forceinline__ void faces(int slot, int s, const double (&zp)[NF], const double (&zm)[NF],
+                                          const Mobility &mob, double pc, double (&mf)[6],
+                                          double (&mu)[6]) const {
+        const double *w = at(slot) + P::N;  // mu
+        const double *xp = w + (s ? 1 : 0), *xm = w + (s ? 0 : -1);
+        constexpr int ph = (NF - 2) * P::N;  // from mu to phi*
+        const double p[6] = {xp[ph], xm[ph], w[ph + P::W], w[ph - P::W], zp[NF - 1], zm[NF - 1]};
+        mu[0] = xp[0];
+        mu[1] = xm[0];
+        mu[2] = w[P::W];
+        mu[3] = w[-P::W];
+        mu[4] = zp[1];
+        mu[5] = zm[1];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) mf[e] = face_mob(mob, pc, p[e]);
+    }
 };
 
 // NRM: as the fused sweep's, half of the stop-test norm: 1 over the colour-0 points of the input (formed with the
@@ -122,9 +146,11 @@ struct PairSlot {
 // (with the last one's).  PK1: f.a is phi^k itself, loaded once.
 // One workgroup's column: the box at (x0, y0), px points wide (the whole box or
 // its left part), planes [z0, z1).  Returns the thread's share of the norm.
-template <typename G, typename T, bool DELTA, int NRM, bool PK1>
+template <typename G, typename T, bool DELTA, bool MOB, int NRM, bool PK1>
 __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, int x0, int y0, int px,
                                                           int z0, int z1, double *lds) {
+    static_assert(!(MOB && DELTA), "M = 1 in the FP32 cycle");
+    constexpr int NF = MOB ? 4 : 3;  // phi, mu, omega (, phi*: rides along unchanged)
     constexpr int NI = (PK1 ? 3 : 4) + (DELTA ? 1 : 0);  // phi^k, f2, f3 (, f1) (, base)
     const int n = a.op.lay.n, hn = n >> 1;
     const unsigned un = (unsigned)n, uhn = (unsigned)hn, plane = un * uhn, H = un * plane;
@@ -150,22 +176,23 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
     using B1 = typename G::template Buf<1>;
     using B2 = typename G::template Buf<2>;
     using B3 = typename G::template Buf<3>;
-    double *const l0 = lds, *const l1 = l0 + 6 * B0::N, *const l2 = l1 + 6 * B1::N, *const l3 = l2 + 6 * B2::N;
+    double *const l0 = lds, *const l1 = l0 + 2 * NF * B0::N, *const l2 = l1 + 2 * NF * B1::N,
+            *const l3 = l2 + 2 * NF * B2::N;
     // A thread whose pair lies outside a buffer never touches it: clamp its slot
     auto own = [&](auto buf, double *l) {
         using P = decltype(buf);
         const int r = min(max(row - P::Y, 0), P::R - 1), c = min(max(mx - P::X, 0), P::W - 1);
         return l + r * P::W + c;
     };
-    const PairSlot<B0> o1{own(B0{}, l0)};  // old colour 1
-    const PairSlot<B1> a0{own(B1{}, l1)};  // first sweep
-    const PairSlot<B2> a1{own(B2{}, l2)};
-    const PairSlot<B3> b0{own(B3{}, l3)};  // second sweep, colour 0
+    const PairSlot<B0, NF> o1{own(B0{}, l0)};  // old colour 1
+    const PairSlot<B1, NF> a0{own(B1{}, l1)};  // first sweep
+    const PairSlot<B2, NF> a1{own(B2{}, l2)};
+    const PairSlot<B3, NF> b0{own(B3{}, l3)};  // second sweep, colour 0
 
     PointCoef co(a.op);
     co.to_scalar();
-    T c1n[3];              // old colour 1 of the next plane
-    T phin[3];             // old phi (NRM = 1: mu, omega) of the next colour-0 point
+    T c1n[NF];             // old colour 1 of the next plane
+    T phin[NF];            // old phi (NRM = 1: mu, omega; phi*) of the next colour-0 point
     T in0[4][NI], in1[4][NI];  // inputs of colour 0 at planes p, p-1 .. p-3, of colour 1 a plane lower
     auto load_in = [&](int c, int q, T (&v)[NI]) {
         const unsigned g = gidx(c, q);
@@ -181,6 +208,7 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
             c1n[0] = a.u.a[g];
             c1n[1] = a.u.b[g];
             c1n[2] = a.u.c[g];
+            if constexpr (MOB) c1n[3] = a.op.mob.phs[g];
         }
     };
     auto load_points = [&](int p) {  // what step p + 1 relaxes first: colour 0 of p, colour 1 of p - 1
@@ -188,6 +216,7 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
         if (d <= 3) {
             const unsigned g = gidx(0, p);
             phin[0] = a.u.a[g];
+            if constexpr (MOB) phin[3] = a.op.mob.phs[g];
             if (NRM == 1 && d == 0) {
                 phin[1] = a.u.b[g];
                 phin[2] = a.u.c[g];
@@ -196,26 +225,52 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
         }
         if (dist(1, p - 1) <= 2) load_in(1, p - 1, in1[0]);
     };
-    auto solve = [&](double ph, const T (&v)[NI], const double (&s)[3], double (&o)[3]) {
-        double x, y2, w;
-        point_solve<DELTA>(co, a.picard, ph, (double)v[0], DELTA ? (double)v[NI - 1] : 0.0,
-                           (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], s[1], s[2], s[0], x,
-                           y2, w);
+    // one point of a half-sweep: old phi ph, inputs v, neighbours in the plane `slot`
+    // of buf and zp, zm, own phi* pc; before and after see the sums and faces
+    auto relax = [&](const auto &buf, int slot, int s, const double (&zp)[NF], const double (&zm)[NF],
+                     double ph, double pc, const T (&v)[NI], double (&o)[NF], auto &&before, auto &&after) {
+        double sm[3], mf[6], mu[6], x, y2, w;
+        buf.sums(slot, s, zp, zm, sm);
+        if constexpr (MOB) buf.faces(slot, s, zp, zm, a.op.mob, pc, mf, mu);
+        before(sm, mf, mu);
+        if constexpr (MOB) {
+            double msum = 0.0, smm = 0.0;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                msum += mf[e];
+                smm += mf[e] * mu[e];
+            }
+            point_solve_mob(a.op, a.picard, ph, (double)v[0], (double)(PK1 ? v[0] : v[3]), (double)v[1],
+                            (double)v[2], msum, smm, sm[2], sm[0], x, y2, w);
+            o[NF - 1] = pc;
+        } else {
+            point_solve<DELTA>(co, a.picard, ph, (double)v[0], DELTA ? (double)v[NI - 1] : 0.0,
+                               (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], sm[1], sm[2],
+                               sm[0], x, y2, w);
+        }
         o[0] = (T)x;  // rounded to the level's type
         o[1] = (T)y2;
         o[2] = (T)w;
+        after(sm, mf, mu);
     };
+    auto none = [](const double (&)[3], const double (&)[6], const double (&)[6]) {};
     unsigned long long nrm = 0;
-    auto norm = [&](const double (&w)[3], const T (&v)[NI], const double (&s)[3]) {
+    auto norm = [&](const double (&w)[NF], const T (&v)[NI], const double (&s)[3], const double (&mf)[6],
+                    const double (&mu)[6]) {
         const double h2inv = a.op.h2inv;
-        const double ls[3] = {(s[0] - 6.0 * w[0]) * h2inv, (s[1] - 6.0 * w[1]) * h2inv,
-                              (s[2] - 6.0 * w[2]) * h2inv};
+        double ls[3] = {(s[0] - 6.0 * w[0]) * h2inv, (s[1] - 6.0 * w[1]) * h2inv, (s[2] - 6.0 * w[2]) * h2inv};
+        if constexpr (MOB) {  // flux form
+            double f6 = 0.0;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) f6 += mf[e] * (mu[e] - w[1]);
+            ls[1] = f6 * h2inv;
+        }
         double r[3];
         resid_from_lap<false>(a.op, ls, w[0], w[1], w[2],
                               (double)(PK1 ? v[0] : v[3]), (double)v[1], (double)v[2], (double)v[0], 0.0, r);
         nrm = umax(nrm, umax(abs_bits(r[0]), umax(abs_bits(r[1]), abs_bits(r[2]))));
     };
-    auto store = [&](int c, int q, const double (&v)[3], bool all) {
+    auto store = [&](int c, int q, const double (&v)[NF], bool all) {
         const unsigned g = gidx(c, q);
         if (a.stream) {
             __builtin_nontemporal_store((T)v[0], &a.o.a[g]);
@@ -236,12 +291,13 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
     for (int p = z0 - 4; p <= z1 + 3; ++p) {
         const int k = p & 1;  // LDS slot of planes p, p-2, p-4
         // a value's lower z-neighbour is taken from the slot it replaces
-        double c1[3], lo[3], v[3], w[3], w0[3] = {phin[0], phin[1], phin[2]};
+        double c1[NF], lo[NF], v[NF], w[NF], w0[NF];
+#pragma unroll
+        for (int fl = 0; fl < NF; ++fl) w0[fl] = phin[fl];
         o1.get(k, lo);  // old colour 1, plane p-2
         if (dist(1, p) <= 4) {
-            c1[0] = c1n[0];
-            c1[1] = c1n[1];
-            c1[2] = c1n[2];
+#pragma unroll
+            for (int fl = 0; fl < NF; ++fl) c1[fl] = c1n[fl];
             o1.put(k, c1);
         }
 #pragma unroll
@@ -254,38 +310,33 @@ __device__ __forceinline__ unsigned long long pair_column(const PairArgs<T> &a, 
         load_c1(p + 1);
         load_points(p);
         const int da = dist(0, p - 1), db = dist(1, p - 2), dc = dist(0, p - 3), dd = dist(1, p - 4);
-        const double oldb = lo[0];  // old phi of plane p-2
-        if (da <= 3) {
-            double s[3];
-            o1.sums(k ^ 1, parity(0, p - 1), c1, lo, s);
-            if constexpr (NRM == 1)
-                if (da == 0) norm(w0, in0[1], s);
-            solve(w0[0], in0[1], s, v);
-        }
+        double old = lo[0], own = lo[NF - 1];  // old phi (MOB: phi*) of the next half-sweep's point
+        if (da <= 3)
+            relax(o1, k ^ 1, parity(0, p - 1), c1, lo, w0[0], w0[NF - 1], in0[1], v,
+                  [&](const double (&s)[3], const double (&mf)[6], const double (&mu)[6]) {
+                      if constexpr (NRM == 1)
+                          if (da == 0) norm(w0, in0[1], s, mf, mu);
+                  }, none);
         a0.get(k ^ 1, lo);  // colour 0, plane p-3
         if (da <= 3) a0.put(k ^ 1, v);
-        const double oldc = lo[0];
-        if (db <= 2) {
-            double s[3];
-            a0.sums(k, parity(1, p - 2), v, lo, s);
-            solve(oldb, in1[1], s, w);
-        }
+        if (db <= 2) relax(a0, k, parity(1, p - 2), v, lo, old, own, in1[1], w, none, none);
+        old = lo[0];
+        own = lo[NF - 1];
         a1.get(k, lo);  // colour 1, plane p-4
         if (db <= 2) a1.put(k, w);
-        const double oldd = lo[0];
         if (dc <= 1) {
-            double s[3];
-            a1.sums(k ^ 1, parity(0, p - 3), w, lo, s);
-            solve(oldc, in0[3], s, v);
+            relax(a1, k ^ 1, parity(0, p - 3), w, lo, old, own, in0[3], v, none, none);
             if (dc == 0) store(0, p - 3, v, !a.skip0);
         }
+        old = lo[0];
+        own = lo[NF - 1];
         b0.get(k ^ 1, lo);  // second colour 0, plane p-5
         if (dc <= 1) b0.put(k ^ 1, v);
         if (dd <= 0) {
-            double s[3];
-            b0.sums(k, parity(1, p - 4), v, lo, s);
-            solve(oldd, in1[3], s, w);
-            if constexpr (NRM == 2) norm(w, in1[3], s);
+            relax(b0, k, parity(1, p - 4), v, lo, old, own, in1[3], w, none,
+                  [&](const double (&s)[3], const double (&mf)[6], const double (&mu)[6]) {
+                      if constexpr (NRM == 2) norm(w, in1[3], s, mf, mu);
+                  });
             store(1, p - 4, w, true);
         }
         __syncthreads();

@@ -2,18 +2,18 @@
 #include "sweep_pair.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace pfc {
 
-template <typename T, bool DELTA, int NRM, bool PK1>
-__global__ __launch_bounds__(PairWide::kThreads, 4) void k_sweep_pair(PairArgs<T> a) {
-    using G = PairWide;
-    __shared__ double lds[G::kLds];
+template <typename G, typename T, bool DELTA, bool MOB, int NRM, bool PK1>
+__global__ __launch_bounds__(G::kThreads, MOB ? 2 : 4) void k_sweep_pair(PairArgs<T> a) {
+    __shared__ double lds[G::lds(MOB ? 4 : 3)];
     __shared__ unsigned long long wmax[G::kThreads / 64];
     if (gate_closed(a.op.gate)) return;
     const int n = a.op.lay.n, nbx = n / G::kX, nby = n / G::kY;
     const int b = (int)xcd_block(), bz = b / (nbx * nby);
-    unsigned long long nrm = pair_column<G, T, DELTA, NRM, PK1>(
+    unsigned long long nrm = pair_column<G, T, DELTA, MOB, NRM, PK1>(
         a, b % nbx * G::kX, b / nbx % nby * G::kY, G::kX, bz * n / a.nz, (bz + 1) * n / a.nz, lds);
     if constexpr (NRM != 0) {
         nrm = block_max_u64_waves(nrm, wmax);
@@ -34,21 +34,28 @@ static int pair_stream(int n) {
     return 9.0 * sizeof(T) * n * n * n > 256e6;
 }
 
-int pair_slots(int device, bool fp32) {
+int pair_slots(int device, int form) {
     int occ = 0, cus = 0;
-    const void *fn = fp32 ? (const void *)k_sweep_pair<float, true, 0, false>
-                          : (const void *)k_sweep_pair<double, false, 0, true>;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, PairWide::kThreads, 0) != hipSuccess ||
+    const void *fn = form == PAIR_FP32 ? (const void *)k_sweep_pair<PairWide, float, true, false, 0, false>
+                     : form == PAIR_MOB
+                         ? (const void *)k_sweep_pair<PairSmall, double, false, true, 0, true>
+                         : (const void *)k_sweep_pair<PairWide, double, false, false, 0, true>;
+    const int th = form == PAIR_MOB ? PairSmall::kThreads : PairWide::kThreads;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, th, 0) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
         return 0;
     return occ * cus;
 }
 
+static int pair_cols(int n, int form) {
+    return form == PAIR_MOB ? (n / PairSmall::kX) * (n / PairSmall::kY) : (n / PairWide::kX) * (n / PairWide::kY);
+}
+
 // Plane ranges per column: the fewest waves of resident workgroups times the
 // steps of one, a range's eight halo planes counted as five (the points in them
 // thin out).
-int pair_nz(int n, int slots) {
-    const int cols = (n / PairWide::kX) * (n / PairWide::kY);
+int pair_nz(int n, int slots, int form) {
+    const int cols = pair_cols(n, form);
     int best = 1;
     long cost = -1;
     for (int nz = 1; nz <= n / 4; ++nz) {
@@ -62,29 +69,40 @@ int pair_nz(int n, int slots) {
     return best;
 }
 
-int pair_blocks(int n, int nz) { return (n / PairWide::kX) * (n / PairWide::kY) * nz; }
+int pair_blocks(int n, int nz, int form) { return pair_cols(n, form) * nz; }
 
 
 void launch_sweep_pair64(hipStream_t s, const OpParams &op, int picard, int nz, Tri<const double> uin,
                          Tri<double> uout, Tri<const double> f, const double *phk, int nrm,
                          unsigned long long *part, bool skip0) {
     PairArgs<double> a{op, picard, nz, skip0 ? 1 : 0, pair_stream<double>(op.lay.n), uin, f, uout, phk, nullptr, part};
-    const dim3 grid((unsigned)pair_blocks(op.lay.n, nz));
-    // the norm halves belong to a time step's finest level, whose f.a is phk
-    if (f.a != phk)
-        hipLaunchKernelGGL((k_sweep_pair<double, false, 0, false>), grid, dim3(PairWide::kThreads), 0, s, a);
-    else if (nrm == 1)
-        hipLaunchKernelGGL((k_sweep_pair<double, false, 1, true>), grid, dim3(PairWide::kThreads), 0, s, a);
-    else if (nrm == 2)
-        hipLaunchKernelGGL((k_sweep_pair<double, false, 2, true>), grid, dim3(PairWide::kThreads), 0, s, a);
+    const bool mob = op.mob.phs != nullptr;
+    const dim3 grid((unsigned)pair_blocks(op.lay.n, nz, mob ? PAIR_MOB : PAIR_FP64));
+    auto go = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a); };
+    auto forms = [&](auto geo, auto m) {
+        using G = decltype(geo);
+        constexpr bool M = decltype(m)::value;
+        // the norm halves belong to a time step's finest level, whose f.a is phk
+        if (f.a != phk)
+            go(k_sweep_pair<G, double, false, M, 0, false>, G::kThreads);
+        else if (nrm == 1)
+            go(k_sweep_pair<G, double, false, M, 1, true>, G::kThreads);
+        else if (nrm == 2)
+            go(k_sweep_pair<G, double, false, M, 2, true>, G::kThreads);
+        else
+            go(k_sweep_pair<G, double, false, M, 0, true>, G::kThreads);
+    };
+    if (mob)
+        forms(PairSmall{}, std::true_type{});
     else
-        hipLaunchKernelGGL((k_sweep_pair<double, false, 0, true>), grid, dim3(PairWide::kThreads), 0, s, a);
+        forms(PairWide{}, std::false_type{});
 }
 
 void launch_sweep_pair32(hipStream_t s, const OpParams &op, int nz, Tri<const float> ein, Tri<float> eout,
                          Tri<const float> f, const float *phk, const float *base, bool skip0) {
     PairArgs<float> a{op, 0, nz, skip0 ? 1 : 0, pair_stream<float>(op.lay.n), ein, f, eout, phk, base, nullptr};
-    hipLaunchKernelGGL((k_sweep_pair<float, true, 0, false>), dim3((unsigned)pair_blocks(op.lay.n, nz)),
+    hipLaunchKernelGGL((k_sweep_pair<PairWide, float, true, false, 0, false>),
+                       dim3((unsigned)pair_blocks(op.lay.n, nz, PAIR_FP32)),
                        dim3(PairWide::kThreads), 0, s, a);
 }
 
@@ -95,12 +113,12 @@ __global__ __launch_bounds__(PairSmall::kThreads, 4) void kb_sweep_pair(
     const PairArgs<double> *__restrict__ segs, const PairTile *__restrict__ tiles,
     unsigned long long *__restrict__ part) {
     using G = PairSmall;
-    __shared__ double lds[G::kLds];
+    __shared__ double lds[G::lds(3)];
     __shared__ unsigned long long wmax[G::kThreads / 64];
     const PairTile t = tiles[blockIdx.x];
     const PairArgs<double> a = segs[t.seg];
     if (gate_closed(a.op.gate)) return;
-    unsigned long long nrm = pair_column<G, double, false, NRM, true>(a, t.x0, t.y0, t.px, t.z0, t.z1, lds);
+    unsigned long long nrm = pair_column<G, double, false, false, NRM, true>(a, t.x0, t.y0, t.px, t.z0, t.z1, lds);
     nrm = block_max_u64_waves(nrm, wmax);
     if (threadIdx.x == 0) part[t.slot] = nrm;
 }

@@ -1,4 +1,4 @@
-"""Two red-black sweeps in one launch (levels of at least 128^3, M = 1).
+"""Two red-black sweeps in one launch (levels of at least 128^3).
 
 A V-cycle is compared with the cycle put together from the kernel-level entry
 points, whose full sweeps are one launch each: the kernels share every point's
@@ -23,11 +23,14 @@ from test_gpu_brick import cycle_by_parts
 
 pytestmark = pytest.mark.gpu
 
+MOB = (1.0, 0.0, -1.0, 0.05)
+
 
 @pytest.mark.parametrize("n,nu,kw", [(128, (2, 2), {}), (192, (2, 2), {}), (128, (2, 1), {}),
                                      (128, (3, 3), {}), (128, (2, 2), dict(lin="picard")),
                                      (192, (2, 2), dict(scheme=1)), (256, (2, 2), {}),
-                                     (256, (3, 4), {})])
+                                     (256, (3, 4), {}), (128, (2, 2), dict(mobility=MOB)),
+                                     (192, (2, 2), dict(mobility=MOB)), (256, (2, 2), dict(mobility=MOB))])
 def test_cycle_equals_kernel_level_cycle(n, nu, kw):
     s = Solver(n, n * math.pi / 4, 0.25, 0.5, nu1=nu[0], nu2=nu[1], **kw)
     g = inputs.rng(300 + n)
@@ -35,6 +38,8 @@ def test_cycle_equals_kernel_level_cycle(n, nu, kw):
     phk, prev = 0.285 + 0.1 * rnd(n, n, n), 0.285 + 0.1 * rnd(n, n, n)
     f = s.source(prev, phk) + 0.01 * rnd(3, n, n, n)  # no structure between f and phi^k
     u = (torch.stack([phk, *s.init_guess(phk)]) + 0.05 * rnd(3, n, n, n)).contiguous()
+    if "mobility" in kw:
+        s.set_phistar(0, 1.5 * phk - 0.5 * prev)
     ref = u.clone()
     cycle_by_parts(s, ref, f, phk, nu)
     s.reset_coarse_cache()  # as the kernel-level coarsest solve
