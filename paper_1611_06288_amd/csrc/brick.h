@@ -19,7 +19,8 @@
 // then every field at once: 5000-7000 cycles), the stages of 1100-1700 cycles
 // each between barriers, and on 64^3 and 96^3 the halo's arithmetic as well.
 // Up to 32^3 that chain is what counts: 4^3 boxes, both sweeps of a side in one
-// launch.  From 48^3 on the halo of two sweeps costs more than a launch (8^3
+// launch; 8 x 4 x 4 at 32^3, where 4^3 boxes are two per CU and share its cycles
+// (a 32^3 cycle 69 -> 62.5 us, 64^3 117 -> 110).  From 48^3 on the halo of two sweeps costs more than a launch (8^3
 // boxes with both sweeps: 57 us per cycle at 64^3, one sweep per launch 45).
 // Measured per V(2,2) cycle, kernel time (before -> now): 64^3 finest with its
 // stop-test norm 60 -> 45 us in 11 -> 4 launches, 32^3 43 -> 22, 16^3 39 -> 16;
@@ -566,57 +567,67 @@ k_brick_sweep(BrickArgs<T> a) {
 }
 
 // Launch of one kernel's form: plain, the first of a coarse level, with the norm.
-template <bool PRE, typename T, int PH, bool DELTA, bool MOB, int B, int S, bool TAU, bool NRM, bool ZERO>
+template <typename Box, bool PRE, typename T, int PH, bool DELTA, bool MOB, int S, bool TAU, bool NRM, bool ZERO>
 static void brick_go(hipStream_t s, const BrickArgs<T> &a) {
-    const int m = a.op.lay.n / B;
-    const dim3 grid((unsigned)(m * m * m));
+    const dim3 grid(Box::blocks(a.op.lay.n));
     if constexpr (PRE) {
-        using K = BrickPre<T, PH, DELTA, MOB, B, B, B, S, TAU, NRM, ZERO>;
-        hipLaunchKernelGGL((k_brick_pre<T, PH, DELTA, MOB, B, B, B, S, TAU, NRM, ZERO>), grid, dim3(K::TH),
-                           0, s, a);
-    } else {
-        using K = BrickSweep<T, PH, DELTA, MOB, B, B, B, S, false, TAU, NRM, ZERO>;
-        hipLaunchKernelGGL((k_brick_sweep<T, PH, DELTA, MOB, B, B, B, S, false, TAU, NRM, ZERO>), grid,
+        using K = BrickPre<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, TAU, NRM, ZERO>;
+        hipLaunchKernelGGL((k_brick_pre<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, TAU, NRM, ZERO>), grid,
                            dim3(K::TH), 0, s, a);
+    } else {
+        using K = BrickSweep<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, false, TAU, NRM, ZERO>;
+        hipLaunchKernelGGL((k_brick_sweep<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, false, TAU, NRM, ZERO>),
+                           grid, dim3(K::TH), 0, s, a);
     }
 }
 
-template <bool PRE, typename T, int PH, bool DELTA, bool MOB, int B, int S>
+template <typename Box, bool PRE, typename T, int PH, bool DELTA, bool MOB, int S>
 static void brick_form(hipStream_t s, const BrickArgs<T> &a, int form) {
     if (form == BRICK_FIRST)
-        return brick_go<PRE, T, PH, DELTA, MOB, B, S, PH != BP_ADJ, false, PH == BP_ADJ>(s, a);
+        return brick_go<Box, PRE, T, PH, DELTA, MOB, S, PH != BP_ADJ, false, PH == BP_ADJ>(s, a);
     if constexpr (!DELTA) {
-        if (form == BRICK_NORM) return brick_go<PRE, T, PH, DELTA, MOB, B, S, false, true, false>(s, a);
+        if (form == BRICK_NORM) return brick_go<Box, PRE, T, PH, DELTA, MOB, S, false, true, false>(s, a);
     }
-    brick_go<PRE, T, PH, DELTA, MOB, B, S, false, false, false>(s, a);
+    brick_go<Box, PRE, T, PH, DELTA, MOB, S, false, false, false>(s, a);
 }
 
-template <typename T, int PH, bool DELTA, bool MOB, int B, int S>
+template <typename Box, typename T, int PH, bool DELTA, bool MOB, int S>
 static void brick_post(hipStream_t s, const BrickArgs<T> &a) {
-    const int m = a.op.lay.n / B;
-    using K = BrickSweep<T, PH, DELTA, MOB, B, B, B, S, true, false, false, false>;
-    hipLaunchKernelGGL((k_brick_sweep<T, PH, DELTA, MOB, B, B, B, S, true, false, false, false>),
-                       dim3((unsigned)(m * m * m)), dim3(K::TH), 0, s, a);
+    using K = BrickSweep<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, true, false, false, false>;
+    hipLaunchKernelGGL((k_brick_sweep<T, PH, DELTA, MOB, Box::X, Box::Y, Box::Z, S, true, false, false, false>),
+                       dim3(Box::blocks(a.op.lay.n)), dim3(K::TH), 0, s, a);
 }
 
-// The launches of one operator: 4^3 boxes with one or two sweeps per launch,
-// 8^3 boxes with one.
+// The launches of one operator with boxes that take up to two sweeps per launch ...
+template <typename Box, typename T, int PH, bool DELTA, bool MOB>
+static void brick_two(hipStream_t s, const BrickArgs<T> &a, int kind, int sweeps, int form) {
+    if (kind == BRICK_POST)
+        sweeps == 1 ? brick_post<Box, T, PH, DELTA, MOB, 1>(s, a) : brick_post<Box, T, PH, DELTA, MOB, 2>(s, a);
+    else
+        sweeps == 1 ? brick_form<Box, true, T, PH, DELTA, MOB, 1>(s, a, form)
+                    : brick_form<Box, true, T, PH, DELTA, MOB, 2>(s, a, form);
+}
+
+// ... and with boxes that take one.
+template <typename Box, typename T, int PH, bool DELTA, bool MOB>
+static void brick_one(hipStream_t s, const BrickArgs<T> &a, int kind, int form) {
+    if (kind == BRICK_POST)
+        brick_post<Box, T, PH, DELTA, MOB, 1>(s, a);
+    else if (kind == BRICK_SWEEP)
+        brick_form<Box, false, T, PH, DELTA, MOB, 1>(s, a, form);
+    else
+        brick_form<Box, true, T, PH, DELTA, MOB, 1>(s, a, form);
+}
+
 template <typename T, int PH, bool DELTA, bool MOB>
 static void brick_launch(hipStream_t s, const BrickArgs<T> &a, int kind, int sweeps, int form) {
-    if (brick_small(a.op.lay.n)) {
-        if (kind == BRICK_POST)
-            sweeps == 1 ? brick_post<T, PH, DELTA, MOB, 4, 1>(s, a) : brick_post<T, PH, DELTA, MOB, 4, 2>(s, a);
-        else
-            sweeps == 1 ? brick_form<true, T, PH, DELTA, MOB, 4, 1>(s, a, form)
-                        : brick_form<true, T, PH, DELTA, MOB, 4, 2>(s, a, form);
-        return;
-    }
-    if (kind == BRICK_POST)
-        brick_post<T, PH, DELTA, MOB, 8, 1>(s, a);
-    else if (kind == BRICK_SWEEP)
-        brick_form<false, T, PH, DELTA, MOB, 8, 1>(s, a, form);
+    const int n = a.op.lay.n;
+    if (n == kBrickPairN)
+        brick_two<BrickBox<8, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
+    else if (brick_small(n))
+        brick_two<BrickBox<4, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
     else
-        brick_form<true, T, PH, DELTA, MOB, 8, 1>(s, a, form);
+        brick_one<BrickBox<8, 8, 8>, T, PH, DELTA, MOB>(s, a, kind, form);
 }
 
 }  // namespace pfc

@@ -177,9 +177,16 @@ struct BrickArgs {
 inline bool brick_small(int n) { return n <= 32; }
 inline bool brick_size(int n) { return n >= 12 && n <= 96 && n % (brick_small(n) ? 4 : 8) == 0; }
 constexpr int kBrickMaxSweeps = 2;  // sweeps per side of the descent
+template <int BX, int BY, int BZ>
+struct BrickBox {
+    static constexpr int X = BX, Y = BY, Z = BZ;
+    static int blocks(int n) { return (n / BX) * (n / BY) * (n / BZ); }
+};
+constexpr int kBrickPairN = 32;  // 8 x 4 x 4 boxes: one per CU
 inline int brick_blocks(int n) {
-    const int m = n / (brick_small(n) ? 4 : 8);
-    return m * m * m;
+    return n == kBrickPairN ? BrickBox<8, 4, 4>::blocks(n)
+           : brick_small(n) ? BrickBox<4, 4, 4>::blocks(n)
+                            : BrickBox<8, 8, 8>::blocks(n);
 }
 // sweeps of the launch: 1 or, with small boxes, 2
 void launch_brick64(hipStream_t s, const BrickArgs<double> &a, int kind, int sweeps, int form);
