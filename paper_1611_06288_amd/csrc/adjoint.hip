@@ -282,6 +282,8 @@ static void adj_tail(pfc_handle *H, int l, bool fcycle) {
     a.lap3 = H->lap3;
     a.minv = H->minv_adj;
     a.valid = H->valid_adj;
+    a.stop = H->stop;
+    H->stop = StopTest{};
     launch_tail_adj(H->stream, a);
 }
 
@@ -355,7 +357,7 @@ pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi
         RunHost r{};
         const double tol = adj_tol * bnorm;
         st = run_units(H, tol, [&](int slot) {
-            launch_stop_test(H->stream, H->partial, parts, tol, H->cfg.max_cycles, run_state(H, slot));
+            unit_stop_test(H, slot, parts, tol, A.brick);
             adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
             parts = adj_norm(H);
         }, &r);

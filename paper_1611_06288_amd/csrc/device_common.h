@@ -245,6 +245,37 @@ __device__ __forceinline__ unsigned long long block_max_u64(unsigned long long v
     return block_max_u64_waves(v, wm);
 }
 
+// The decision the host loop of a time step takes before each cycle: stop on
+// a non-finite norm, on norm <= tol, or when max_cycles cycles have run;
+// otherwise count the cycle that follows.  stop_test_max: this thread's share of
+// the maxima in a workgroup of TH threads; stop_test_decide: by every thread of
+// it, with the workgroup's maximum and the cycles counted so far (read by all
+// before one writes them), while the step is active; true to go on.
+template <int TH>
+__device__ __forceinline__ unsigned long long stop_test_max(const StopTest &t) {
+    unsigned long long m = 0;
+    for (int b = threadIdx.x; b < t.count; b += TH) m = umax(m, t.partial[b]);
+    return m;
+}
+__device__ __forceinline__ bool stop_test_decide(const StopTest &t, unsigned long long m, int c) {
+    const double r = __longlong_as_double((long long)m);
+    const int status = !isfinite(r) ? 3 : (!(r <= t.tol) && c == t.max_cycles ? 2 : 0);  // PFC_ERR_*
+    const bool go = status == 0 && !(r <= t.tol);
+    if (threadIdx.x == 0) {
+        const RunState &st = t.st;
+        const double r0 = c == 0 ? r : *st.res0;
+        *st.res0 = r0;
+        *st.res = r;
+        *st.status = status;
+        if (go)
+            *st.cycles = c + 1;
+        else
+            *st.active = 0;
+        if (st.host) *st.host = RunHost{go ? 1 : 0, go ? c + 1 : c, status, 0, r0, r};
+    }
+    return go;
+}
+
 // r = S - N(u) at one point (M = 1) from the discrete Laplacians ls of phi, mu
 // and omega there: the three equations of the scheme's operator (the cubic
 // term as g, or its correction form with base bb when DELTA).  Every kernel

@@ -182,36 +182,16 @@ void launch_run_reset(hipStream_t s, RunState st) {
     hipLaunchKernelGGL(k_run_reset, dim3(1), dim3(64), 0, s, st);
 }
 
-// The decision the host loop of a time step takes before each cycle: stop on
-// a non-finite norm, on norm <= tol, or when max_cycles cycles have run;
-// otherwise count the cycle that follows.
-__global__ __launch_bounds__(kBlock) void k_stop_test(const unsigned long long *partial,
-                                                      int count, double tol, int max_cycles,
-                                                      RunState st) {
-    // the state and the first partials are loaded together
-    const int active = *st.active, c = *st.cycles;
-    unsigned long long m = (int)threadIdx.x < count ? partial[threadIdx.x] : 0;
+__global__ __launch_bounds__(kBlock) void k_stop_test(StopTest t) {
+    __shared__ unsigned long long wm[kBlock / 64];
+    const int active = *t.st.active, c = *t.st.cycles;
+    const unsigned long long m = stop_test_max<kBlock>(t);
     if (active == 0) return;  // the same for every thread of the block
-    for (int b = threadIdx.x + kBlock; b < count; b += kBlock) m = umax(m, partial[b]);
-    m = block_max_u64(m);
-    if (threadIdx.x != 0) return;
-    const double r = __longlong_as_double((long long)m);
-    const int status = !isfinite(r) ? 3 : (!(r <= tol) && c == max_cycles ? 2 : 0);  // PFC_ERR_*
-    const bool go = status == 0 && !(r <= tol);
-    if (c == 0) *st.res0 = r;
-    *st.res = r;
-    *st.status = status;
-    if (go)
-        *st.cycles = c + 1;
-    else
-        *st.active = 0;
-    if (st.host) *st.host = RunHost{go ? 1 : 0, go ? c + 1 : c, status, 0, c == 0 ? r : *st.res0, r};
+    stop_test_decide(t, block_max_u64_waves(m, wm), c);
 }
 
-void launch_stop_test(hipStream_t s, const unsigned long long *partial, int count, double tol,
-                      int max_cycles, RunState st) {
-    hipLaunchKernelGGL(k_stop_test, dim3(1), dim3(kBlock), 0, s, partial, count, tol, max_cycles,
-                       st);
+void launch_stop_test(hipStream_t s, const StopTest &t) {
+    hipLaunchKernelGGL(k_stop_test, dim3(1), dim3(kBlock), 0, s, t);
 }
 
 // ------------------------------------------------ residual + coarsening

@@ -230,6 +230,34 @@ inline void brick_run_post(BrickArgs<T> a, int nu1, int nu2, Tri<T> u, Tri<T> x,
     go(a, BRICK_SWEEP, 1, BRICK_PLAIN);
 }
 
+// Device-side stop test of the time loop: the cycle loop's decision on the
+// residual max-norm before a cycle, reduced from the per-workgroup maxima
+// partial[0 .. count) (IEEE bit patterns) by the same one-block launch, made
+// on the GPU so that a
+// replayed graph of cycles needs no host round trip.  active: cycles still
+// wanted (the gate of the cycle kernels); cycles: cycles started; status: a
+// pfc_status; res0/res: first and latest norm.
+// host (may be null): pinned memory that takes the state when a test of an
+// active step has decided.
+struct RunHost {
+    int active, cycles, status, unused;
+    double res0, res;
+};
+struct RunState {
+    int *active = nullptr;
+    int *cycles = nullptr;
+    int *status = nullptr;
+    double *res0 = nullptr;
+    double *res = nullptr;
+    RunHost *host = nullptr;
+};
+struct StopTest {
+    const unsigned long long *partial = nullptr;  // null: no test
+    int count = 0, max_cycles = 0;
+    double tol = 0.0;
+    RunState st{};
+};
+
 // ---- the 8^3 (6^3) level and the coarsest below it in one launch (tail.h) ----
 template <typename T>
 struct TailArgs {
@@ -242,6 +270,7 @@ struct TailArgs {
     const double *lap1 = nullptr, *lap2 = nullptr, *lap3 = nullptr;
     double *minv = nullptr;
     int *valid = nullptr, *iters = nullptr;
+    StopTest stop{};  // also takes the loop's decision (everything before it is scratch)
 };
 inline bool tail_size(int n) { return n == 8 || n == 6; }
 void launch_tail64(hipStream_t s, const TailArgs<double> &a);
@@ -314,30 +343,8 @@ void launch_max_final(hipStream_t s, const unsigned long long *partial, int coun
 void launch_norm_seed(hipStream_t s, const unsigned long long *partial, int count,
                       unsigned long long *dst, int dcount);
 
-// Device-side stop test of the time loop: the cycle loop's decision on the
-// residual max-norm before a cycle, reduced from the per-workgroup maxima
-// partial[0 .. count) (IEEE bit patterns) by the same one-block launch, made
-// on the GPU so that a
-// replayed graph of cycles needs no host round trip.  active: cycles still
-// wanted (the gate of the cycle kernels); cycles: cycles started; status: a
-// pfc_status; res0/res: first and latest norm.
-// host (may be null): pinned memory that takes the state when a test of an
-// active step has decided.
-struct RunHost {
-    int active, cycles, status, unused;
-    double res0, res;
-};
-struct RunState {
-    int *active;
-    int *cycles;
-    int *status;
-    double *res0;
-    double *res;
-    RunHost *host = nullptr;
-};
 void launch_run_reset(hipStream_t s, RunState st);
-void launch_stop_test(hipStream_t s, const unsigned long long *partial, int count, double tol,
-                      int max_cycles, RunState st);
+void launch_stop_test(hipStream_t s, const StopTest &t);
 
 // Coarsest level (natural layout, n = 3 or 4).  lu/piv: cached factorisation
 // of the Newton matrix (device scratch of 64*64 doubles and 64 ints), reused

@@ -419,6 +419,8 @@ static void tail64(pfc_handle *H, int l, bool fcycle) {
     a.minv = H->minv64;
     a.valid = H->valid64;
     a.iters = H->d_iters;
+    a.stop = H->stop;
+    H->stop = StopTest{};
     H->begin_timed(PFC_KERNEL_COARSE, l, 0.0);
     launch_tail64(H->stream, a);
     H->end_timed();

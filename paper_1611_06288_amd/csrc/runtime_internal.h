@@ -104,6 +104,7 @@ struct pfc_handle {
     int split_pre = 0, split_post = 0;
     // graph-driven time loop (pfc_run)
     const int *gate = nullptr;            // cycle gate, set only while its graph is recorded
+    pfc::StopTest stop{};                 // the loop's decision, for the cycle's first tail launch to take
     hipStream_t run_stream = nullptr;     // the loop's own stream (capturable)
     hipEvent_t run_ev = nullptr;
     hipEvent_t norm_ev = nullptr;         // the mixed form's norm copied to the host
@@ -220,6 +221,15 @@ pfc_status unit_events(pfc_handle *H);
 // what it needs before the first one, and whether the level iterates are back
 // in their buffers after one, so that units can follow each other unseen.
 void step_unit(pfc_handle *H, int slot);
+// The unit's decision on `count` maxima in H->partial.  scratch: whatever the unit
+// launches from here to the 8^3 (6^3) level writes neither the iterate nor the
+// cached inverse; the test then rides in that level's launch instead of taking
+// 4.4 us of its own (cycle of 16^3 46.5 -> 44.8 us, 32^3 63 -> 61.4, 64^3 110.9 ->
+// 109.6), up to 64^3: beyond, the maxima are more than that workgroup reads in
+// passing (96^3 207 -> 209) and the descent of the unit that stops, now run for
+// nothing, costs as much.
+constexpr int kTailTestMaxN = 64;
+void unit_stop_test(pfc_handle *H, int slot, int count, double tol, bool scratch);
 void step_unit_seed(pfc_handle *H);
 bool units_usable(const pfc_handle *H);
 // The handle's own non-blocking stream (created on first use): recorded

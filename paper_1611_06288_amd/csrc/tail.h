@@ -31,6 +31,7 @@ struct Tail {
         T u[NF][2][HC];                 // upper level, colour-split
         T cu[3][PC], cf[3][PC], cb[3][PC];  // coarsest: iterate, right-hand side, I u
         CoarseShared cs;
+        unsigned long long wm[kThreads / 64];
     };
 
     const TailArgs<T> &a;
@@ -275,7 +276,19 @@ struct Tail {
                 if constexpr (MOB) sm.u[3][c][p.q] = (T)a.op.mob.phs[g];
             }
         }
+        const bool test = a.stop.partial != nullptr;
+        int counted = 0;
+        if (test) {
+            counted = *a.stop.st.cycles;
+            const unsigned long long m = wave_umax(stop_test_max<kThreads>(a.stop));
+            if ((threadIdx.x & 63) == 0) sm.wm[threadIdx.x >> 6] = m;
+        }
         __syncthreads();
+        if (test) {
+            unsigned long long m = sm.wm[0];
+            for (int w = 1; w < kThreads / 64; ++w) m = umax(m, sm.wm[w]);
+            if (!stop_test_decide(a.stop, m, counted)) return;
+        }
         cycles(cached);
         if (act)
 #pragma unroll

@@ -46,21 +46,35 @@ bool units_usable(const pfc_handle *H) {
     return true;
 }
 
+void unit_stop_test(pfc_handle *H, int slot, int count, double tol, bool scratch) {
+    StopTest t;
+    t.partial = H->partial;
+    t.count = count;
+    t.max_cycles = H->cfg.max_cycles;
+    t.tol = tol;
+    t.st = run_state(H, slot);
+    if (scratch && H->lev[0].n <= kTailTestMaxN && H->nlev >= 2 && H->lev[H->nlev - 2].tail)
+        H->stop = t;
+    else
+        launch_stop_test(H->stream, t);
+}
+
 void step_unit(pfc_handle *H, int slot) {
     const bool fcycle = H->cfg.cycle == PFC_CYCLE_F;
     if (H->split_norm) {
         ahead64(H);
-        launch_stop_test(H->stream, H->partial, H->split_pre + H->split_post, H->cfg.tol,
-                         H->cfg.max_cycles, run_state(H, slot));
+        // (one launch before the descent leaves its input alone, a second one
+        // would write back there)
+        unit_stop_test(H, slot, H->split_pre + H->split_post, H->cfg.tol,
+                       H->cfg.nu1 == ahead_sweeps(H));
         cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
     } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
         const int cnt = brick_pre64(H, 0, BRICK_NORM);
-        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles, run_state(H, slot));
+        unit_stop_test(H, slot, cnt, H->cfg.tol, true);
         cycle64(H, 0, fcycle, kCyclePreDone);
     } else {
         const int cnt = enqueue_norm64(H);
-        launch_stop_test(H->stream, H->partial, cnt, H->cfg.tol, H->cfg.max_cycles,
-                         run_state(H, slot));
+        unit_stop_test(H, slot, cnt, H->cfg.tol, false);
         cycle64(H, 0, fcycle);
     }
 }
