@@ -133,6 +133,25 @@ pfc_status hip_fail(pfc_handle *H, hipError_t e, const char *what) {
     return fail(H, PFC_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+bool dalloc_bytes(pfc_handle *H, void **p, size_t bytes) {
+    const size_t need = (bytes + 255) / 256 * 256;
+    if (need > H->arena_left) {
+        // a finest level's fields and the coarser levels' after them, at least what
+        // the fixed tables take; a request larger than a block is its own block
+        const size_t n = (size_t)H->cfg.n, fields = n * n * n * sizeof(double);
+        const size_t block = std::max(need, std::min((size_t)64 << 20, 20 * fields + ((size_t)3 << 20)));
+        void *q = nullptr;
+        if (hipMalloc(&q, block) != hipSuccess) return false;
+        H->allocs.push_back(q);
+        H->arena = (char *)q;
+        H->arena_left = block;
+    }
+    *p = H->arena;
+    H->arena += need;
+    H->arena_left -= need;
+    return true;
+}
+
 OpParams op_of(const pfc_handle *H, int l) {
     OpParams op{H->lev[l].lay, H->lev[l].h2inv, H->cfg.dt, H->cfg.eps};
     op.fo = H->cfg.scheme == PFC_SCHEME_CS1 ? 1 : 0;
