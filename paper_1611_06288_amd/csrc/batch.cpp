@@ -35,6 +35,20 @@ struct pfc_batch {
     int maxdepth = 0;
     std::vector<std::vector<BSeg>> h_all, h_mid, h_bot;  // per depth (host copies)
     std::vector<BSeg *> d_all, d_mid, d_bot;              // device copies
+    // depths from small_from on have no level above 16^3 left: 16^3 and 12^3 take
+    // one brick launch on either side of the descent, 8^3 and 6^3 with the
+    // coarsest below them one in all (32 of 16^3: cycle 171 -> 130 us, 4 of 64^3
+    // 325 -> 264).  A depth with larger levels runs its phases for those anyway, and
+    // the small ones cost less in them than in launches of their own.
+    int small_from = 0;
+    struct Small {
+        BrickArgs<double> *first = nullptr, *again = nullptr, *post = nullptr;
+        BlockRef *blocks = nullptr;
+        unsigned nblocks = 0;
+        TailArgs<double> *tails = nullptr;
+        int ntails = 0;
+    };
+    std::vector<Small> small;
     BSeg *d_norm = nullptr;
     int n_norm = 0;
     unsigned norm_blocks = 0;
@@ -137,7 +151,17 @@ void phase(pfc_batch *B, int kind, const std::vector<BSeg> &h, BSeg *d, int arg0
                  B->threads[kind], B->persist[kind] ? B->slots[kind] : 0u, arg0, arg1);
 }
 
-BSeg make_seg(pfc_handle *h, int l, int i, const int *active) {
+bool small_level(const pfc_handle *h, int l) {
+    return l > 0 && (h->lev[l].tail || (h->lev[l].brick && h->lev[l].n <= 16));
+}
+bool in_bricks(const pfc_batch *B, const pfc_handle *h, int l) {
+    return l >= B->small_from && l < h->nlev && small_level(h, l) && h->lev[l].brick;
+}
+bool in_tail(const pfc_batch *B, const pfc_handle *h, int l) {
+    return l >= B->small_from && small_level(h, l) && h->lev[l].tail;
+}
+
+BSeg make_seg(const pfc_batch *B, pfc_handle *h, int l, int i, const int *active) {
     BSeg g{};
     const Level &A = h->lev[l];
     g.op = op_of(h, l);
@@ -152,7 +176,7 @@ BSeg make_seg(pfc_handle *h, int l, int i, const int *active) {
         const Level &C = h->lev[l + 1];
         g.lay_c = C.lay;
         g.uc = C.u;
-        g.fc = C.f;
+        g.fc = in_bricks(B, h, l + 1) ? C.fr : C.f;  // where the child looks for I r
         g.ubarc = C.ubar;
     } else {
         g.lay_c = A.lay;
@@ -250,12 +274,15 @@ bool pair_tables(pfc_batch *B) {
 // tau: the levels at depth d still hold I r in f and I u in ubar (the middle
 // levels' first pre-sweep, the coarsest levels' solve launch forms the tau
 // correction).
-void bcycle(pfc_batch *B, int d, bool fcycle, bool tau = false) {
+void bcycle(pfc_batch *B, int d, bool fcycle, bool tau = false, bool again = false) {
     const hipStream_t s = B->stream;
+    const auto &sm = B->small[d];
+    if (sm.ntails && !again)  // (its launch includes the second visit of an F-cycle)
+        launch_batch_tail(s, sm.tails, sm.ntails, fcycle ? 1 : 0);
     if (!B->h_bot[d].empty())
         launch_batch_coarse(s, B->d_bot[d], (int)B->h_bot[d].size(), tau ? 1 : 0);
-    if (B->h_mid[d].empty()) return;
     const auto &mid = B->h_mid[d];
+    if (mid.empty() && !sm.nblocks) return;
     const int picard = B->cfg.lin == PFC_LIN_PICARD;
     // the finest levels' f.a is their phi^k (make_seg): loaded once there
     const int pk1 = d == 0 ? 2 : 0;
@@ -263,16 +290,22 @@ void bcycle(pfc_batch *B, int d, bool fcycle, bool tau = false) {
         for (int c = 0; c < 2; ++c) phase(B, BK_SMOOTH, mid, B->d_mid[d], c, picard | pk1 | flags);
     };
     const bool pair = d == 0 && B->pair;
-    if (!pair)
-        for (int q = 0; q < B->cfg.nu1; ++q) sweep(q == 0 && tau ? 4 : 0);
-    phase(B, BK_RR, mid, B->d_mid[d], 0, 0);
     // with pre-sweeps the next depth's levels form the tau correction
     // themselves: the middle ones in their first sweep, the coarsest ones in
     // their solve's launch
     const bool tau_sweep = B->cfg.nu1 >= 1;
-    if (!tau_sweep) phase(B, BK_TAU, B->h_all[d + 1], B->d_all[d + 1], 0, 0);
+    if (sm.nblocks)
+        launch_batch_brick(s, BRICK_PRE, B->cfg.nu1, tau, tau ? sm.first : sm.again, sm.blocks, sm.nblocks);
+    if (!mid.empty()) {
+        if (!pair)
+            for (int q = 0; q < B->cfg.nu1; ++q) sweep(q == 0 && tau ? 4 : 0);
+        phase(B, BK_RR, mid, B->d_mid[d], 0, 0);
+        if (!tau_sweep) phase(B, BK_TAU, B->h_all[d + 1], B->d_all[d + 1], 0, 0);
+    }
     bcycle(B, d + 1, fcycle, tau_sweep);
-    if (fcycle) bcycle(B, d + 1, false);
+    if (fcycle) bcycle(B, d + 1, false, false, true);
+    if (sm.nblocks) launch_batch_brick(s, BRICK_POST, B->cfg.nu2, false, sm.post, sm.blocks, sm.nblocks);
+    if (mid.empty()) return;
     if (d == 0 && B->ptile) {  // forms the coarse error itself
         launch_batch_ptile(s, B->d_mid[0], (int)mid.size(), ptile_tiles(mid, B->ptile_zi),
                            B->ptile_zi, B->cfg.nu2 >= 1 ? 1 : 0);
@@ -317,6 +350,62 @@ pfc_status capture(pfc_batch *B) {
     if (e != hipSuccess) return bfail(B, PFC_ERR_HIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
     B->graph_ready = true;
     return PFC_OK;
+}
+
+// Brick and tail launches of every depth.
+bool small_tables(pfc_batch *B) {
+    auto upload = [&](const auto &v, auto **d) {
+        return v.empty() || (balloc(B, d, v.size()) && hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]),
+                                                                 hipMemcpyHostToDevice) == hipSuccess);
+    };
+    B->small.resize((size_t)B->maxdepth);
+    bool ok = true;
+    for (int d = 1; d < B->maxdepth && ok; ++d) {
+        std::vector<BrickArgs<double>> first, again, post;
+        std::vector<BlockRef> blocks;
+        std::vector<TailArgs<double>> tails;
+        for (int i = 0; i < B->count; ++i) {
+            pfc_handle *h = B->inst[i];
+            if (d + 1 >= h->nlev) continue;
+            Level &A = h->lev[d], &C = h->lev[d + 1];
+            const int *active = B->st.active + i;
+            if (in_tail(B, h, d)) {
+                TailArgs<double> t = tail_args64(h, d);
+                t.op.gate = active;
+                tails.push_back(t);
+            } else if (in_bricks(B, h, d)) {
+                for (int b = 0; b < brick_blocks(A.n); ++b)
+                    blocks.push_back(BlockRef{(int)first.size(), (unsigned)b});
+                BrickArgs<double> a;
+                a.op = op_of(h, d);
+                a.op.gate = active;
+                a.picard = B->cfg.lin == PFC_LIN_PICARD;
+                a.phk = A.phk;
+                a.LC = C.lay;
+                a.fo = A.f;
+                a.cu = C.ubar;
+                a.cr = C.f;  // a tail's
+                a.u = cst(A.ubar);
+                a.uo = A.u2;
+                a.f = cst(A.fr);
+                first.push_back(a);
+                a.u = cst(A.u);
+                a.f = cst(A.f);
+                again.push_back(a);
+                a.u = cst(A.u2);
+                a.uo = A.u;
+                a.v = cst(C.u);
+                a.ub = cst(C.ubar);
+                post.push_back(a);
+            }
+        }
+        auto &S = B->small[(size_t)d];
+        S.nblocks = (unsigned)blocks.size();
+        S.ntails = (int)tails.size();
+        ok = upload(first, &S.first) && upload(again, &S.again) && upload(post, &S.post) &&
+             upload(blocks, &S.blocks) && upload(tails, &S.tails);
+    }
+    return ok;
 }
 
 // Tables of the set-up and end launches (instances of n = 4, whose only level is
@@ -524,14 +613,24 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
               std::all_of(B->inst.begin(), B->inst.end(), [](const pfc_handle *h) {
                   return batch_pair_fits(h->lev[0].n) && h->lev[0].u2.a;
               });
+    for (int d = B->maxdepth; d > 0; --d) {
+        const bool all = std::all_of(B->inst.begin(), B->inst.end(), [d](const pfc_handle *h) {
+            return d + 1 >= h->nlev || small_level(h, d);
+        });
+        if (!all) break;
+        B->small_from = d;
+    }
+    if (!B->small_from) B->small_from = B->maxdepth;
     // segment lists by depth
     B->h_all.resize(B->maxdepth);
     B->h_mid.resize(B->maxdepth);
     B->h_bot.resize(B->maxdepth);
     for (int i = 0; i < count; ++i)
         for (int l = 0; l < nlev[i]; ++l) {
-            const BSeg g = make_seg(B->inst[i], l, i, B->st.active + i);
+            const BSeg g = make_seg(B, B->inst[i], l, i, B->st.active + i);
             B->h_all[l].push_back(g);
+            const pfc_handle *h = B->inst[i];  // (a tail holds its coarsest level)
+            if (in_tail(B, h, l) || (l > 0 && in_tail(B, h, l - 1)) || in_bricks(B, h, l)) continue;
             BSeg m = g;
             if (l == 0 && B->pair) m.u = B->inst[i]->lev[0].u2;
             (l + 1 < nlev[i] ? B->h_mid[l] : B->h_bot[l]).push_back(m);
@@ -588,7 +687,7 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
          hipHostMalloc((void **)&B->h_stats, 2 * n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_res, 2 * n * sizeof(double), 0) == hipSuccess;
     if (ok && B->pair) ok = pair_tables(B);
-    ok = ok && io_tables(B);
+    ok = ok && io_tables(B) && small_tables(B);
     if (!ok) {
         delete B;
         return bfail(nullptr, PFC_ERR_OOM, "allocation of batch tables failed");

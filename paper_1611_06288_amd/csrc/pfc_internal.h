@@ -506,6 +506,11 @@ struct RestrictSeg {
     const double *from;
     double *to;
 };
+// Brick launches (4^3 boxes, levels of 12^3 and 16^3) and two-level tails of many
+// instances; the gate in a segment's op is its instance's active flag.
+void launch_batch_brick(hipStream_t s, int kind, int sweeps, bool first, const BrickArgs<double> *segs,
+                        const BlockRef *blocks, unsigned count);
+void launch_batch_tail(hipStream_t s, const TailArgs<double> *segs, int nseg, int fcycle);
 void launch_batch_begin(hipStream_t s, const BatchIO *io, const BlockRef *blocks, unsigned count, int ip,
                         int ic);
 void launch_batch_end(hipStream_t s, const BatchIO *io, const BlockRef *blocks, unsigned count, int in);

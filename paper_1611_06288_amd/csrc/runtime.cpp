@@ -417,16 +417,14 @@ static void brick_post64(pfc_handle *H, int l) {
                            });
 }
 
-// The levels from l (8^3 or 6^3) down; an F-cycle's second visit included.
-static void tail64(pfc_handle *H, int l, bool fcycle) {
-    Level &A = H->lev[l], &B = H->lev[l + 1];
+TailArgs<double> tail_args64(const pfc_handle *H, int l) {
+    const Level &A = H->lev[l], &B = H->lev[l + 1];
     TailArgs<double> a;
     a.op = op_of(H, l);
     a.opc = op_of(H, l + 1);
     a.picard = H->cfg.lin == PFC_LIN_PICARD;
     a.nu1 = H->cfg.nu1;
     a.nu2 = H->cfg.nu2;
-    a.fcycle = fcycle ? 1 : 0;
     a.u = A.u;
     a.f = cst(A.f);
     a.ub = cst(A.ubar);
@@ -438,6 +436,13 @@ static void tail64(pfc_handle *H, int l, bool fcycle) {
     a.minv = H->minv64;
     a.valid = H->valid64;
     a.iters = H->d_iters;
+    return a;
+}
+
+// The levels from l (8^3 or 6^3) down; an F-cycle's second visit included.
+static void tail64(pfc_handle *H, int l, bool fcycle) {
+    TailArgs<double> a = tail_args64(H, l);
+    a.fcycle = fcycle ? 1 : 0;
     a.stop = H->stop;
     H->stop = StopTest{};
     H->begin_timed(PFC_KERNEL_COARSE, l, 0.0);

@@ -161,6 +161,8 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags = 0);
 // iterate stays in u, the smoothed one goes to another buffer, from where the
 // part after the descent takes it: dropping the launch's output costs nothing.
 int brick_pre64(pfc_handle *H, int l, int form);
+// The two-level tail's launch on level l (but fcycle and the stop test).
+TailArgs<double> tail_args64(const pfc_handle *H, int l);
 // Level l's right-hand side as its kernels read it.  In a time step the
 // first component of the finest level's S is phi^k itself (scheme-PFC-s1),
 // held bitwise in both f.a and phk; reading it from phk spares the kernels a

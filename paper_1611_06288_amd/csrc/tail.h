@@ -21,11 +21,12 @@ namespace pfc {
 // coarse cell are a quad of lanes.
 // PH: the scheme's cycle, or the adjoint's linear one (f = b, phk = D; the
 // iterate starts at zero and the coarse correction is the coarse iterate).
-template <typename T, int PH, bool DELTA, bool MOB, int N>
+template <typename T, int PH, bool DELTA, bool MOB, int N, int TH = (N * N * N / 2 + 63) / 64 * 64>
 struct Tail {
     static constexpr bool ADJ = PH == BP_ADJ;
     static constexpr int HN = N / 2, HC = N * N * HN, NC = HN, PC = NC * NC * NC;
-    static constexpr int kActive = 4 * PC, kThreads = (kActive + 63) / 64 * 64;
+    static constexpr int kActive = 4 * PC, kThreads = TH;
+    static_assert(kActive <= TH && TH % 64 == 0, "a thread per x-pair, whole waves");
     static constexpr int NF = MOB ? 4 : 3;
     struct Shared {
         T u[NF][2][HC];                 // upper level, colour-split

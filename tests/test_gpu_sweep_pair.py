@@ -8,6 +8,9 @@ pre-sweeps from I u after the tau correction; odd sweep counts leave a single
 sweep beside the pair.  (The stop test's halves and the time loop on pairs:
 test_gpu_split_norm.py, test_gpu_timeloop.py.)
 
+The batched form's small depths (bricks of 12^3 and 16^3, tails of 8^3 and 6^3
+of both sizes in one launch) run in the same test.
+
 The batched pairs take 32 x 16 boxes: one step of a batch against single steps
 (bricks up to 96^3), bit for bit with the norms; 48-point rows leave half a
 box, a tolerance met by one instance long before the others masks it.
@@ -51,7 +54,8 @@ def test_cycle_equals_kernel_level_cycle(n, nu, kw):
 
 
 @pytest.mark.parametrize("sizes,kw", [((32,), {}), ((48, 32, 64), {}), ((96, 48, 128, 64, 32), {}),
-                                      ((64, 96, 48), dict(cycle="F")), ((48, 64), dict(lin="picard")),
+                                      ((64, 96, 48), dict(cycle="F")), ((48, 64), dict(lin="picard")), ((16, 24, 12), {}), ((24, 24), dict(cycle="F")),
+                                      ((32, 12, 16, 48), dict(nu1=1, nu2=2)),
                                       ((32, 48, 96), dict(max_cycles=3))])
 def test_batch_step_equals_single_steps(sizes, kw):
     tol = 1e-14 if "max_cycles" in kw else 1e-10
