@@ -20,12 +20,15 @@
 // each between barriers, and on 64^3 and 96^3 the halo's arithmetic as well.
 // Up to 32^3 that chain is what counts: 4^3 boxes, both sweeps of a side in one
 // launch; 8 x 4 x 4 at 32^3, where 4^3 boxes are two per CU and share its cycles
-// (a 32^3 cycle 69 -> 62.5 us, 64^3 117 -> 110).  From 48^3 on the halo of two sweeps costs more than a launch (8^3
-// boxes with both sweeps: 57 us per cycle at 64^3, one sweep per launch 45).
-// Measured per V(2,2) cycle, kernel time (before -> now): 64^3 finest with its
-// stop-test norm 60 -> 45 us in 11 -> 4 launches, 32^3 43 -> 22, 16^3 39 -> 16;
-// a 64^3 long-run cycle in all 178 -> 107 us.  From 128^3 on, where bandwidth
-// counts, the z-marching kernels take over.
+// (a 32^3 cycle 69 -> 62.5 us, 64^3 117 -> 110).  From 48^3 on the halo of two
+// sweeps costs more than a launch (8^3 boxes with both sweeps: 57 us per cycle at
+// 64^3, one sweep per launch 45).  The cycle gate is tested behind the loads, not
+// ahead of them (0.3-0.5 us per launch; 64^3 cycle 108.6 -> 105.3 us, 96^3 F-cycle
+// 363.5 -> 353.5).
+// Measured per V(2,2) cycle, kernel time (half-sweeps -> now): 64^3 finest with its
+// stop-test norm 60 -> 44 us in 11 -> 4 launches, 32^3 43 -> 18, 16^3 39 -> 15; a
+// 64^3 long-run cycle in all 178 -> 104 us.  From 128^3 on, where bandwidth counts,
+// the z-marching kernels take over.
 #pragma once
 
 #include "brick_geo.h"
@@ -297,6 +300,7 @@ struct BrickPre {
         for (int i = 0; i < N0; ++i) B.load_f(i0[i].g, f0[i], a0[i], b0[i]);
 #pragma unroll
         for (int i = 0; i < F1; ++i) B.load_f(i1[i].g, f1[i], a1[i], b1[i]);
+        if (gate_closed(a.op.gate)) return;  // its load runs beside the others
 #pragma unroll
         for (int i = 0; i < N1; ++i)
             if (iu[i].d <= DU) {
@@ -460,6 +464,7 @@ struct BrickSweep {
         for (int i = 0; i < N0; ++i) B.load_f(i0[i].g, f0[i], a0[i], b0[i]);
 #pragma unroll
         for (int i = 0; i < F1; ++i) B.load_f(i1[i].g, f1[i], a1[i], b1[i]);
+        if (gate_closed(a.op.gate)) return;  // its load runs beside the others
         if constexpr (PROL) {
             T *e = &sm.e[0][0][0][0];
 #pragma unroll
@@ -551,7 +556,6 @@ __global__ __launch_bounds__((BrickPre<T, PH, DELTA, MOB, BX, BY, BZ, S, TAU, NR
 k_brick_pre(BrickArgs<T> a) {
     using K = BrickPre<T, PH, DELTA, MOB, BX, BY, BZ, S, TAU, NRM, ZERO>;
     __shared__ typename K::Shared sm;
-    if (gate_closed(a.op.gate)) return;
     K::run(a, (int)xcd_block(), sm, a.part);
 }
 
@@ -562,7 +566,6 @@ __global__ __launch_bounds__((BrickSweep<T, PH, DELTA, MOB, BX, BY, BZ, S, PROL,
 k_brick_sweep(BrickArgs<T> a) {
     using K = BrickSweep<T, PH, DELTA, MOB, BX, BY, BZ, S, PROL, TAU, NRM, ZERO>;
     __shared__ typename K::Shared sm;
-    if (gate_closed(a.op.gate)) return;
     K::run(a, (int)xcd_block(), sm, a.part);
 }
 

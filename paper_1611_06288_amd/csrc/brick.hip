@@ -18,7 +18,6 @@ kb_brick_pre(const BrickArgs<double> *__restrict__ segs, const BlockRef *__restr
     __shared__ typename K::Shared sm;
     const BlockRef b = blocks[blockIdx.x];
     const BrickArgs<double> a = segs[b.seg];
-    if (gate_closed(a.op.gate)) return;
     K::run(a, (int)b.blk, sm, nullptr);
 }
 
@@ -30,7 +29,6 @@ kb_brick_post(const BrickArgs<double> *__restrict__ segs, const BlockRef *__rest
     __shared__ typename K::Shared sm;
     const BlockRef b = blocks[blockIdx.x];
     const BrickArgs<double> a = segs[b.seg];
-    if (gate_closed(a.op.gate)) return;
     K::run(a, (int)b.blk, sm, nullptr);
 }
 
