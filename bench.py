@@ -33,19 +33,18 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 
-# HBM traffic of one finest-level FP64 smoother launch at 256^3, from two
-# rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, averaged over
-# the step's 256^3 launches of the sweeps the smoother timing covers: plain,
-# plain without the dead colour-0 writes, and norm-carrying post-sweeps) scaled
-# by what the same counters read for a 1 GiB device copy (FETCH x 2.0,
-# WRITE x 1.0).  Valid only for the smoother sources
-# it was measured on (first 16 hex digits of the sha256 of smooth.hip, smooth.h,
-# device_common.h and runtime.cpp, which chooses the buffers the sweeps read,
-# concatenated); otherwise reported null.
-SMOOTHER_TRAFFIC = {"sources_sha256_16": "38676dba7cbfe3e2", "n": 256,
-                    "fetch_KiB": 360756, "write_KiB": 350145,
+# HBM traffic of one finest-level FP64 sweep at 256^3, half of a launch of two, from
+# two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE; KiB per dispatch, averaged over
+# the sweeps the smoother timing covers: both of the post-sweeps' launch and the
+# second of the pre-sweeps') scaled by what the same counters read for a 1 GiB
+# device copy (FETCH x 2.0, WRITE x 1.0).  Valid only for the smoother sources
+# it was measured on (first 16 hex digits of the sha256 of the files below,
+# concatenated; runtime.cpp chooses the buffers the sweeps read); otherwise
+# reported null.
+SMOOTHER_TRAFFIC = {"sources_sha256_16": "e27a52ed530e0b9b", "n": 256,
+                    "fetch_KiB": 204916, "write_KiB": 194974,
                     "fetch_scale": 2.0, "write_scale": 1.0}
-SMOOTHER_SOURCES = ("smooth.hip", "smooth.h", "device_common.h", "runtime.cpp")
+SMOOTHER_SOURCES = ("sweep_pair.hip", "sweep_pair.h", "smooth.h", "device_common.h", "runtime.cpp")
 METRIC = "time-steps/s & V-cycles/s at 256^3 (FP64 vs mixed); smoother HBM GB/s %peak"
 # (m0, m1, m2, mmin) of the variable-mobility run: M(v) = max(0.05, 1 - v^2)
 MOBILITY = (1.0, 0.0, -1.0, 0.05)
@@ -548,8 +547,8 @@ def main():
     sm = fp64["kernels"].get("smooth0", {})
     achieved = sm.get("achieved_GBps")
     roofline = {
-        "kernel": ("finest-level fused red-black sweep (one full sweep per launch; 64 B/pt, 56 "
-                   "where the next sweep makes colour-0 mu, omega dead; mean over launches)"),
+        "kernel": ("finest-level red-black sweep, two full sweeps per launch of 64 B/pt (72 with "
+                   "the norm half; a sweep's share: half; mean over sweeps)"),
         "bound": "hbm",
         "achieved": achieved,
         "peak": HBM_PEAK_GBS,

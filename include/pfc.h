@@ -146,7 +146,8 @@ pfc_status pfc_init_guess(pfc_handle *h, const double *phi0, double *mu, double 
  * phi_prev or phi_cur.  info (host, nullable) receives the report.
  * Returns NOT_CONVERGED after max_cycles cycles (outputs hold the last
  * iterate, info filled) and NONFINITE if the residual is NaN/Inf.
- * Synchronises the stream (one 8-byte residual read-back per cycle). */
+ * Synchronises the stream (the loop's decisions are read back while a
+ * cycle ahead of them runs). */
 pfc_status pfc_step(pfc_handle *h, const double *phi_prev, const double *phi_cur,
                     double *phi_next, double *mu, double *omega, pfc_step_info *info);
 
@@ -206,8 +207,8 @@ pfc_status pfc_energy(pfc_handle *h, const double *phi, const double *phi_prev, 
  * pointers to n^3 FP64 values in C order on the current device, L the box
  * edge (h = L/n), eps as in the config; out3 is a DEVICE pointer to 3
  * doubles receiving (F_h, modified energy, mass) as pfc_energy's out.
- * The per-workgroup partial sums live in a 768 KiB device array of the
- * library, one per GPU, held until the process ends; its address is looked
+ * The per-workgroup partial sums live in a device array of 768 KiB and
+ * 48 bytes of the library, one per GPU, held until the process ends; its address is looked
  * up on the first call on each device (call with the stream's device
  * current).  Every call on a GPU uses that GPU's one array: calls that
  * overlap on one GPU (other streams, other host threads) race and must be
