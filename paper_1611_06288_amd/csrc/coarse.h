@@ -230,16 +230,27 @@ __device__ __forceinline__ void coarse_body(const OpParams &op, Tri<T> u, Tri<co
         dvec[p] = act ? (x - tau * lw - w3 * tau * l3 - bp) : 0.0;
         wave_sync();
         double d = 0.0;
-#pragma unroll 1
-        for (int q0 = 0; q0 < P; q0 += 16) {  // 16 columns' loads in one block; past P: 0 times 0
-            double m[16], v[16];
+        // 8 columns' loads in one block, ahead of the sums over the 8 before; past P: 0
+        // times 0
+        double ma[8], va[8], mb[8], vb[8];
+        auto load = [&](double (&m)[8], double (&v)[8], int q0) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
+            for (int i = 0; i < 8; ++i) {
                 m[i] = A[(q0 + i) * P + p];
                 v[i] = dvec[q0 + i];
             }
+        };
+        auto add = [&](const double (&m)[8], const double (&v)[8], int q0) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) d -= (act && q0 + i < P ? m[i] : 0.0) * v[i];
+            for (int i = 0; i < 8; ++i) d -= (act && q0 + i < P ? m[i] : 0.0) * v[i];
+        };
+        load(ma, va, 0);
+#pragma unroll 1
+        for (int q0 = 0; q0 < P; q0 += 16) {
+            load(mb, vb, q0 + 8);
+            add(ma, va, q0);
+            load(ma, va, q0 + 16 < P ? q0 + 16 : 0);
+            add(mb, vb, q0 + 8);
         }
         x += d;
         const double dm = wave_max(fabs(d));

@@ -39,11 +39,12 @@ struct Tail {
     Shared &sm;
     int I, J, K, zz, b;
     bool act;
+    double own[2];  // phi of the thread's points while a smoothing run lasts
     T f[2][3], ak[2], bb[2];  // of the thread's point of each colour
 
     __device__ __forceinline__ Tail(const TailArgs<T> &a_, Shared &s_) : a(a_), sm(s_) {
         const int t = threadIdx.x;
-        act = t < kActive;
+        act = kActive == TH || t < kActive;
         const int cell = act ? t >> 2 : 0;
         zz = t >> 1 & 1;
         b = t & 1;
@@ -94,10 +95,39 @@ struct Tail {
             ls[1] = s * h2inv;
         }
     }
+    // point_solve in two parts, its operations in its order: what the own old value
+    // gives is formed while the neighbours' loads are under way (with every neighbour's
+    // load ahead of the sums, own values in registers and the coarsest product's loads
+    // ahead of its sums: cycle of 32^3 60.1 -> 59.3 us, 64^3 106.3 -> 105.4, 96^3 F
+    // 353.2 -> 351.5).  Here and not in point_solve: split there, the compiler lays the
+    // two-sweep launch out otherwise, 128^3 252 -> 258 us per cycle.
+    __device__ __forceinline__ void point_cubic(const PointCoef &q, double phin, double k, double base,
+                                                double &c, double &cubic) const {
+        if (!DELTA && a.picard) {
+            const double qq = q.fo ? phin * phin : 0.25 * (phin * phin + k * k);
+            c = qq + q.lin_c;
+            cubic = q.fo ? 0.0 : qq * k;
+        } else {
+            const double gp = dg_of<DELTA>(q.fo, phin, k, base);
+            c = gp + q.lin_c;
+            cubic = g_of<DELTA>(q.fo, phin, k, base) - gp * phin;
+        }
+    }
+    // s3: the neighbours' sums of phi, mu, omega
+    __device__ __forceinline__ void point_rest(const PointCoef &q, double c, double cubic, double f1,
+                                               double f2, double f3, const double (&s3)[3], double &phi,
+                                               double &mu, double &om) const {
+        const double r2 = f2 + s3[2] * q.h2inv + cubic;
+        const double r1 = f1 + q.tau * s3[1] * q.h2inv;
+        const double r3 = f3 + q.w3 * s3[0] * q.h2inv;
+        phi = (r1 - q.A * r2 + q.AB * r3) / (1.0 + q.A * (c + q.BD));
+        om = r3 - q.Dd * phi;
+        mu = r2 + c * phi - q.B * om;
+    }
     __device__ __forceinline__ void half_sweep(int c) {
         if (act) {
             const Pt p = pt(c);
-            const double phin = (double)sm.u[0][c][p.q], k = (double)ak[c];
+            const double phin = own[c], k = (double)ak[c];
             const double f0 = (double)f[c][0], f1 = (double)f[c][1], f2 = (double)f[c][2];
             double phi, mu, om;
             if constexpr (ADJ) {
@@ -119,9 +149,19 @@ struct Tail {
                 point_solve_mob(a.op, a.picard, phin, k, f0, f1, f2, msum, smm, sum(2, c, p),
                                 sum(0, c, p), phi, mu, om);
             } else {
-                point_solve<DELTA>(a.op, a.picard, phin, k, (double)bb[c], f0, f1, f2, sum(1, c, p),
-                                   sum(2, c, p), sum(0, c, p), phi, mu, om);
+                double nb[3][6], co, cubic, s3[3];
+#pragma unroll
+                for (int fl = 0; fl < 3; ++fl)
+#pragma unroll
+                    for (int e = 0; e < 6; ++e) nb[fl][e] = (double)sm.u[fl][c ^ 1][p.nb[e]];
+                const PointCoef q(a.op);
+                point_cubic(q, phin, k, (double)bb[c], co, cubic);
+#pragma unroll
+                for (int fl = 0; fl < 3; ++fl)
+                    s3[fl] = (nb[fl][0] + nb[fl][1]) + (nb[fl][2] + nb[fl][3]) + (nb[fl][4] + nb[fl][5]);
+                point_rest(q, co, cubic, f0, f1, f2, s3, phi, mu, om);
             }
+            own[c] = (double)(T)phi;
             sm.u[0][c][p.q] = (T)phi;
             sm.u[1][c][p.q] = (T)mu;
             sm.u[2][c][p.q] = (T)om;
@@ -157,6 +197,8 @@ struct Tail {
                     prolong();
                     __syncthreads();
                 }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) own[c] = act ? (double)sm.u[0][c][pt(c).q] : 0.0;
 #pragma unroll 1
                 for (int s = 0; s < (side ? a.nu2 : a.nu1); ++s) {
                     half_sweep(0);
