@@ -44,6 +44,8 @@ Div make_div(int d) {
     return r;
 }
 
+static bool div_exact(const Div &d, int n) { return (d.three ? 3 : 1) << d.shift == n; }
+
 Lay make_lay(int n, bool split) {
     Lay l;
     l.n = n;
@@ -841,7 +843,9 @@ struct EnergySums {
     }
 };
 
-template <bool PREV>
+// ANY: n is no solver size (pfc_energy_static takes every n), so that Div does not
+// divide by it.
+template <bool PREV, bool ANY>
 __global__ __launch_bounds__(kBlock) void k_energy_part(Lay L, double hinv, double h2inv,
                                                         const double *__restrict__ phi,
                                                         const double *__restrict__ prev,
@@ -851,7 +855,14 @@ __global__ __launch_bounds__(kBlock) void k_energy_part(Lay L, double hinv, doub
     const unsigned total = (unsigned)npts(L), blk = xcd_block();
     for (unsigned t = blk * kBlock + threadIdx.x; t < total; t += gridDim.x * kBlock) {
         int i, j, k;
-        decode(L, t, i, j, k);
+        if constexpr (ANY) {
+            const unsigned n = (unsigned)L.n, row = t / n;
+            i = (int)(t - row * n);
+            k = (int)(row / n);
+            j = (int)(row - (unsigned)k * n);
+        } else {
+            decode(L, t, i, j, k);
+        }
         const Off q = offs(L, i, j, k);
         const double a[6] = {phi[q.xp], phi[q.xm], phi[q.yp], phi[q.ym], phi[q.zp], phi[q.zm]};
         double b[4] = {0, 0, 0, 0};
@@ -985,13 +996,18 @@ template <bool PREV>
 static void energy_part(hipStream_t s, const Lay &nat, double h, const double *phi,
                         const double *phi_prev, double *part, int parts) {
     const unsigned un = (unsigned)nat.n;
+    if (!div_exact(nat.dn, nat.n)) {
+        hipLaunchKernelGGL((k_energy_part<PREV, true>), dim3((unsigned)parts), dim3(kBlock), 0, s, nat, 1.0 / h,
+                           1.0 / (h * h), phi, phi_prev, part);
+        return;
+    }
     if (un >= 128 && un % 16 == 0) {  // whole parts per plane; enough workgroups
         const unsigned pp = un * un / kBlock, groups = ((unsigned)parts + kEZ * pp - 1) / (kEZ * pp);
         hipLaunchKernelGGL(k_energy_march<PREV>, dim3(groups * pp), dim3(kBlock), 0, s, nat, 1.0 / h,
                            1.0 / (h * h), phi, phi_prev, part, (unsigned)parts);
         return;
     }
-    hipLaunchKernelGGL(k_energy_part<PREV>, dim3((unsigned)parts), dim3(kBlock), 0, s, nat, 1.0 / h,
+    hipLaunchKernelGGL((k_energy_part<PREV, false>), dim3((unsigned)parts), dim3(kBlock), 0, s, nat, 1.0 / h,
                        1.0 / (h * h), phi, phi_prev, part);
 }
 

@@ -21,7 +21,8 @@ struct Tri {
 template <typename T>
 __host__ __device__ inline Tri<const T> cst(Tri<T> t) { return Tri<const T>{t.a, t.b, t.c}; }
 
-// Division by n = 2^s or 3*2^s without integer divide instructions.
+// Division by n = 2^s or 3*2^s without integer divide instructions (by no other n:
+// it would divide by a smaller number of that form).
 struct Div {
     unsigned shift;  // s
     unsigned three;  // 1 if n = 3*2^s
@@ -31,7 +32,7 @@ struct Div {
     }
 };
 
-Div make_div(int d);  // host: d must be 2^s or 3*2^s
+Div make_div(int d);  // host
 
 // Storage of one level's fields.  Natural: C order [k][j][i].  Colour-split
 // (n even): the points of colour c = (i+j+k) mod 2 are stored in block c of
