@@ -479,7 +479,7 @@ pfc_status run_step(pfc_batch *B, pfc_step_info *infos_step) {
         const pfc_status stc = capture(B);
         if (stc != PFC_OK) return stc;
     }
-    for (int guard = 0; guard <= B->cfg.max_cycles + 2; ++guard) {
+    for (int guard = 0; guard - 2 <= B->cfg.max_cycles; ++guard) {  // (may be INT_MAX)
         e = hipGraphLaunch(B->exec, s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(B->h_num, B->st.active, B->count * sizeof(int), hipMemcpyDeviceToHost, s);

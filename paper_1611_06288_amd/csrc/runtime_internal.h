@@ -303,7 +303,7 @@ pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out) {
             *out = r;
             return PFC_OK;
         }
-        if (i > H->cfg.max_cycles + 2)
+        if (i - 2 > H->cfg.max_cycles)  // (max_cycles may be INT_MAX)
             return fail(H, PFC_ERR_HIP, "cycle loop: the device stop test did not end it");
         next = i > 0 ? r.res * (r.res / res) : INFINITY;
         res = r.res;

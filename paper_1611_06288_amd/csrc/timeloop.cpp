@@ -150,7 +150,7 @@ pfc_status graph_step(pfc_handle *H, const double *prev, const double *cur, doub
         total += launches;
         HIP_TRY(H, hipStreamSynchronize(H->stream));
         if (!hs->active) break;
-        if (total > H->cfg.max_cycles + 1)
+        if (total - 1 > H->cfg.max_cycles)  // (may be INT_MAX)
             return fail(H, PFC_ERR_HIP, "time loop: the device stop test did not end the step");
         launches = 1;
     }
