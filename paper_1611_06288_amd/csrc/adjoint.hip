@@ -356,11 +356,14 @@ pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi
     if (bnorm > 0.0) {  // the first unit tests |b| itself
         RunHost r{};
         const double tol = adj_tol * bnorm;
-        st = run_units(H, tol, [&](int slot) {
-            unit_stop_test(H, slot, parts, tol, A.brick);
-            adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
-            parts = adj_norm(H);
-        }, &r);
+        st = run_units(
+            H, tol, bnorm,
+            [&](int i, bool ride) { unit_stop_test(H, i & 1, parts, tol, A.brick && ride); },
+            [&](int) {
+                adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false, A.brick);
+                parts = adj_norm(H);
+            },
+            &r);
         if (st != PFC_OK) return st;
         c = r.cycles;
         status = r.status;

@@ -211,20 +211,26 @@ inline RunState run_state(pfc_handle *H, int slot = 0) {
     return RunState{H->d_run,        H->d_run + 1,    H->d_run + 2, H->d_runres,
                     H->d_runres + 1, run_host(H, slot)};
 }
-// A cycle loop driven by the host, the decisions on the device: `unit`
-// enqueues the stop test (with run_state(H, slot)) and one cycle with the norm
-// after or before it, every launch gated on the test.  Unit i + 1 is enqueued
-// before the host looks at unit i's test, so the device does not wait for the
-// host between cycles (a 32^3 step waited 12-25 us of every 78 us cycle), unless
-// the norms so far say that unit i stops: a unit behind that one does nothing,
-// but takes 4 us a launch.  tol: the test's.  out: the last decision.
-template <typename Unit>
-pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out);
+// A cycle loop driven by the host, the decisions on the device.  Unit i is
+// head(i, ride), the launches up to and with the stop test (into run_state(H, i & 1);
+// ride: the test may ride in a launch of the body), and body(i), the rest of a cycle,
+// every launch gated on the test.  While the norms so far say that the loop goes on,
+// units are enqueued whole, one ahead of the host, so that the device does not wait
+// between cycles (a 32^3 step waited 12-25 us of every 78 us cycle).  Where they say
+// that a test will stop it, or say nothing yet, its body waits for the decision:
+// behind a stop it would do nothing, but takes 4 us a launch (a step that starts
+// converged, all units whole: 64^3 V(2,2) 178 us instead of 105, 96^3 F(4,4), 150
+// launches a cycle, 1411 instead of 120).
+// first: the norm at the first test where the host has it, else NaN.  tol: the
+// test's.  out: the last decision.
+template <typename Head, typename Body>
+pfc_status run_units(pfc_handle *H, double tol, double first, Head head, Body body, RunHost *out);
 pfc_status unit_events(pfc_handle *H);
-// The unit of a time step's loop (pfc_step, and recorded as pfc_run's graph),
-// what it needs before the first one, and whether the level iterates are back
-// in their buffers after one, so that units can follow each other unseen.
-void step_unit(pfc_handle *H, int slot);
+// The unit of a time step's loop (pfc_step after its first, and recorded as pfc_run's
+// graph), what pfc_run needs before the first one, and whether the level iterates are
+// back in their buffers after one, so that units can follow each other unseen.
+void step_head(pfc_handle *H, int slot, bool ride);
+void step_body(pfc_handle *H);
 // The unit's decision on `count` maxima in H->partial.  scratch: whatever the unit
 // launches from here to the 8^3 (6^3) level writes neither the iterate nor the
 // cached inverse; the test then rides in that level's launch instead of taking
@@ -273,8 +279,8 @@ pfc_status hip_fail(pfc_handle *H, hipError_t e, const char *what);
     } while (0)
 
 namespace pfc {
-template <typename Unit>
-pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out) {
+template <typename Head, typename Body>
+pfc_status run_units(pfc_handle *H, double tol, double first, Head head, Body body, RunHost *out) {
     const pfc_status st = unit_events(H);
     if (st != PFC_OK) return st;
     struct Gate {  // set while the units are enqueued
@@ -283,20 +289,22 @@ pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out) {
         ~Gate() { H->gate = nullptr; }
     } gate(H);
     launch_run_reset(H->stream, run_state(H));
-    auto enqueue = [&](int i) -> pfc_status {
-        unit(i & 1);
+    auto enqueue = [&](int i, bool whole) -> pfc_status {
+        head(i, whole);
+        if (whole) body(i);
         HIP_TRY(H, hipGetLastError());
         HIP_TRY(H, hipEventRecord(H->unit_ev[i & 1], H->stream));
         return PFC_OK;
     };
-    pfc_status e = enqueue(0);
+    constexpr double kContraction = 0.1;  // until two norms are known: a good cycle's
+    double expect = first, rate = kContraction, res = first;  // test i's norm; per cycle; the last known
+    auto goes_on = [&](int i, double norm) { return norm > tol && i < H->cfg.max_cycles; };
+    bool whole = goes_on(0, expect);
+    pfc_status e = enqueue(0, whole);
     if (e != PFC_OK) return e;
-    double res = 0.0, next = INFINITY;  // the last norm known, the next one at its contraction
-    bool ahead = false;
     for (int i = 0;; ++i) {
-        // unit i is enqueued; the next one too unless i is expected to stop
-        ahead = next > tol;
-        if (ahead && (e = enqueue(i + 1)) != PFC_OK) return e;
+        bool next = whole && goes_on(i + 1, expect * rate);
+        if (whole && (e = enqueue(i + 1, next)) != PFC_OK) return e;
         HIP_TRY(H, hipEventSynchronize(H->unit_ev[i & 1]));
         const RunHost r = *run_host(H, i & 1);
         if (!r.active) {
@@ -305,9 +313,15 @@ pfc_status run_units(pfc_handle *H, double tol, Unit unit, RunHost *out) {
         }
         if (i - 2 > H->cfg.max_cycles)  // (max_cycles may be INT_MAX)
             return fail(H, PFC_ERR_HIP, "cycle loop: the device stop test did not end it");
-        next = i > 0 ? r.res * (r.res / res) : INFINITY;
+        if (i > 0) rate = r.res / res;
         res = r.res;
-        if (!ahead && (e = enqueue(i + 1)) != PFC_OK) return e;
+        expect = res * rate;
+        if (!whole) {
+            body(i);
+            next = goes_on(i + 1, expect);
+            if ((e = enqueue(i + 1, next)) != PFC_OK) return e;
+        }
+        whole = next;
     }
 }
 }  // namespace pfc

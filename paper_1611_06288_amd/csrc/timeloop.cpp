@@ -59,24 +59,24 @@ void unit_stop_test(pfc_handle *H, int slot, int count, double tol, bool scratch
         launch_stop_test(H->stream, t);
 }
 
-void step_unit(pfc_handle *H, int slot) {
-    const bool fcycle = H->cfg.cycle == PFC_CYCLE_F;
+void step_head(pfc_handle *H, int slot, bool ride) {
     if (H->split_norm) {
         ahead64(H);
-        // (one launch before the descent leaves its input alone, a second one
-        // would write back there)
-        unit_stop_test(H, slot, H->split_pre + H->split_post, H->cfg.tol,
-                       H->cfg.nu1 == ahead_sweeps(H));
-        cycle64(H, 0, fcycle, kCyclePreDone | kCyclePostNorm);
+        unit_stop_test(H, slot, H->split_pre + H->split_post, H->cfg.tol, false);
     } else if (H->lev[0].brick) {  // the part before the descent, then the decision on its input
         const int cnt = brick_pre64(H, 0, BRICK_NORM);
-        unit_stop_test(H, slot, cnt, H->cfg.tol, true);
-        cycle64(H, 0, fcycle, kCyclePreDone);
+        unit_stop_test(H, slot, cnt, H->cfg.tol, ride);
     } else {
         const int cnt = enqueue_norm64(H);
         unit_stop_test(H, slot, cnt, H->cfg.tol, false);
-        cycle64(H, 0, fcycle);
     }
+}
+
+void step_body(pfc_handle *H) {
+    const unsigned flags = H->split_norm       ? kCyclePreDone | kCyclePostNorm
+                           : H->lev[0].brick ? kCyclePreDone
+                                             : 0u;
+    cycle64(H, 0, H->cfg.cycle == PFC_CYCLE_F, flags);
 }
 
 void step_unit_seed(pfc_handle *H) {
@@ -120,7 +120,8 @@ pfc_status record_graph(pfc_handle *H) {
         return hip_fail(H, e, "hipStreamBeginCapture");
     }
     H->gate = H->d_run;  // every launch below reads the active flag
-    step_unit(H, 0);
+    step_head(H, 0, true);
+    step_body(H);
     H->gate = nullptr;
     H->timing = timing;
     e = hipStreamEndCapture(H->stream, &H->run_graph);
