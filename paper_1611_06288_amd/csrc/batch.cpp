@@ -152,7 +152,7 @@ void phase(pfc_batch *B, int kind, const std::vector<BSeg> &h, BSeg *d, int arg0
 }
 
 bool small_level(const pfc_handle *h, int l) {
-    return l > 0 && (h->lev[l].tail || (h->lev[l].brick && h->lev[l].n <= 16));
+    return l > 0 && (h->lev[l].tail || (h->lev[l].brick && batch_brick(h->lev[l].n)));
 }
 bool in_bricks(const pfc_batch *B, const pfc_handle *h, int l) {
     return l >= B->small_from && l < h->nlev && small_level(h, l) && h->lev[l].brick;
@@ -568,11 +568,17 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
         delete B;
         return bfail(nullptr, PFC_ERR_HIP, "stream/event creation failed");
     }
+    // V(2,2) or F(2,2) on instances of 32^3 and larger: a cycle of 2 to 64 of
+    // them (0.5 to 20 million points) takes 0.73 to 0.95 of the half-sweeps' time,
+    // 20.1 million points 3.42 -> 2.50 ms, 0.92 million 412 -> 376 us.
+    B->pair = cfgs[0].nu1 == 2 && cfgs[0].nu2 == 2 &&
+              std::all_of(cfgs, cfgs + count, [](const pfc_config &c) { return batch_pair_fits(c.n); });
     bool ok = true;
     std::vector<int> nlev(count);
     for (int i = 0; i < count && ok; ++i) {
         pfc_handle *h = nullptr;
-        const pfc_status st = pfc_create(&cfgs[i], B->stream, &h);
+        const pfc_status st =
+            create_handle(&cfgs[i], B->stream, B->pair ? USE_BATCH_PAIRS : USE_BATCH, &h);
         if (st != PFC_OK) {
             const std::string msg = pfc_last_error(nullptr);
             delete B;
@@ -606,13 +612,6 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
     }
     B->st.norm_first = nf;
     B->st.norm_blocks = nbk;
-    // V(2,2) or F(2,2) on instances of 32^3 and larger: a cycle of 2 to 64 of
-    // them (0.5 to 20 million points) takes 0.73 to 0.95 of the half-sweeps' time,
-    // 20.1 million points 3.42 -> 2.50 ms, 0.92 million 412 -> 376 us.
-    B->pair = cfgs[0].nu1 == 2 && cfgs[0].nu2 == 2 &&
-              std::all_of(B->inst.begin(), B->inst.end(), [](const pfc_handle *h) {
-                  return batch_pair_fits(h->lev[0].n) && h->lev[0].u2.a;
-              });
     for (int d = B->maxdepth; d > 0; --d) {
         const bool all = std::all_of(B->inst.begin(), B->inst.end(), [d](const pfc_handle *h) {
             return d + 1 >= h->nlev || small_level(h, d);

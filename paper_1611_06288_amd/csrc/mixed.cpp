@@ -38,9 +38,7 @@ constexpr double kMinDefectFactor = 1e-5;
 constexpr double kTolMargin = 1.5;
 constexpr double kFloorQ = 0.5;
 
-pfc_status mixed_init(pfc_handle *H) {
-    if (hipEventCreateWithFlags(&H->norm_ev, hipEventDisableTiming) != hipSuccess)
-        return fail(H, PFC_ERR_HIP, "event creation failed");
+void mixed_plan(pfc_handle *H) {
     const int slots = pair_slots(H->device, PAIR_FP32);
     for (int l = 0; l < H->nlev; ++l) {
         Level32 &A = H->lev32[l];
@@ -49,34 +47,27 @@ pfc_status mixed_init(pfc_handle *H) {
         const int pairs = H->cfg.nu1 / 2 + H->cfg.nu2 / 2;
         A.pair = pair_fits(H->lev[l].n, true) && pairs > 0 && (pairs & 1) == 0;
         A.pnz = pair_nz(H->lev[l].n, slots, PAIR_FP32);
-        const size_t P = H->lev[l].P;
-        float *e, *f, *eb;
-        const bool ok = dalloc(H, &e, 3 * P) && dalloc(H, &f, 3 * P) && dalloc(H, &eb, 3 * P) &&
-                        dalloc(H, &A.phk, P) && dalloc(H, &A.base, P);
-        if (!ok) return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
-        A.e = Tri<float>{e, e + P, e + 2 * P};
-        A.f = Tri<float>{f, f + P, f + 2 * P};
-        A.ebar = Tri<float>{eb, eb + P, eb + 2 * P};
-        if (H->lev[l].brick || A.pair) {
-            float *e2;
-            if (!dalloc(H, &e2, 3 * P))
-                return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
-            A.e2 = Tri<float>{e2, e2 + P, e2 + 2 * P};
-        }
-        if (H->lev[l].brick) {
-            float *fr;
-            if (!dalloc(H, &fr, 3 * P))
-                return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
-            A.fr = Tri<float>{fr, fr + P, fr + 2 * P};
-            if (!brick_small(H->lev[l].n)) {
-                float *e3;
-                if (!dalloc(H, &e3, 3 * P))
-                    return fail(H, PFC_ERR_OOM, "device allocation for the FP32 hierarchy failed");
-                A.e3 = Tri<float>{e3, e3 + P, e3 + 2 * P};
-            }
-        }
     }
-    return PFC_OK;
+}
+
+bool mixed_alloc(pfc_handle *H) {
+    for (int l = 0; l < H->nlev; ++l) {
+        Level32 &A = H->lev32[l];
+        const Level &D = H->lev[l];
+        if (!dalloc(H, &A.e, D.P) || !dalloc(H, &A.f, D.P) || !dalloc(H, &A.ebar, D.P) ||
+            !dalloc(H, &A.phk, D.P) || !dalloc(H, &A.base, D.P))
+            return false;
+        const bool apart = D.brick && !brick_small(D.n);
+        if (l == 0) {  // nothing is restricted to it: ebar is free
+            if (apart && !dalloc(H, &A.e2, D.P)) return false;
+            (apart ? A.e3 : A.e2) = A.ebar;
+            continue;
+        }
+        if ((D.brick || A.pair) && !dalloc(H, &A.e2, D.P)) return false;
+        if (D.brick && !dalloc(H, &A.fr, D.P)) return false;
+        if (apart) A.e3 = A.fr;
+    }
+    return true;
 }
 
 // tau: the first sweep of a coarse level, forming the tau correction from

@@ -176,6 +176,7 @@ struct BrickArgs {
 // has CUs to spare; from 48^3 on 8^3 boxes and one sweep per launch, whose
 // halos cost less than the launch they would save.
 inline bool brick_small(int n) { return n <= 32; }
+inline bool batch_brick(int n) { return n <= 16; }  // those of a batch (launch_batch_brick)
 inline bool brick_size(int n) { return n >= 12 && n <= 96 && n % (brick_small(n) ? 4 : 8) == 0; }
 constexpr int kBrickMaxSweeps = 2;  // sweeps per side of the descent
 template <int BX, int BY, int BZ>

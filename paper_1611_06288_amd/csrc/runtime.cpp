@@ -135,20 +135,19 @@ pfc_status hip_fail(pfc_handle *H, hipError_t e, const char *what) {
 
 bool dalloc_bytes(pfc_handle *H, void **p, size_t bytes) {
     const size_t need = (bytes + 255) / 256 * 256;
-    if (need > H->arena_left) {
-        // a finest level's fields and the coarser levels' after them, at least what
-        // the fixed tables take; a request larger than a block is its own block
-        const size_t n = (size_t)H->cfg.n, fields = n * n * n * sizeof(double);
-        const size_t block = std::max(need, std::min((size_t)64 << 20, 20 * fields + ((size_t)3 << 20)));
-        void *q = nullptr;
-        if (hipMalloc(&q, block) != hipSuccess) return false;
-        H->allocs.push_back(q);
-        H->arena = (char *)q;
-        H->arena_left = block;
+    *p = nullptr;
+    if (H->planning) {
+        if (need < kOwnBlock) H->arena_left += need;
+        return true;
     }
-    *p = H->arena;
-    H->arena += need;
-    H->arena_left -= need;
+    if (need < kOwnBlock && need <= H->arena_left) {
+        *p = H->arena;
+        H->arena += need;
+        H->arena_left -= need;
+        return true;
+    }
+    if (hipMalloc(p, need) != hipSuccess) return false;
+    H->allocs.push_back(*p);
     return true;
 }
 
@@ -607,6 +606,140 @@ void step_end(pfc_handle *H, double *phi_next, double *mu, double *omega) {
     else
         from_level0(H, phi_next, mu, omega);
 }
+// ------------------------------------------------------------ creation
+
+// The levels' sizes and launch forms.
+static void plan_levels(pfc_handle *H, const std::vector<int> &sizes, HandleUse use) {
+    const pfc_config &cfg = H->cfg;
+    const bool mob = mobility_on(H);
+    const int slots = fused_slots(H->device, mob);
+    const int p_form = mob ? PAIR_MOB : PAIR_FP64, p_slots = pair_slots(H->device, p_form);
+    int rt_slots[RT_MODES];
+    for (int m = 0; m < RT_MODES; ++m) rt_slots[m] = resid_tile_slots(H->device, m, mob);
+    const int pt_slots[2] = {prolong_tile_slots(H->device, false), prolong_tile_slots(H->device, true)};
+    const bool sweeps = cfg.nu1 >= 1 && cfg.nu1 <= kBrickMaxSweeps && cfg.nu2 >= 1 &&
+                        cfg.nu2 <= kBrickMaxSweeps;
+    H->nlev = (int)sizes.size();
+    for (int l = 0; l < H->nlev; ++l) {
+        Level &A = H->lev[l];
+        A.n = sizes[l];
+        A.h = cfg.L / A.n;
+        A.h2inv = 1.0 / (A.h * A.h);
+        A.P = (size_t)A.n * A.n * A.n;
+        A.lay = make_lay(A.n, l < H->nlev - 1);
+        A.rt = resid_tile_fits(A.lay);
+        for (int m = 0; m < RT_MODES; ++m) A.rt_nz[m] = resid_tile_nz(A.n, rt_slots[m], m);
+        if (l + 1 < H->nlev)
+            for (int t = 0; t < 2; ++t) A.pz[t] = prolong_tile_nzr(pt_slots[t], A.n / 2, A.n);
+        A.fused = l < H->nlev - 1 && fused_fits(A.n);
+        if (A.fused) A.nz = fused_nz(A.n, slots);
+        // (a cycle recorded as a graph needs an even number of launches, each of
+        // which exchanges the iterate buffers: pairs must not make it odd)
+        A.pair = A.fused && pair_fits(A.n, false);
+        A.pair = A.pair && ((sweep_launches(H, l) & 1) == 0 || ((cfg.nu1 + cfg.nu2) & 1));
+        A.pnz = pair_nz(A.n, p_slots, p_form);
+        A.brick = l < H->nlev - 1 && sweeps && brick_size(A.n) && (use == USE_SINGLE || batch_brick(A.n));
+        A.tail = l > 0 && l == H->nlev - 2 && sweeps && tail_size(A.n);
+    }
+    // the split stop test (the graph loop seeds it behind both halves)
+    const Level &A = H->lev[0];
+    const int one = A.fused ? fused_blocks(A.n, A.nz) : 0;
+    const int two = A.pair ? pair_blocks(A.n, A.pnz, p_form) : 0;
+    H->split_pre = ahead_sweeps(H) == 2 ? two : one;
+    H->split_post = A.pair && cfg.nu2 >= 2 && (cfg.nu2 & 1) == 0 ? two : one;
+    H->split_norm = A.fused && cfg.nu1 >= 1 && cfg.nu2 >= 1 && cfg.precision == PFC_FP64 &&
+                    std::max(H->split_pre, H->split_post) <= kMaxReduceBlocks;
+    if (cfg.precision == PFC_MIXED) mixed_plan(H);
+}
+
+// Every request for device memory of a new handle (the sums' partials: the batch has its own).
+static bool alloc_levels(pfc_handle *H, HandleUse use) {
+    for (int l = 0; l < H->nlev; ++l) {
+        Level &A = H->lev[l];
+        if (!dalloc(H, &A.u, A.P) || !dalloc(H, &A.f, A.P) || !dalloc(H, &A.ubar, A.P) ||
+            !dalloc(H, &A.phk, A.P) || (mobility_on(H) && !dalloc(H, &A.phs, A.P)))
+            return false;
+        if (A.brick && l > 0 && !dalloc(H, &A.fr, A.P)) return false;
+        const bool apart = A.brick && !brick_small(A.n);
+        if (apart) A.u3 = l > 0 ? A.fr : A.ubar;
+        const bool own = use == USE_SINGLE ? A.fused || (l > 0 ? A.brick : A.rt || apart)
+                         : l > 0           ? A.brick
+                                           : use == USE_BATCH_PAIRS;
+        if (own && !dalloc(H, &A.u2, A.P)) return false;
+        if (!own && A.brick) A.u2 = A.ubar;
+    }
+    // a workgroup leaves one value per norm, six per energy sum; below 64^3 it takes
+    // 64 points (4^3 bricks) or more
+    const Level &F = H->lev[0];
+    const size_t parts = F.n < 64 ? F.P / 64 + 1 : (size_t)kMaxReduceBlocks;
+    if (use == USE_SINGLE && (!dalloc(H, &H->partial, 3 * parts + 16) ||
+                              !dalloc(H, &H->energy_part, 6 * parts + 16)))
+        return false;
+    const size_t C = H->lev[H->nlev - 1].P;
+    return dalloc(H, &H->d_iters, 4) && dalloc(H, &H->d_run, 4) && dalloc(H, &H->d_runres, 2) &&
+           dalloc(H, &H->minv64, 64 * 64) && dalloc(H, &H->minv32, 64 * 64) &&
+           dalloc(H, &H->valid64, 4) && dalloc(H, &H->valid32, 4) &&
+           dalloc(H, &H->minv_adj, 64 * 64) && dalloc(H, &H->valid_adj, 4) &&
+           dalloc(H, &H->lap1, C * C) && dalloc(H, &H->lap2, C * C) && dalloc(H, &H->lap3, C * C) &&
+           (H->cfg.precision != PFC_MIXED || mixed_alloc(H));
+}
+
+pfc_status create_handle(const pfc_config *cfg, void *stream, HandleUse use, pfc_handle **out) {
+    if (!out) return fail(nullptr, PFC_ERR_INVALID_ARG, "out is NULL");
+    *out = nullptr;
+    const std::string why = validate_config(cfg);
+    if (!why.empty()) return fail(nullptr, PFC_ERR_INVALID_ARG, why);
+    pfc_handle *H = new pfc_handle();
+    H->cfg = *cfg;
+    H->stream = (hipStream_t)stream;
+    if (hipGetDevice(&H->device) != hipSuccess) {
+        delete H;
+        return fail(nullptr, PFC_ERR_HIP, "hipGetDevice failed");
+    }
+    std::vector<int> sizes;
+    level_sizes(cfg->n, sizes);
+    plan_levels(H, sizes, use);
+    H->planning = true;
+    bool ok = alloc_levels(H, use);
+    H->planning = false;
+    if (hipMalloc((void **)&H->arena, H->arena_left) != hipSuccess) {
+        H->arena = nullptr;
+        ok = false;
+    } else {
+        H->allocs.push_back(H->arena);
+    }
+    ok = ok && alloc_levels(H, use);
+    if (ok && hipHostMalloc((void **)&H->h_pin, 64 * sizeof(double), 0) != hipSuccess) {
+        H->h_pin = nullptr;
+        ok = false;
+    }
+    if (!ok) {
+        delete H;
+        return fail(nullptr, PFC_ERR_OOM, "device or pinned allocation failed");
+    }
+    const Level &C = H->lev[H->nlev - 1];
+    std::vector<double> l1, l2, l3;
+    coarse_matrices(C.n, C.h, l1, l2, l3);
+    if (hipMemcpy(H->lap1, l1.data(), l1.size() * sizeof(double), hipMemcpyHostToDevice) !=
+            hipSuccess ||
+        hipMemcpy(H->lap2, l2.data(), l2.size() * sizeof(double), hipMemcpyHostToDevice) !=
+            hipSuccess ||
+        hipMemcpy(H->lap3, l3.data(), l3.size() * sizeof(double), hipMemcpyHostToDevice) !=
+            hipSuccess ||
+        hipMemset(H->valid64, 0, sizeof(int)) != hipSuccess ||
+        hipMemset(H->valid32, 0, sizeof(int)) != hipSuccess) {
+        delete H;
+        return fail(nullptr, PFC_ERR_HIP, "initialisation of coarse-level data failed");
+    }
+    if (cfg->precision == PFC_MIXED &&
+        hipEventCreateWithFlags(&H->norm_ev, hipEventDisableTiming) != hipSuccess) {
+        delete H;
+        return fail(nullptr, PFC_ERR_HIP, "event creation failed");
+    }
+    *out = H;
+    return PFC_OK;
+}
+
 }  // namespace pfc
 
 // ------------------------------------------------------------- C ABI
@@ -630,129 +763,7 @@ const char *pfc_last_error(const pfc_handle *h) {
 }
 
 pfc_status pfc_create(const pfc_config *cfg, void *stream, pfc_handle **out) {
-    if (!out) return fail(nullptr, PFC_ERR_INVALID_ARG, "out is NULL");
-    *out = nullptr;
-    const std::string why = validate_config(cfg);
-    if (!why.empty()) return fail(nullptr, PFC_ERR_INVALID_ARG, why);
-    pfc_handle *H = new pfc_handle();
-    H->cfg = *cfg;
-    H->stream = (hipStream_t)stream;
-    if (hipGetDevice(&H->device) != hipSuccess) {
-        delete H;
-        return fail(nullptr, PFC_ERR_HIP, "hipGetDevice failed");
-    }
-    std::vector<int> sizes;
-    level_sizes(cfg->n, sizes);
-    H->nlev = (int)sizes.size();
-    int device = 0;
-    if (hipGetDevice(&device) != hipSuccess) device = 0;
-    const bool mob = cfg->mobility == PFC_MOBILITY_QUADRATIC;
-    const int slots = fused_slots(device, mob);
-    const int p_form = mob ? PAIR_MOB : PAIR_FP64, p_slots = pair_slots(device, p_form);
-    int rt_slots[RT_MODES];
-    for (int m = 0; m < RT_MODES; ++m) rt_slots[m] = resid_tile_slots(device, m, mob);
-    const int pt_slots[2] = {prolong_tile_slots(device, false), prolong_tile_slots(device, true)};
-    bool ok = true;
-    for (int l = 0; l < H->nlev && ok; ++l) {
-        Level &A = H->lev[l];
-        A.n = sizes[l];
-        A.h = cfg->L / A.n;
-        A.h2inv = 1.0 / (A.h * A.h);
-        A.P = (size_t)A.n * A.n * A.n;
-        A.lay = make_lay(A.n, l < H->nlev - 1);
-        double *u, *f, *ub;
-        ok = dalloc(H, &u, 3 * A.P) && dalloc(H, &f, 3 * A.P) && dalloc(H, &ub, 3 * A.P) &&
-             dalloc(H, &A.phk, A.P);
-        if (ok && cfg->mobility == PFC_MOBILITY_QUADRATIC) ok = dalloc(H, &A.phs, A.P);
-        if (!ok) break;
-        A.u = Tri<double>{u, u + A.P, u + 2 * A.P};
-        A.f = Tri<double>{f, f + A.P, f + 2 * A.P};
-        A.ubar = Tri<double>{ub, ub + A.P, ub + 2 * A.P};
-        A.rt = resid_tile_fits(A.lay);
-        for (int m = 0; m < RT_MODES; ++m) A.rt_nz[m] = resid_tile_nz(A.n, rt_slots[m], m);
-        if (l + 1 < H->nlev)
-            for (int t = 0; t < 2; ++t) A.pz[t] = prolong_tile_nzr(pt_slots[t], A.n / 2, A.n);
-        A.fused = l < H->nlev - 1 && fused_fits(A.n);
-        // (a cycle recorded as a graph needs an even number of launches, each of
-        // which exchanges the iterate buffers: pairs must not make it odd)
-        A.pair = A.fused && pair_fits(A.n, false);
-        A.pair = A.pair && ((sweep_launches(H, l) & 1) == 0 || ((cfg->nu1 + cfg->nu2) & 1));
-        A.pnz = pair_nz(A.n, p_slots, p_form);
-        const bool sweeps = cfg->nu1 >= 1 && cfg->nu1 <= kBrickMaxSweeps && cfg->nu2 >= 1 &&
-                            cfg->nu2 <= kBrickMaxSweeps;
-        A.brick = l < H->nlev - 1 && sweeps && brick_size(A.n);
-        A.tail = l > 0 && l == H->nlev - 2 && sweeps && tail_size(A.n);
-        if (A.brick && l > 0) {
-            double *fr;
-            ok = dalloc(H, &fr, 3 * A.P);
-            if (!ok) break;
-            A.fr = Tri<double>{fr, fr + A.P, fr + 2 * A.P};
-        }
-        if (A.brick && !brick_small(A.n)) {
-            double *u3;
-            ok = dalloc(H, &u3, 3 * A.P);
-            if (!ok) break;
-            A.u3 = Tri<double>{u3, u3 + A.P, u3 + 2 * A.P};
-        }
-        if (A.fused || A.brick || (l == 0 && A.rt)) {
-            A.nz = fused_nz(A.n, slots);
-            double *u2;
-            ok = dalloc(H, &u2, 3 * A.P);
-            if (!ok) break;
-            A.u2 = Tri<double>{u2, u2 + A.P, u2 + 2 * A.P};
-        }
-    }
-    ok = ok && dalloc(H, &H->partial, (size_t)3 * kMaxReduceBlocks + 16);
-    if (ok) {  // the split stop test (the graph loop seeds it behind both halves)
-        const Level &A = H->lev[0];
-        const int one = A.fused ? fused_blocks(A.n, A.nz) : 0;
-        const int two = A.pair ? pair_blocks(A.n, A.pnz, p_form) : 0;
-        H->split_pre = ahead_sweeps(H) == 2 ? two : one;
-        H->split_post = A.pair && cfg->nu2 >= 2 && (cfg->nu2 & 1) == 0 ? two : one;
-        H->split_norm = A.fused && cfg->nu1 >= 1 && cfg->nu2 >= 1 && cfg->precision == PFC_FP64 &&
-                        std::max(H->split_pre, H->split_post) <= kMaxReduceBlocks;
-    }
-    ok = ok && dalloc(H, &H->d_iters, 4) && dalloc(H, &H->d_run, 4) && dalloc(H, &H->d_runres, 2);
-    ok = ok && dalloc(H, &H->energy_part, (size_t)6 * kMaxReduceBlocks + 16);
-    ok = ok && dalloc(H, &H->minv64, 64 * 64) && dalloc(H, &H->minv32, 64 * 64) &&
-         dalloc(H, &H->valid64, 4) && dalloc(H, &H->valid32, 4) &&
-         dalloc(H, &H->minv_adj, 64 * 64) && dalloc(H, &H->valid_adj, 4);
-    std::vector<double> l1, l2, l3;
-    if (ok) {
-        const Level &C = H->lev[H->nlev - 1];
-        coarse_matrices(C.n, C.h, l1, l2, l3);
-        ok = dalloc(H, &H->lap1, l1.size()) && dalloc(H, &H->lap2, l2.size()) &&
-             dalloc(H, &H->lap3, l3.size());
-    }
-    if (ok && hipHostMalloc((void **)&H->h_pin, 64 * sizeof(double), 0) != hipSuccess) {
-        H->h_pin = nullptr;
-        ok = false;
-    }
-    if (!ok) {
-        delete H;
-        return fail(nullptr, PFC_ERR_OOM, "device or pinned allocation failed");
-    }
-    if (hipMemcpy(H->lap1, l1.data(), l1.size() * sizeof(double), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemcpy(H->lap2, l2.data(), l2.size() * sizeof(double), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemcpy(H->lap3, l3.data(), l3.size() * sizeof(double), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemset(H->valid64, 0, sizeof(int)) != hipSuccess ||
-        hipMemset(H->valid32, 0, sizeof(int)) != hipSuccess) {
-        delete H;
-        return fail(nullptr, PFC_ERR_HIP, "initialisation of coarse-level data failed");
-    }
-    if (cfg->precision == PFC_MIXED) {
-        const pfc_status st = mixed_init(H);
-        if (st != PFC_OK) {
-            g_create_error = H->err;
-            delete H;
-            return st;
-        }
-    }
-    *out = H;
-    return PFC_OK;
+    return create_handle(cfg, stream, USE_SINGLE, out);
 }
 
 pfc_status pfc_destroy(pfc_handle *h) {

@@ -26,7 +26,9 @@ struct Level {
     Tri<double> f{nullptr, nullptr, nullptr};     // right-hand side
     Tri<double> ubar{nullptr, nullptr, nullptr};  // restricted fine iterate I u (scratch on level 0)
     Tri<double> u2{nullptr, nullptr, nullptr};    // second iterate buffer (fused sweeps, fused correction, bricks)
-    Tri<double> u3{nullptr, nullptr, nullptr};    // third iterate buffer (bricks)
+    // third iterate buffer (bricks that run the two sweeps of a side apart): fr, which
+    // a cycle reads in its first launch only, on level 0 the scratch ubar
+    Tri<double> u3{nullptr, nullptr, nullptr};
     Tri<double> fr{nullptr, nullptr, nullptr};    // I r of a coarse brick level (its f is f + N(I u))
     double *phk = nullptr;                        // phi^kappa on this level
     double *phs = nullptr;                        // phi* of the variable mobility (else null)
@@ -46,8 +48,8 @@ struct Level {
 struct Level32 {
     Tri<float> e{nullptr, nullptr, nullptr};     // correction iterate
     Tri<float> f{nullptr, nullptr, nullptr};     // right-hand side
-    Tri<float> ebar{nullptr, nullptr, nullptr};  // restricted fine correction
-    Tri<float> e2{nullptr, nullptr, nullptr}, e3{nullptr, nullptr, nullptr};  // more iterate buffers (bricks, pairs)
+    Tri<float> ebar{nullptr, nullptr, nullptr};  // restricted fine correction (unused on level 0)
+    Tri<float> e2{nullptr, nullptr, nullptr}, e3{nullptr, nullptr, nullptr};  // more iterate buffers (bricks, pairs), as u2, u3
     Tri<float> fr{nullptr, nullptr, nullptr};    // I r of a coarse brick level
     bool pair = false;                           // two sweeps in a row take one launch (sweep_pair.h)
     int pnz = 1;                                 // its plane ranges per column
@@ -81,7 +83,10 @@ struct pfc_handle {
     pfc::Level lev[pfc::kMaxLevels];
     pfc::Level32 lev32[pfc::kMaxLevels];
     std::vector<void *> allocs;
-    char *arena = nullptr;  // rest of the last block
+    // the block of the requests smaller than kOwnBlock: counted in a first pass over
+    // the requests (planning), then allocated once and dealt out in a second
+    bool planning = false;
+    char *arena = nullptr;
     size_t arena_left = 0;
     unsigned long long *partial = nullptr;
     int *d_iters = nullptr;
@@ -200,7 +205,12 @@ void restrict_phk(pfc_handle *H);
 pfc_status resid_norm64(pfc_handle *H, Tri<double> r, double *out);
 int enqueue_norm64(pfc_handle *H, unsigned long long *dst = nullptr);
 pfc_status read_norm(pfc_handle *H, int partials, double *out);
-pfc_status mixed_init(pfc_handle *H);
+void mixed_plan(pfc_handle *H);   // the FP32 levels' forms
+bool mixed_alloc(pfc_handle *H);  // their memory
+// pfc_create.  A batch launches its instances' cycles itself and needs fewer buffers:
+// bricks on its small levels only, a second iterate on level 0 for paired sweeps.
+enum HandleUse { USE_SINGLE, USE_BATCH, USE_BATCH_PAIRS };
+pfc_status create_handle(const pfc_config *cfg, void *stream, HandleUse use, pfc_handle **out);
 pfc_status step64(pfc_handle *h, const double *phi_prev, const double *phi_cur, double *phi_next,
                   double *mu, double *omega, pfc_step_info *info);
 // The device state of a cycle loop; its decisions reach h_pin through slot 0 or 1.
@@ -257,15 +267,23 @@ void step_begin(pfc_handle *H, const double *phi_prev, const double *phi_cur, co
                 const double *omega);
 void step_end(pfc_handle *H, double *phi_next, double *mu, double *omega);
 void invalidate_coarse(pfc_handle *H);
-// Device memory of a handle, given back with it: out of blocks of about the size
-// that its levels need (a handle makes some 40 requests, 5 to 15 us each as calls
-// of their own: 96^3 392 -> 197 us to create, 64^3 268 -> 160), whole cache lines apart.
+// Device memory of a handle, given back with it.  The small ones of its some 40
+// requests share one block of exactly their size (96^3: 870 us to create with a call
+// for each, 240 in one block).
+constexpr size_t kOwnBlock = (size_t)64 << 20;
 bool dalloc_bytes(pfc_handle *H, void **p, size_t bytes);
 template <typename T>
 bool dalloc(pfc_handle *H, T **p, size_t count) {
     void *q = nullptr;
     if (!dalloc_bytes(H, &q, count * sizeof(T))) return false;
     *p = (T *)q;
+    return true;
+}
+template <typename T>
+bool dalloc(pfc_handle *H, Tri<T> *t, size_t P) {
+    T *q;
+    if (!dalloc(H, &q, 3 * P)) return false;
+    *t = q ? Tri<T>{q, q + P, q + 2 * P} : Tri<T>{nullptr, nullptr, nullptr};
     return true;
 }
 pfc_status fail(pfc_handle *H, pfc_status st, const std::string &msg);
