@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <fstream>
 #include <functional>
 #include <map>
@@ -122,6 +123,34 @@ bool balloc(pfc_batch *B, T **p, size_t count) {
     return true;
 }
 
+// The launches' tables: collected, then allocated and copied as one (a batch has
+// some 40, 10 to 25 us each on their own: 8 instances of 16^3 1790 us to create with
+// calls for each, 1340 so; one of 48^3 590 and 220).
+class Tables {
+    std::vector<char> host;
+    std::vector<std::function<void(char *)>> set;
+
+public:
+    // *d: v's place on the device once put() has returned; null if v is empty
+    template <typename T, typename D>
+    void add(const std::vector<T> &v, D **d) {
+        *d = nullptr;
+        if (v.empty()) return;
+        const size_t at = (host.size() + 255) / 256 * 256, bytes = v.size() * sizeof(T);
+        host.resize(at + bytes);
+        std::memcpy(host.data() + at, v.data(), bytes);
+        set.push_back([d, at](char *base) { *d = reinterpret_cast<T *>(base + at); });
+    }
+    bool put(pfc_batch *B) const {
+        char *base = nullptr;
+        if (!balloc(B, &base, host.size()) ||
+            hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess)
+            return false;
+        for (const auto &f : set) f(base);
+        return true;
+    }
+};
+
 // Tiles of shape `shape` in a launch of `kind` over the list v.
 unsigned seg_tiles(const BSeg &g, int kind, int shape) {
     const unsigned W = (unsigned)kTileMin << (shape % kWOpts), Z = 1u << (shape / kWOpts);
@@ -200,7 +229,7 @@ pfc_status bfail(pfc_batch *B, pfc_status s, const std::string &m) {
 }
 
 // Segments, tiles and norm blocks of the paired sweeps.
-bool pair_tables(pfc_batch *B) {
+bool pair_tables(pfc_batch *B, Tables &t) {
     const size_t n = (size_t)B->count;
     std::vector<PairArgs<double>> pre(n), post(n);
     for (size_t i = 0; i < n; ++i) {
@@ -254,20 +283,13 @@ bool pair_tables(pfc_batch *B) {
     for (const PairTile &t : tiles) ++blocks[(size_t)t.seg];
     for (size_t i = 1; i < n; ++i) first[i] = first[i - 1] + blocks[i - 1];
     B->n_tiles = (int)tiles.size();
-    unsigned *pf = nullptr, *pb = nullptr;
-    const bool ok =
-        balloc(B, &B->d_pre, n) && balloc(B, &B->d_post, n) && balloc(B, &B->d_tiles, tiles.size()) &&
-        balloc(B, &B->halves, 2 * tiles.size()) && balloc(B, &pf, n) && balloc(B, &pb, n) &&
-        hipMemcpy(B->d_pre, pre.data(), n * sizeof(pre[0]), hipMemcpyHostToDevice) == hipSuccess &&
-        hipMemcpy(B->d_post, post.data(), n * sizeof(post[0]), hipMemcpyHostToDevice) == hipSuccess &&
-        hipMemcpy(B->d_tiles, tiles.data(), tiles.size() * sizeof(tiles[0]), hipMemcpyHostToDevice) ==
-            hipSuccess &&
-        hipMemcpy(pf, first.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess &&
-        hipMemcpy(pb, blocks.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess;
+    t.add(pre, &B->d_pre);
+    t.add(post, &B->d_post);
+    t.add(tiles, &B->d_tiles);
     B->pst = B->st;
-    B->pst.norm_first = pf;
-    B->pst.norm_blocks = pb;
-    return ok;
+    t.add(first, &B->pst.norm_first);
+    t.add(blocks, &B->pst.norm_blocks);
+    return balloc(B, &B->halves, 2 * tiles.size());
 }
 
 // One cycle of every active instance, aligned by depth from the finest level.
@@ -353,14 +375,9 @@ pfc_status capture(pfc_batch *B) {
 }
 
 // Brick and tail launches of every depth.
-bool small_tables(pfc_batch *B) {
-    auto upload = [&](const auto &v, auto **d) {
-        return v.empty() || (balloc(B, d, v.size()) && hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]),
-                                                                 hipMemcpyHostToDevice) == hipSuccess);
-    };
+void small_tables(pfc_batch *B, Tables &t) {
     B->small.resize((size_t)B->maxdepth);
-    bool ok = true;
-    for (int d = 1; d < B->maxdepth && ok; ++d) {
+    for (int d = 1; d < B->maxdepth; ++d) {
         std::vector<BrickArgs<double>> first, again, post;
         std::vector<BlockRef> blocks;
         std::vector<TailArgs<double>> tails;
@@ -370,9 +387,9 @@ bool small_tables(pfc_batch *B) {
             Level &A = h->lev[d], &C = h->lev[d + 1];
             const int *active = B->st.active + i;
             if (in_tail(B, h, d)) {
-                TailArgs<double> t = tail_args64(h, d);
-                t.op.gate = active;
-                tails.push_back(t);
+                TailArgs<double> a = tail_args64(h, d);
+                a.op.gate = active;
+                tails.push_back(a);
             } else if (in_bricks(B, h, d)) {
                 for (int b = 0; b < brick_blocks(A.n); ++b)
                     blocks.push_back(BlockRef{(int)first.size(), (unsigned)b});
@@ -402,21 +419,19 @@ bool small_tables(pfc_batch *B) {
         auto &S = B->small[(size_t)d];
         S.nblocks = (unsigned)blocks.size();
         S.ntails = (int)tails.size();
-        ok = upload(first, &S.first) && upload(again, &S.again) && upload(post, &S.post) &&
-             upload(blocks, &S.blocks) && upload(tails, &S.tails);
+        t.add(first, &S.first);
+        t.add(again, &S.again);
+        t.add(post, &S.post);
+        t.add(blocks, &S.blocks);
+        t.add(tails, &S.tails);
     }
-    return ok;
 }
 
 // Tables of the set-up and end launches (instances of n = 4, whose only level is
 // in natural order, leave them empty: those batches go instance by instance).
-bool io_tables(pfc_batch *B) {
+void io_tables(pfc_batch *B, Tables &t) {
     for (auto *h : B->inst)
-        if (!h->lev[0].lay.split) return true;
-    auto upload = [&](const auto &v, auto **d) {
-        return balloc(B, d, v.size()) &&
-               hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice) == hipSuccess;
-    };
+        if (!h->lev[0].lay.split) return;
     auto add = [](std::vector<BlockRef> &v, int seg, size_t items) {
         for (size_t b = 0; b * kBlock < items; ++b) v.push_back(BlockRef{seg, (unsigned)b});
     };
@@ -428,25 +443,25 @@ bool io_tables(pfc_batch *B) {
                              A.f, A.u, A.phk});
         add(blocks, i, A.P / 2);
     }
-    bool ok = upload(io, &B->d_io) && upload(blocks, &B->d_io_blocks);
+    t.add(io, &B->d_io);
+    t.add(blocks, &B->d_io_blocks);
     B->io_blocks = (unsigned)blocks.size();
-    for (int d = 0; d + 1 < B->maxdepth && ok; ++d) {
+    const size_t depths = (size_t)B->maxdepth - 1;
+    B->d_rs.resize(depths);
+    B->d_rs_blocks.resize(depths);
+    for (size_t d = 0; d < depths; ++d) {
         std::vector<RestrictSeg> segs;
         blocks.clear();
         for (auto *h : B->inst)
-            if (d + 1 < h->nlev) {
+            if ((int)d + 1 < h->nlev) {
                 const Level &A = h->lev[d], &C = h->lev[d + 1];
                 add(blocks, (int)segs.size(), C.P);
                 segs.push_back(RestrictSeg{A.lay, C.lay, A.phk, C.phk});
             }
-        RestrictSeg *ds = nullptr;
-        BlockRef *db = nullptr;
-        ok = upload(segs, &ds) && upload(blocks, &db);
-        B->d_rs.push_back(ds);
-        B->d_rs_blocks.push_back(db);
+        t.add(segs, &B->d_rs[d]);
+        t.add(blocks, &B->d_rs_blocks[d]);
         B->rs_blocks.push_back((unsigned)blocks.size());
     }
-    return ok;
 }
 
 void steps_begin(pfc_batch *B) {
@@ -602,16 +617,11 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
     }
     const size_t n = (size_t)count;
     ok = ok && balloc(B, &B->st.active, n) && balloc(B, &B->st.cycles, n) && balloc(B, &B->st.status, n) &&
-         balloc(B, &B->st.res0, n) && balloc(B, &B->st.res, n) &&
-         balloc(B, &B->d_valid, n);
-    unsigned *nf = nullptr, *nbk = nullptr;
-    ok = ok && balloc(B, &nf, n) && balloc(B, &nbk, n);
+         balloc(B, &B->st.res0, n) && balloc(B, &B->st.res, n);
     if (!ok) {
         delete B;
         return bfail(nullptr, PFC_ERR_OOM, "device allocation failed");
     }
-    B->st.norm_first = nf;
-    B->st.norm_blocks = nbk;
     for (int d = B->maxdepth; d > 0; --d) {
         const bool all = std::all_of(B->inst.begin(), B->inst.end(), [d](const pfc_handle *h) {
             return d + 1 >= h->nlev || small_level(h, d);
@@ -634,11 +644,8 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
             if (l == 0 && B->pair) m.u = B->inst[i]->lev[0].u2;
             (l + 1 < nlev[i] ? B->h_mid[l] : B->h_bot[l]).push_back(m);
         }
-    auto upload = [&](const std::vector<BSeg> &v, BSeg **d) -> bool {
-        if (v.empty()) {
-            *d = nullptr;
-            return true;
-        }
+    Tables tables;
+    auto add = [&](const std::vector<BSeg> &v, BSeg **d) {
         std::vector<BSeg> w = v;  // with this list's first tiles
         for (int kind = 0; kind < BK_KINDS; ++kind)
             for (int sh = 0; sh < kShapes; ++sh) {
@@ -655,18 +662,18 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
                 acc += batch_ptile_count(g, zi);
             }
         }
-        return balloc(B, d, w.size()) &&
-               hipMemcpy(*d, w.data(), w.size() * sizeof(BSeg), hipMemcpyHostToDevice) == hipSuccess;
+        tables.add(w, d);
     };
     B->d_all.resize(B->maxdepth);
     B->d_mid.resize(B->maxdepth);
     B->d_bot.resize(B->maxdepth);
-    for (int d = 0; d < B->maxdepth && ok; ++d)
-        ok = upload(B->h_all[d], &B->d_all[d]) && upload(B->h_mid[d], &B->d_mid[d]) &&
-             upload(B->h_bot[d], &B->d_bot[d]);
+    for (int d = 0; d < B->maxdepth; ++d) {
+        add(B->h_all[d], &B->d_all[d]);
+        add(B->h_mid[d], &B->d_mid[d]);
+        add(B->h_bot[d], &B->d_bot[d]);
+    }
     // stop test over the finest levels
     B->ptile = B->maxdepth > 1 && ptile_fits_all(B->h_mid[0]);
-    B->d_norm = B->d_all.empty() ? nullptr : B->d_all[0];
     B->n_norm = count;
     std::vector<unsigned> first(n), nblk(n);
     unsigned acc = 0;
@@ -678,15 +685,16 @@ pfc_status pfc_batch_create(int32_t count, const pfc_config *cfgs, void *stream,
     B->norm_blocks = acc;
     std::vector<int *> valids(n);
     for (int i = 0; i < count; ++i) valids[i] = B->inst[i]->valid64;
-    ok = ok && balloc(B, &B->partial, acc + 16) &&
-         hipMemcpy(nf, first.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(nbk, nblk.data(), n * sizeof(unsigned), hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(B->d_valid, valids.data(), n * sizeof(int *), hipMemcpyHostToDevice) == hipSuccess &&
+    tables.add(first, &B->st.norm_first);
+    tables.add(nblk, &B->st.norm_blocks);
+    tables.add(valids, &B->d_valid);
+    io_tables(B, tables);
+    small_tables(B, tables);
+    ok = balloc(B, &B->partial, acc + 16) && (!B->pair || pair_tables(B, tables)) && tables.put(B) &&
          hipHostMalloc((void **)&B->h_num, n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_stats, 2 * n * sizeof(int), 0) == hipSuccess &&
          hipHostMalloc((void **)&B->h_res, 2 * n * sizeof(double), 0) == hipSuccess;
-    if (ok && B->pair) ok = pair_tables(B);
-    ok = ok && io_tables(B) && small_tables(B);
+    B->d_norm = B->d_all[0];
     if (!ok) {
         delete B;
         return bfail(nullptr, PFC_ERR_OOM, "allocation of batch tables failed");
