@@ -339,8 +339,11 @@ pfc_status pfc_batch_run(pfc_batch *b, int32_t steps, pfc_step_info *infos);
  * workgroup, and tiles of W = 64 .. 1024 consecutive work items of a plane
  * (half-sweep points, coarse cells, fine x-pairs or points, in the level's
  * storage order) over Z = 1 .. 8 consecutive planes, walked plane by plane.
+ * A phase is timed over all depths that run it; one that the batch's cycle does
+ * not launch (tau with nu1 >= 1) keeps its default.
  * With cache_path (nullable) choices are read from / written to a JSON file
- * keyed by GPU architecture, instance sizes and phase.  Where the column
+ * keyed by GPU architecture, instance sizes, sweep counts and phase; other
+ * entries of the file are left as they are.  Where the column
  * tiles apply it then times them with Z = 1, 2, 4 or 8 coarse planes per
  * tile against the chosen coarse-error pass plus interpolation and keeps the
  * faster.  chosen (host, nullable): 20 ints, (persistent, threads, W, Z) per

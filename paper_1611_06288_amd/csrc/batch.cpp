@@ -774,6 +774,8 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
     std::ostringstream sig;
     sig << device_name() << "|" << sizes.size() << ":";
     for (size_t i = 0; i < sizes.size(); ++i) sig << (i ? "," : "") << sizes[i];
+    // (the levels that run a phase depend on the sweep counts)
+    sig << "|nu" << b->cfg.nu1 << "," << b->cfg.nu2;
     static const char *kind_name[5] = {"smooth", "resid_restrict", "tau", "prolong", "coarse_err"};
     std::map<std::string, int> cache;
     if (cache_path) cache = read_cache(cache_path);
@@ -801,6 +803,8 @@ pfc_status pfc_batch_autotune(pfc_batch *b, const char *cache_path, int32_t *cho
         b->slots[kind] = ps ? (unsigned)batch_phase_slots(kind, th, dev) : 0u;
     };
     for (int kind = 0; kind < 5; ++kind) {
+        // with pre-sweeps the cycle forms the tau correction in other launches
+        if (kind == BK_TAU && b->cfg.nu1 >= 1) continue;
         // paired sweeps leave the half-sweeps to the coarser depths
         const bool coarse = kind == BK_SMOOTH && b->pair;
         const std::string key = sig.str() + "|" + kind_name[kind] + (coarse ? "_coarse" : "");
