@@ -146,8 +146,8 @@ pfc_status pfc_init_guess(pfc_handle *h, const double *phi0, double *mu, double 
  * phi_prev or phi_cur.  info (host, nullable) receives the report.
  * Returns NOT_CONVERGED after max_cycles cycles (outputs hold the last
  * iterate, info filled) and NONFINITE if the residual is NaN/Inf.
- * Synchronises the stream (the loop's decisions are read back while a
- * cycle ahead of them runs). */
+ * Synchronises the stream (the loop's decisions are taken on the device and
+ * read back while a cycle runs; the first one before it starts). */
 pfc_status pfc_step(pfc_handle *h, const double *phi_prev, const double *phi_cur,
                     double *phi_next, double *mu, double *omega, pfc_step_info *info);
 
@@ -172,8 +172,8 @@ pfc_status pfc_reset_coarse_cache(pfc_handle *h);
  * residual test before it are recorded once as a hipGraph on a stream the
  * handle owns and replayed, the loop's decisions taken by a kernel; results
  * equal those of calling pfc_step `steps` times, bit for bit (a configuration
- * whose fused sweeps would not return to their buffers over a cycle, odd
- * nu1 + nu2 at n >= 128, and the mixed form run the pfc_step loop instead).
+ * whose sweeps would not return to their buffers over a cycle, an odd number of
+ * sweep launches at n >= 128, and the mixed form run the pfc_step loop instead).
  * Per-kernel timing is not recorded by this call.  Stops at the first step
  * that fails and returns its status (NOT_CONVERGED, NONFINITE: that step's
  * last iterate is the new phi_cur).  Synchronises once or twice per step. */
@@ -366,7 +366,18 @@ const char *pfc_batch_last_error(const pfc_batch *b);
 #define PFC_KERNEL_COUNT 6
 /* When enabled, HIP events bracket each launch of the listed kernels on the
  * handle's stream and their durations are accumulated at every host
- * synchronisation point of the handle. */
+ * synchronisation point of the handle.  How launches that do several of these
+ * things are booked (FP64; the mixed form's FP32 cycle is recorded as a graph
+ * and not timed):
+ *   - two sweeps in one launch (128^3 and more) count as two of SMOOTH0, or as
+ *     one of SWEEP_NORM0 and one of SMOOTH0, half of the time and bytes each;
+ *   - on a finest level of 12^3 to 96^3 with one or two sweeps per side a launch
+ *     holds sweeps with the residual and its coarsening, the interpolation or
+ *     the stop test's norm: SMOOTH0, counted as the half-sweeps it runs (two a
+ *     sweep).  RESIDUAL0, PROLONG0 and NORM0 have no launches of their own then;
+ *   - the launch of the 8^3 (6^3) level and the coarsest together is one of
+ *     COARSE, the upper level's smoothing and transfers included.
+ * SMOOTH0 leaves out the sweeps that ran ahead of the decision to stop. */
 pfc_status pfc_timing_enable(pfc_handle *h, int32_t on);
 /* launches and total milliseconds accumulated for `kernel` since the last
  * reset; bytes_per_launch: the kernel's algorithmic HBM bytes per launch at

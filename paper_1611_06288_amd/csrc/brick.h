@@ -625,12 +625,12 @@ static void brick_one(hipStream_t s, const BrickArgs<T> &a, int kind, int form) 
 template <typename T, int PH, bool DELTA, bool MOB>
 static void brick_launch(hipStream_t s, const BrickArgs<T> &a, int kind, int sweeps, int form) {
     const int n = a.op.lay.n;
-    if (n == kBrickPairN)
-        brick_two<BrickBox<8, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
-    else if (brick_small(n))
-        brick_two<BrickBox<4, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
-    else
+    if (!brick_small(n))
         brick_one<BrickBox<8, 8, 8>, T, PH, DELTA, MOB>(s, a, kind, form);
+    else if (brick_wide(n))
+        brick_two<BrickBox<8, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
+    else
+        brick_two<BrickBox<4, 4, 4>, T, PH, DELTA, MOB>(s, a, kind, sweeps, form);
 }
 
 }  // namespace pfc

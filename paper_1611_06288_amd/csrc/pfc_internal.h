@@ -184,11 +184,14 @@ struct BrickBox {
     static constexpr int X = BX, Y = BY, Z = BZ;
     static int blocks(int n) { return (n / BX) * (n / BY) * (n / BZ); }
 };
-constexpr int kBrickPairN = 32;  // 8 x 4 x 4 boxes: one per CU
+// 8 x 4 x 4 boxes where the 4^3 ones are more than the device's CUs, of which then
+// some run two and share their cycles (of the levels up to 32^3 that one: 512).
+constexpr int kCUs = 256;
+inline bool brick_wide(int n) { return n % 8 == 0 && BrickBox<4, 4, 4>::blocks(n) > kCUs; }
 inline int brick_blocks(int n) {
-    return n == kBrickPairN ? BrickBox<8, 4, 4>::blocks(n)
-           : brick_small(n) ? BrickBox<4, 4, 4>::blocks(n)
-                            : BrickBox<8, 8, 8>::blocks(n);
+    return !brick_small(n) ? BrickBox<8, 8, 8>::blocks(n)
+           : brick_wide(n) ? BrickBox<8, 4, 4>::blocks(n)
+                           : BrickBox<4, 4, 4>::blocks(n);
 }
 // sweeps of the launch: 1 or, with small boxes, 2
 void launch_brick64(hipStream_t s, const BrickArgs<double> &a, int kind, int sweeps, int form);

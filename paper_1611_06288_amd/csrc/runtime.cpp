@@ -340,11 +340,11 @@ static void pair64(pfc_handle *H, int l, int nrm, bool then_sweep, bool tau = fa
     std::swap(A.u, A.u2);
 }
 
-void sweeps64(pfc_handle *H, int l, int from, int count, int nrm, bool tau) {
+void sweeps64(pfc_handle *H, int l, int from, int count, bool norm, bool tau) {
     for (int s = from; s < count;) {
         const bool two = H->lev[l].pair && s + 1 < count;
         const int e = s + (two ? 2 : 1);
-        const int q = (nrm & 1) && s == from ? 1 : (nrm & 2) && e == count ? 2 : 0;
+        const int q = norm && e == count ? 2 : 0;
         if (two)
             pair64(H, l, q, e < count, tau && s == 0);
         else
@@ -471,7 +471,7 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
         return;
     }
     Level &B = H->lev[l + 1];
-    sweeps64(H, l, (flags & kCyclePreDone) ? ahead_sweeps(H) : 0, H->cfg.nu1, 0, flags & kCycleTauSweep);
+    sweeps64(H, l, (flags & kCyclePreDone) ? ahead_sweeps(H) : 0, H->cfg.nu1, false, flags & kCycleTauSweep);
     H->begin_timed(PFC_KERNEL_RESIDUAL0, l);
     if (A.rt) {
         ResidTileArgs ra;
@@ -501,7 +501,7 @@ void cycle64(pfc_handle *H, int l, bool fcycle, unsigned flags) {
     launch_prolong<double>(H->stream, B.lay, A.lay, cst(B.u), cst(B.ubar), A.u, H->gate,
                            H->cfg.nu2 >= 1, A.pz[0]);
     H->end_timed();
-    sweeps64(H, l, 0, H->cfg.nu2, (flags & kCyclePostNorm) ? 2 : 0);
+    sweeps64(H, l, 0, H->cfg.nu2, flags & kCyclePostNorm);
 }
 
 void restrict_phk(pfc_handle *H) {

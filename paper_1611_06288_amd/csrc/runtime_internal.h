@@ -97,7 +97,7 @@ struct pfc_handle {
     double *minv_adj = nullptr;  // cached coarsest inverse of the adjoint solve
     int *valid_adj = nullptr;
     double *energy_part = nullptr;
-    // stop test split over the finest level's fused sweeps (FP64, M = 1): the
+    // stop test split over the finest level's fused sweeps (FP64): the
     // last post-sweep of a cycle leaves the colour-1 half of the norm in
     // partial[split_pre .. split_pre + split_post), the next cycle's first
     // pre-sweep (with the second, where two take one launch), run ahead of
@@ -188,10 +188,9 @@ inline Tri<const double> frhs(const pfc_handle *H, int l) {
 void sweep64(pfc_handle *H, int l, int nrm = 0, bool then_sweep = false,
              bool tau = false);
 // Sweeps from .. count - 1 of one side of the descent, in pairs where the level
-// takes two per launch.  nrm: bit 0 asks the first for the colour-0 half of the
-// norm of its input, bit 1 the last for the colour-1 half of its output; tau:
-// sweep 0 forms the tau correction.
-void sweeps64(pfc_handle *H, int l, int from, int count, int nrm = 0, bool tau = false);
+// takes two per launch.  norm: the last one leaves the colour-1 half of the norm of
+// its output; tau: sweep 0 forms the tau correction.
+void sweeps64(pfc_handle *H, int l, int from, int count, bool norm = false, bool tau = false);
 // The pre-sweeps that run ahead of the loop's decision (split_norm): the first,
 // or the first two where they take one launch.  One exchange of the iterate
 // buffers, so exchanging them back drops the launch.

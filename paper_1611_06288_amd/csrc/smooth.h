@@ -8,17 +8,8 @@
 namespace pfc {
 
 // ------------------------------------------------------------- smoothing
-//
-// Pointwise solve of the three equations of N(u) = f at one point with the
-// six neighbours held (Section 5 smoothing scheme, M = 1):
-//     phi + A mu             = r1     A = 6 tau/h^2, r1 = f1 + tau S_mu/h^2
-//    -c phi + mu + B omega   = r2     B = 6/h^2,     r2 = f2 + S_om/h^2 + (lin.)
-//     Dd phi + omega         = r3     Dd = 3/h^2,    r3 = f3 + S_phi/(2h^2)
-// (first-order scheme: Dd = 6/h^2, r3 = f3 + S_phi/h^2).
-// c is the linearised slope of the cubic term; eliminating omega and mu gives
-// phi = (r1 - A r2 + A B r3) / (1 + A (c + B Dd)).
-// One thread per point of colour `colour` (colour-split storage only).
-// The level's coefficients in that solve.
+
+// The level's coefficients in the pointwise solve below.
 struct PointCoef {
     double h2inv, tau, lin_c, w3, A, AB, B, Dd, BD;
     int fo;
@@ -35,6 +26,15 @@ struct PointCoef {
     }
 };
 
+// Pointwise solve of the three equations of N(u) = f at one point with the
+// six neighbours held (Section 5 smoothing scheme, M = 1):
+//     phi + A mu             = r1     A = 6 tau/h^2, r1 = f1 + tau S_mu/h^2
+//    -c phi + mu + B omega   = r2     B = 6/h^2,     r2 = f2 + S_om/h^2 + (lin.)
+//     Dd phi + omega         = r3     Dd = 3/h^2,    r3 = f3 + S_phi/(2h^2)
+// (first-order scheme: Dd = 6/h^2, r3 = f3 + S_phi/h^2).
+// c is the linearised slope of the cubic term; eliminating omega and mu gives
+// phi = (r1 - A r2 + A B r3) / (1 + A (c + B Dd)).  (tail.h has these operations in
+// two parts, for the reason given there; a change here belongs there too.)
 template <bool DELTA>
 __device__ __forceinline__ void point_solve(const PointCoef &q, int picard, double phin, double a,
                                             double b, double f1, double f2, double f3, double smu,
@@ -91,6 +91,7 @@ __device__ __forceinline__ void point_solve_mob(const OpParams &op, int picard, 
     mu = r2 + c * phi - B * om;
 }
 
+// One point of a half-sweep, the t-th of colour `colour` (colour-split storage only).
 // PK1: f.a is phi^k itself (one buffer), loaded once.
 // TAU (the first sweep on a coarse level): the point's right-hand side first
 // takes the tau correction, f + N(I u) with I u = uo, written back through

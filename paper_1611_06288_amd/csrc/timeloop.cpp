@@ -14,12 +14,12 @@
 // the host round trips drop from one per cycle to one or two per step and the
 // launches of a cycle go out as one graph.
 //
-// With the split stop test (FP64, M = 1, fused finest level) the recorded
-// unit is instead: the next cycle's first finest-level pre-sweep, which also
-// yields the colour-0 half of the norm of its input, then the decision on
-// both halves, then the rest of the cycle, whose last post-sweep leaves the
-// colour-1 half for the next replay.  A replay that stops leaves the iterate
-// in the pre-sweep's input buffer, which the sweep does not write.  Before a
+// With the split stop test (finest level of 128^3 and more) the recorded unit
+// is instead: the next cycle's first finest-level pre-sweeps, which also yield the
+// colour-0 half of the norm of their input, then the decision on both halves,
+// then the rest of the cycle, whose last post-sweep leaves the colour-1 half
+// for the next replay.  A replay that stops leaves the iterate in the
+// pre-sweeps' input buffer, which their launch does not write.  Before a
 // step's first replay the colour-1 half is seeded with the whole-level norm.
 //
 // On a brick finest level the recorded unit is the whole part before the
