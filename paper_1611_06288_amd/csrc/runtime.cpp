@@ -141,6 +141,10 @@ bool dalloc_bytes(pfc_handle *H, void **p, size_t bytes) {
         return true;
     }
     if (need < kOwnBlock && need <= H->arena_left) {
+        if (!H->arena) {
+            if (hipMalloc((void **)&H->arena, H->arena_left) != hipSuccess) return false;
+            H->allocs.push_back(H->arena);
+        }
         *p = H->arena;
         H->arena += need;
         H->arena_left -= need;
@@ -700,15 +704,9 @@ pfc_status create_handle(const pfc_config *cfg, void *stream, HandleUse use, pfc
     level_sizes(cfg->n, sizes);
     plan_levels(H, sizes, use);
     H->planning = true;
-    bool ok = alloc_levels(H, use);
+    (void)alloc_levels(H, use);
     H->planning = false;
-    if (hipMalloc((void **)&H->arena, H->arena_left) != hipSuccess) {
-        H->arena = nullptr;
-        ok = false;
-    } else {
-        H->allocs.push_back(H->arena);
-    }
-    ok = ok && alloc_levels(H, use);
+    bool ok = alloc_levels(H, use);
     if (ok && hipHostMalloc((void **)&H->h_pin, 64 * sizeof(double), 0) != hipSuccess) {
         H->h_pin = nullptr;
         ok = false;
