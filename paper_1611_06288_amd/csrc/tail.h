@@ -3,7 +3,8 @@
 // As launches of their own these two levels took seven dependent launches of
 // 2.5-6.5 us per V-cycle (29 us) for 0.3 us of arithmetic; here a half-sweep
 // costs one LDS round trip, the point solve's chain and a barrier (1370
-// cycles), the whole launch 16 us.  It is bound by those chains: the loads
+// cycles), the whole launch 16-19 us (6^3: 13; the adjoint's 14; about 210 where
+// the coarsest inverse is formed).  It is bound by those chains: the loads
 // 5000 cycles, eight half-sweeps 11000-14000, the coarsest solve 3500-6000 per
 // iteration.  One thread per point and half-sweep (four waves at 8^3): two
 // points per thread in two waves measured 24 us.  Every value is computed by the
