@@ -353,9 +353,24 @@ pfc_status adjoint_step(pfc_handle *H, const double *phi_prev, const double *phi
     if (!std::isfinite(bnorm)) return fail(H, PFC_ERR_NONFINITE, "gbar_next is not finite");
     int c = 0;
     pfc_status status = PFC_OK;
-    if (bnorm > 0.0) {  // the first unit tests |b| itself
+    const double tol = adj_tol * bnorm;
+    if (H->nlev == 1) {  // solved in one cycle: the host decides (4^3 285 us in units, here 251)
+        for (double rho = bnorm; rho > tol; ++c) {
+            if (c == H->cfg.max_cycles) {
+                status = PFC_ERR_NOT_CONVERGED;
+                break;
+            }
+            adj_cycle(H, 0, H->cfg.cycle == PFC_CYCLE_F, false);
+            st = read_norm(H, adj_norm(H), &rho);
+            if (st != PFC_OK) return st;
+            if (!std::isfinite(rho)) {
+                status = PFC_ERR_NONFINITE;
+                ++c;
+                break;
+            }
+        }
+    } else if (bnorm > 0.0) {  // the first unit tests |b| itself
         RunHost r{};
-        const double tol = adj_tol * bnorm;
         st = run_units(
             H, tol, bnorm,
             [&](int i, bool ride) { unit_stop_test(H, i & 1, parts, tol, A.brick && ride); },
